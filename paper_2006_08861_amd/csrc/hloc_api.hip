@@ -423,8 +423,22 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
   // wide regions: chunks the wide kernel of this screen takes
   const bool rs = fmt && lp_wide_rs(fmt, db->dp);
   const int32_t wide_rows = rs ? kWideRowsRs : std::min(db->tile_rows, kWideRows);
-  HIPCHK(launch_sched(regions, p.nq, p.nr, db->R, db->reg_start, db->tile_rows, wide_rows,
-                      rs ? kWideRunsRs : 1,
+  SchedCut cut{};
+  cut.T = db->tile_rows;
+  cut.W = wide_rows;
+  cut.WM = rs ? kWideRunsRs : 1;
+  // the LDS-stage wide kernels run a group per wave, the register-row kernels
+  // one group of the whole block; the other lengths have no wide kernel, and
+  // their one kernel gets by with the coarsest cut
+  const bool lds_wide = !rs && (fmt || f32_wide_supports(db->dp));
+  cut.log_gu = lds_wide ? 2 : 0;
+  cut.max_steps = lds_wide ? kListFrames / (4 * kGroup) : kWideSteps;
+  cut.max_items = (int32_t)p.items_bound;
+  // about two items for each of the blocks that run at once (two per compute
+  // unit)
+  cut.steps_scale =
+      rs || lds_wide ? 1.f / ((float)(cut.W << cut.log_gu) * (float)(2 * 2 * db->num_cu)) : 1e30f;
+  HIPCHK(launch_sched(regions, p.nq, p.nr, db->R, db->reg_start, cut,
                       as<int32_t>(ws->rcount), as<int32_t>(ws->rfill), as<int32_t>(ws->vord),
                       as<int32_t>(ws->rq_off),
                       as<int32_t>(ws->item_off), cand_off, as<int32_t>(ws->slot_row),

@@ -45,6 +45,53 @@ __device__ __forceinline__ double lane_xor_f64(double v, int o) {
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// v moved between lanes by a DPP control (VALU, no LDS); lanes without a
+// source, or outside the row mask, get 0.
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ int dpp_or0(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+
+// Inclusive sum over the wave: within rows of 16 lanes (row_shr 1, 2, 4, 8),
+// then lane 15 of rows 0 and 2 into the next row (row_bcast15), then lane 31
+// into rows 2 and 3 (row_bcast31). A shuffle scan goes through LDS six times
+// in a row instead.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += dpp_or0<0x111>(v);
+  v += dpp_or0<0x112>(v);
+  v += dpp_or0<0x114>(v);
+  v += dpp_or0<0x118>(v);
+  v += dpp_or0<0x142, 0xa>(v);
+  v += dpp_or0<0x143, 0xc>(v);
+  return v;
+}
+
+// The same for a float (a fixed order of additions); lane 63 holds the sum.
+__device__ __forceinline__ float wave_incl_scan_f32(float v) {
+  v += __int_as_float(dpp_or0<0x111>(__float_as_int(v)));
+  v += __int_as_float(dpp_or0<0x112>(__float_as_int(v)));
+  v += __int_as_float(dpp_or0<0x114>(__float_as_int(v)));
+  v += __int_as_float(dpp_or0<0x118>(__float_as_int(v)));
+  v += __int_as_float(dpp_or0<0x142, 0xa>(__float_as_int(v)));
+  v += __int_as_float(dpp_or0<0x143, 0xc>(__float_as_int(v)));
+  return v;
+}
+
+// Block sums of each wave's total (at most 16 waves; tot[w] written by the
+// caller before a barrier): the sum over the waves before this one, and over
+// all of them. Every lane of the wave must call this.
+__device__ __forceinline__ int waves_before(const int *tot, int w, int nw, int *all) {
+  const int lane = lane_id();
+  int t = lane < nw ? tot[lane] : 0;
+  t += dpp_or0<0x111>(t);
+  t += dpp_or0<0x112>(t);
+  t += dpp_or0<0x114>(t);
+  t += dpp_or0<0x118>(t);
+  *all = __builtin_amdgcn_readlane(t, 15);
+  const int before = __builtin_amdgcn_readlane(t, w > 0 ? __builtin_amdgcn_readfirstlane(w) - 1 : 0);
+  return w > 0 ? before : 0;
+}
+
 // Smallest of one frame's 16 screen words of a 16-row block, as the MFMA
 // tile holds them: lane l has frame l % 16 and rows 4 (l / 16) .. + 3 in wd
 // (0xFFFFFFFF for rows past the end). The lanes of one frame exchange across

@@ -45,7 +45,7 @@ constexpr int kListFrames = 1024;   // frames per wide list item (rows re-read o
 constexpr int kWideRows = 64;       // rows per wide work item (the LDS stage of the wide kernels)
 constexpr int kWideRowsRs = 128;    // rows per run of the register-row kernels (bf16, fp8)
 constexpr int kWideRunsRs = 16;     // runs of kWideRowsRs rows per wide item at most
-constexpr int kWideSteps = 32;      // (run, 16-frame group) steps a multi-run wide item aims at
+constexpr int kWideSteps = 32;      // (run, 16-frame group) steps of a register-row wide item at most
 constexpr int kMaxItemRows = 128;   // rows per narrow work item at most
 constexpr int kBlock = 256;         // threads per block of most kernels
 constexpr int kSelectLds = 4096;    // keys held in LDS by the select kernel
@@ -105,8 +105,9 @@ struct ScreenArgs {
   // frame_list[0 .. *frame_count), each writing its own row of cand
   const int32_t *frame_list;
   const int32_t *frame_count;
-  // register-row wide screen: 8 item counters, zero on entry, one per XCD
-  // span of the items (NULL: each block takes a fixed share of its span)
+  // register-row wide screen: 8 item counters kItemCtrStride apart, zero on
+  // entry, one per XCD span of the items (NULL: each block takes a fixed
+  // share of its span)
   int32_t *item_ctr;
 };
 
@@ -173,10 +174,13 @@ __device__ __forceinline__ int2 wide_entry(const ScreenArgs &a, const WideItem &
 }
 
 // Per-batch counters of a workspace (cleared by the prep kernel): [0] items,
-// [1] coarse fallbacks, [4] narrow items, [8] large aggregation lists, [10]
-// deferred coarse frames, [16, 24) the wide screen's item counters.
-constexpr int kMiscInts = 32;
-constexpr int kMiscItemCtr = 16;
+// [1] coarse fallbacks, [4] narrow items, [5] steps per wide item, [8] large
+// aggregation lists, [10] deferred coarse frames, from [kMiscItemCtr] on the wide screen's item
+// counters, one per XCD, each on a cache line of its own: on one line the
+// blocks' additions queue up behind each other.
+constexpr int kItemCtrStride = 32;
+constexpr int kMiscItemCtr = 32;
+constexpr int kMiscInts = kMiscItemCtr + 8 * kItemCtrStride;
 
 // Padded copy and squared norm of each frame; block 0 also clears
 // zero[0 .. kMiscInts).
@@ -219,11 +223,18 @@ hipError_t launch_broadcast_ids(const int32_t *ids, int32_t nr, int32_t nq, int3
 // 16-row blocks in the frame's block list, slot_row[f][j] the region's first
 // row, slot_len[f][j] its rows; n_cand[f] the frame's block count, n_rows[f]
 // its candidate rows. An rq
-// entry is (frame, cand_off of the region in that frame). Narrow chunks hold
-// T rows; wide chunks W rows, or with WM > 1 up to WM runs of W rows.
+// entry is (frame, cand_off of the region in that frame).
+// How the items are cut: narrow chunks hold T rows; wide chunks W rows, or
+// with WM > 1 up to WM runs of W rows, against whole units of 2^log_gu groups
+// of kGroup frames (the groups the wide kernel's block takes at once). With S
+// (row, group) pairs over all wide regions an item aims at S * steps_scale
+// (W rows, unit) steps, max_steps at most; at most max_items items in all.
+struct SchedCut {
+  int32_t T, W, WM, log_gu, max_steps, max_items;
+  float steps_scale;
+};
 hipError_t launch_sched(const int32_t *regions, int32_t nq, int32_t nr, int32_t R,
-                        const int64_t *reg_start, int32_t T, int32_t W, int32_t WM,
-                        int32_t *rcount,
+                        const int64_t *reg_start, const SchedCut &sc, int32_t *rcount,
                         int32_t *rfill,
                         int32_t *vord, int32_t *rq_off, int32_t *item_off, int32_t *cand_off,
                         int32_t *slot_row, int32_t *slot_len, int32_t *n_cand, int32_t *n_rows,

@@ -45,93 +45,142 @@ __device__ __forceinline__ int owner_slot(const int32_t *iof, int R, int t) {
   return lo;
 }
 
-// Rows per chunk of a region kept by g frames: T for narrow regions, W (what
-// the wide kernel of the screen takes) for wide ones. With WM > 1 a wide
-// chunk is up to WM runs of W rows (the register-row kernels take such an
-// item run by run with its frames staged once), as many as bring the item to
-// about kWideSteps (W rows, kGroup frames) steps: items of few frame groups
-// then carry enough work to hide their set-up.
-__device__ __forceinline__ int chunk_rows(int g, int T, int W, int WM) {
-  if (g <= kGroup) return T;
-  const int groups = (min(g, kListFrames) + kGroup - 1) / kGroup;
-  return W * max(1, min(WM, (kWideSteps + groups - 1) / groups));
+// How a region of `rows` rows kept by g frames is cut into items: chunks of
+// rows, each against runs of frames.
+struct Cut {
+  int rows, frames, nrun;
+};
+
+// Narrow regions: chunks of T rows, one run of frames. Wide regions: the unit
+// of work is a step, W rows against c.gu groups of kGroup frames; an item aims
+// at `target` of them, first by its frames (their rows are read again for
+// every further run), then, with WM > 1 (the register-row kernels take such
+// an item W rows at a time with its frames staged once), by up to WM runs of
+// W rows, so that items of few frames still hide their set-up.
+// (Not inlined, here and below: one block runs this code once, and its
+// instruction fetches cost more than the calls.)
+__device__ __noinline__ Cut cut_region(int g, SchedCut c, int target) {
+  Cut k;
+  k.rows = c.T;
+  k.frames = kListFrames;
+  k.nrun = 1;
+  if (g <= kGroup) return k;
+  const int most = kListFrames / kGroup;
+  const int groups = (g + kGroup - 1) / kGroup;
+  int gi = target >= c.max_steps ? most : min(most, target << c.log_gu);
+  if (groups > gi) {
+    // even runs of whole units
+    k.nrun = (groups + gi - 1) / gi;
+    gi = min(most, ((groups + k.nrun - 1) / k.nrun + (1 << c.log_gu) - 1) >> c.log_gu << c.log_gu);
+    k.nrun = (groups + gi - 1) / gi;
+  }
+  k.frames = gi * kGroup;
+  const int steps = (min(groups, gi) + (1 << c.log_gu) - 1) >> c.log_gu;
+  k.rows = c.W * max(1, min(c.WM, (min(target, c.max_steps) + steps - 1) / steps));
+  return k;
 }
 
-__device__ __forceinline__ int items_of(int g, int64_t rows, int T, int W, int WM) {
-  const int C = chunk_rows(g, T, W, WM);
-  return g > 0 ? (int)((rows + C - 1) / C) * ((g + kListFrames - 1) / kListFrames) : 0;
+__device__ __forceinline__ int items_of(int g, int rows, const SchedCut &c, int target) {
+  if (g <= 0) return 0;
+  const Cut k = cut_region(g, c, target);
+  return (rows + k.rows - 1) / k.rows * k.nrun;
 }
 
 // Work item t of a region whose rows are [r0, r0 + rows) and whose frames are
-// rq[q_begin, q_end): chunk-major, frame groups inner, so consecutive items
+// rq[q_begin, q_end): chunk-major, frame runs inner, so consecutive items
 // re-read the same rows.
 __device__ __forceinline__ Item make_item(int t, int item_begin, int q_begin, int q_end, int r0,
-                                          int rows, int T, int W, int WM) {
-  const int g = q_end - q_begin, ngr = (g + kListFrames - 1) / kListFrames;
-  const int C = chunk_rows(g, T, W, WM);
-  const int local = t - item_begin, c = local / ngr, b = local - c * ngr;
+                                          int rows, const SchedCut &sc, int target) {
+  const int g = q_end - q_begin;
+  const Cut k = cut_region(g, sc, target);
+  const int local = t - item_begin, c = local / k.nrun, b = local - c * k.nrun;
   Item it;
-  it.row_begin = r0 + c * C;
-  it.chunk_row = c * C;
-  it.q0 = q_begin + b * kListFrames;
-  it.nrows_gq = (min(C, rows - c * C) << 16) | min(kListFrames, g - b * kListFrames);
+  it.row_begin = r0 + c * k.rows;
+  it.chunk_row = c * k.rows;
+  it.q0 = q_begin + b * k.frames;
+  it.nrows_gq = (min(k.rows, rows - c * k.rows) << 16) | min(k.frames, g - b * k.frames);
   return it;
 }
 
 // Block-wide (blockDim.x <= 1024) scans over the regions, each thread taking a
 // contiguous range of them: rq_off (R + 1, first frame of each region in id
 // order), vord / iof (the regions in narrow-then-wide order and their first
-// item), n_items[0] (all items) and n_items[4] (narrow items). With fill set,
-// fill[r] = rq_off[r]. count may alias fill. s_red holds 72 ints of LDS.
+// item), n_items[0] (all items), n_items[4] (narrow items) and n_items[5] (the
+// step target of the wide items). With fill set, fill[r] = rq_off[r]. count
+// may alias fill. s_red holds 81 ints of LDS.
 // reg_start: first row of each region (R + 1 entries, device or LDS).
+//
+// Step target: S steps over all wide regions make items of c.steps_scale S
+// (about two for each block that runs at once, to balance with), up to
+// max_steps, where a longer item gains nothing more. Items used to be cut for
+// max_steps whatever S: a batch of 2,048 frames on 500k x 512 bf16 rows then
+// had 408 wide items for 512 blocks, and the longest set the launch's time;
+// with this cut (and item counters on lines of their own) the launch takes
+// 105 us instead of 169, 67 instead of 134 on fp8 rows (2,048 frames of 256
+// requests), and 256 frames of one video on 200k x 256 fp32 rows (18 regions
+// kept by all) 10.5 instead of 30. The host sizes the item buffer for the cut
+// at max_steps (c.max_items): a finer cut that does not fit falls back to it.
 template <class RS>
 __device__ void sched_scan(const int32_t *count, int R, const RS *__restrict__ reg_start,
-                           int T, int W, int WM, int32_t *rq_off, int32_t *vord, int32_t *iof,
+                           const SchedCut &c, int32_t *rq_off, int32_t *vord, int32_t *iof,
                            int32_t *n_items, int32_t *fill, int *s_red) {
   const int tid = threadIdx.x, nt = blockDim.x;
   const int per = (R + nt - 1) / nt;
   const int r0 = min(R, tid * per), r1 = min(R, r0 + per);
-  // frames, narrow items, wide items, narrow regions
-  int v[4] = {0, 0, 0, 0};
-  for (int r = r0; r < r1; ++r) {
-    const int g = count[r];
-    const int m = items_of(g, reg_start[r + 1] - reg_start[r], T, W, WM);
-    v[0] += g;
-    if (g <= kGroup) {
-      v[1] += m;
-      v[3] += 1;
+  const int lane = tid & 63, wv = tid >> 6, nw = nt >> 6;
+  // first the cut at max_steps, with the sum of the steps beside it; if that
+  // asks for shorter items, the cut again
+  int target = c.max_steps;
+  int v[4], inc[4], all[4];
+#pragma unroll 1
+  for (int pass = 0;; ++pass) {
+    // frames, narrow items, wide items, narrow regions
+    v[0] = v[1] = v[2] = v[3] = 0;
+    float steps = 0.f;  // (an estimate is enough: the cut never changes a result)
+#pragma unroll 1
+    for (int r = r0; r < r1; ++r) {
+      const int g = count[r], rows = reg_start[r + 1] - reg_start[r];
+      const int m = items_of(g, rows, c, target);
+      v[0] += g;
+      if (g <= kGroup) {
+        v[1] += m;
+        v[3] += 1;
+      } else {
+        v[2] += m;
+        steps += (float)(rows + c.W - 1) * (float)((g + kGroup - 1) / kGroup + (1 << c.log_gu) - 1);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) inc[q] = wave_incl_scan(v[q]);
+    steps = wave_incl_scan_f32(steps);
+    if (lane == 63) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s_red[q * 16 + wv] = inc[q];
+      s_red[64 + wv] = __float_as_int(steps);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) inc[q] += waves_before(s_red + q * 16, wv, nw, &all[q]);
+    steps = lane < nw ? __int_as_float(s_red[64 + lane]) : 0.f;
+    steps = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_incl_scan_f32(steps)), 63));
+    // (uniform from here on)
+    const bool fits = all[1] + all[2] <= c.max_items;
+    if (pass == 0 && all[2] > 0) {
+      target = (int)fminf(fmaxf(steps * c.steps_scale, 1.f), (float)c.max_steps);
+      if (target >= c.max_steps) break;
+    } else if (pass != 1 || fits) {
+      break;
     } else {
-      v[2] += m;
+      target = c.max_steps;
     }
+    __syncthreads();
   }
-  const int lane = tid & 63, wv = tid >> 6;
-  int inc[4] = {v[0], v[1], v[2], v[3]};
-  for (int o = 1; o < 64; o <<= 1) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int y = __shfl_up(inc[q], o);
-      if (lane >= o) inc[q] += y;
-    }
-  }
-  if (lane == 63) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) s_red[q * 16 + wv] = inc[q];
-  }
-  __syncthreads();
-  for (int i = 0; i < wv; ++i) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) inc[q] += s_red[q * 16 + i];
-  }
-  if (tid == nt - 1) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) s_red[64 + q] = inc[q];
-  }
-  __syncthreads();
-  const int BN = s_red[65], CN = s_red[67];
+  const int BN = all[1], CN = all[3];
   int pa = inc[0] - v[0], pbn = inc[1] - v[1], pbw = inc[2] - v[2], pcn = inc[3] - v[3];
+#pragma unroll 1
   for (int r = r0; r < r1; ++r) {
     const int g = count[r];
-    const int m = items_of(g, reg_start[r + 1] - reg_start[r], T, W, WM);
+    const int m = items_of(g, reg_start[r + 1] - reg_start[r], c, target);
     rq_off[r] = pa;
     if (fill) fill[r] = pa;
     pa += g;
@@ -153,6 +202,8 @@ __device__ void sched_scan(const int32_t *count, int R, const RS *__restrict__ r
     iof[R] = inc[1] + inc[2];
     n_items[0] = inc[1] + inc[2];
     n_items[4] = inc[1];
+    n_items[5] = target;
+    s_red[80] = target;
   }
 }
 
@@ -247,12 +298,12 @@ __global__ void k_sched_count(const int32_t *__restrict__ regions, int nq, int n
 
 // One block: the scans of sched_scan over the region counts; clears rfill.
 __global__ __launch_bounds__(1024) void k_sched_scan(const int32_t *__restrict__ rcount, int R,
-                                                     const int64_t *__restrict__ reg_start, int T, int W, int WM,
+                                                     const int64_t *__restrict__ reg_start, SchedCut sc,
                                                      int32_t *rq_off, int32_t *vord,
                                                      int32_t *iof, int32_t *n_items,
                                                      int32_t *rfill) {
-  __shared__ int s_red[72];
-  sched_scan(rcount, R, reg_start, T, W, WM, rq_off, vord, iof, n_items, nullptr, s_red);
+  __shared__ int s_red[81];
+  sched_scan(rcount, R, reg_start, sc, rq_off, vord, iof, n_items, nullptr, s_red);
   for (int r = threadIdx.x; r < R; r += blockDim.x) rfill[r] = 0;
 }
 
@@ -290,14 +341,15 @@ __global__ void k_sched_scatter(const int32_t *__restrict__ regions, int nq, int
 __global__ void k_sched_items(int R, const int32_t *__restrict__ vord,
                               const int32_t *__restrict__ iof,
                               const int32_t *__restrict__ rq_off,
-                              const int64_t *__restrict__ reg_start, int T, int W, int WM, Item *items) {
-  const int n = iof[R];
+                              const int64_t *__restrict__ reg_start, SchedCut sc,
+                              const int32_t *__restrict__ n_items, Item *items) {
+  const int n = iof[R], target = n_items[5];
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
     const int k = owner_slot(iof, R, t);
     const int r = vord[k];
     const int64_t r0 = reg_start[r];
-    items[t] = make_item(t, iof[k], rq_off[r], rq_off[r + 1], (int)r0, (int)(reg_start[r + 1] - r0), T,
-                         W, WM);
+    items[t] = make_item(t, iof[k], rq_off[r], rq_off[r + 1], (int)r0, (int)(reg_start[r + 1] - r0), sc,
+                         target);
   }
 }
 
@@ -317,7 +369,7 @@ size_t fused_lds_bytes(int R) { return (size_t)(4 * R + 2) * sizeof(int); }
 
 __global__ __launch_bounds__(1024) void k_sched_fused(const int32_t *__restrict__ regions, int nq,
                                                       int nr, int R,
-                                                      const int64_t *__restrict__ reg_start, int T, int W, int WM,
+                                                      const int64_t *__restrict__ reg_start, SchedCut sc,
                                                       int32_t *rq_off, int32_t *cand_off,
                                                       int32_t *slot_row, int32_t *slot_len,
                                                       int32_t *n_cand,
@@ -328,7 +380,7 @@ __global__ __launch_bounds__(1024) void k_sched_fused(const int32_t *__restrict_
   int *s_vord = s_mem + R;     // R: regions in narrow-then-wide order
   int *s_iof = s_mem + 2 * R;  // R + 1: first item of each slot of s_vord
   int *s_rs = s_mem + 3 * R + 1;  // R + 1: first row of each region
-  __shared__ int s_red[72];
+  __shared__ int s_red[81];
   const int tid = threadIdx.x, nt = blockDim.x;
   // with one frame per thread and at most kFusedRegs regions per frame, the
   // frame's region ids and list offsets stay in registers for the scatter
@@ -390,8 +442,9 @@ __global__ __launch_bounds__(1024) void k_sched_fused(const int32_t *__restrict_
   }
   __syncthreads();
   // counts -> fill pointers (each thread reads and rewrites only its own range)
-  sched_scan(s_fill, R, s_rs, T, W, WM, rq_off, s_vord, s_iof, n_items, s_fill, s_red);
+  sched_scan(s_fill, R, s_rs, sc, rq_off, s_vord, s_iof, n_items, s_fill, s_red);
   __syncthreads();
+  const int target = s_red[80];
   if (regs) {
     if (tid < nq) {
 #pragma unroll
@@ -420,7 +473,7 @@ __global__ __launch_bounds__(1024) void k_sched_fused(const int32_t *__restrict_
     const int k = owner_slot(s_iof, R, t);
     const int rr = s_vord[k];
     const int q0 = rr > 0 ? s_fill[rr - 1] : 0;
-    items[t] = make_item(t, s_iof[k], q0, s_fill[rr], s_rs[rr], s_rs[rr + 1] - s_rs[rr], T, W, WM);
+    items[t] = make_item(t, s_iof[k], q0, s_fill[rr], s_rs[rr], s_rs[rr + 1] - s_rs[rr], sc, target);
   }
 }
 
@@ -431,7 +484,7 @@ hipError_t prepare_sched_kernels() {
 }
 
 hipError_t launch_sched(const int32_t *regions, int32_t nq, int32_t nr, int32_t R,
-                        const int64_t *reg_start, int32_t T, int32_t W, int32_t WM, int32_t *rcount,
+                        const int64_t *reg_start, const SchedCut &sc, int32_t *rcount,
                         int32_t *rfill,
                         int32_t *vord, int32_t *rq_off, int32_t *item_off, int32_t *cand_off,
                         int32_t *slot_row, int32_t *slot_len, int32_t *n_cand, int32_t *n_rows,
@@ -440,7 +493,7 @@ hipError_t launch_sched(const int32_t *regions, int32_t nq, int32_t nr, int32_t 
   const int64_t pairs = (int64_t)nq * nr;
   if (R <= kFusedMaxR && pairs <= kFusedMaxPairs) {
     return launch_kernel(k_sched_fused, dim3(1), dim3(1024), (uint32_t)fused_lds_bytes(R), s,
-                         regions, nq, nr, R, reg_start, T, W, WM, rq_off, cand_off, slot_row,
+                         regions, nq, nr, R, reg_start, sc, rq_off, cand_off, slot_row,
                          slot_len, n_cand, n_rows, n_items, rq, items);
   }
   hipError_t e = launch_fill_i32(rcount, R, 0, s);
@@ -456,7 +509,7 @@ hipError_t launch_sched(const int32_t *regions, int32_t nq, int32_t nr, int32_t 
                              n_cand, n_rows);
     if (e != hipSuccess) return e;
   }
-  if ((e = launch_kernel(k_sched_scan, dim3(1), dim3(1024), 0, s, rcount, R, reg_start, T, W, WM,
+  if ((e = launch_kernel(k_sched_scan, dim3(1), dim3(1024), 0, s, rcount, R, reg_start, sc,
                          rq_off, vord, item_off, n_items, rfill)) != hipSuccess)
     return e;
   if (pairs > 0) {
@@ -468,7 +521,7 @@ hipError_t launch_sched(const int32_t *regions, int32_t nq, int32_t nr, int32_t 
     if (e != hipSuccess) return e;
   }
   return launch_kernel(k_sched_items, dim3(1024), dim3(256), 0, s, R, vord, item_off, rq_off,
-                       reg_start, T, W, WM, items);
+                       reg_start, sc, n_items, items);
 }
 
 }  // namespace hloc

@@ -24,7 +24,8 @@ __global__ __launch_bounds__(256) void k_prep_queries(const float *__restrict__ 
                                                       int dp, float *__restrict__ qp,
                                                       float *__restrict__ qn2,
                                                       int32_t *__restrict__ zero) {
-  if (blockIdx.x == 0 && threadIdx.x < kMiscInts && zero) zero[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && zero)
+    for (int t = threadIdx.x; t < kMiscInts; t += 256) zero[t] = 0;
   const int f = blockIdx.x * 4 + wave_id();
   const int lane = lane_id();
   if (f >= nq) return;

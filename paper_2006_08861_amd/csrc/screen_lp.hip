@@ -494,10 +494,10 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
   const int it0 = lo + x * span, it1 = min(hi, it0 + span);
   // staging: thread t loads pieces (t % TPF) + TPF u of frame t / TPF
   const int sj = tid / TPF, sc = tid % TPF;
-  // With item counters the blocks of XCD x take the items of x's span in
-  // order, one counter increment each, then those left in the other spans
-  // (x + 1, x + 2, ... mod 8), so no block idles while items remain; thread
-  // 0 takes the next item at an item's start and the block reads it after
+  // With item counters block jb of XCD x begins with item jb of x's span; the
+  // blocks then take the span's other items in order, one counter increment
+  // each, then those left in the other spans (x + 1, x + 2, ... mod 8), so no
+  // block idles while items remain; thread 0 takes the next item at an item's start and the block reads it after
   // the item's first barrier (two slots by item parity: the slot thread 0
   // writes was last read before the previous item's set-up barrier). Without
   // them block jb of XCD x takes items it0 + jb, + nb, ...
@@ -508,7 +508,15 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
     while (xs < kXcd) {
       const int xx = x + xs < kXcd ? x + xs : x + xs - kXcd;
       const int b0 = lo + xx * span, b1 = min(hi, b0 + span);
-      const int j = atomicAdd(a.item_ctr + xx, 1);
+      int32_t *ctr = a.item_ctr + xx * kItemCtrStride;
+      // another XCD's span is looked at first: reads of a finished span run
+      // side by side, additions would queue up
+      if (xs > 0 &&
+          b0 + nb + __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= b1) {
+        ++xs;
+        continue;
+      }
+      const int j = nb + atomicAdd(ctr, 1);
       if (b0 + j < b1) return b0 + j;
       ++xs;
     }
@@ -516,9 +524,11 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
   };
   int it = it0 + jb, lim = it1;
   if (dyn) {
-    if (tid == 0) s_nx[0] = grab();
-    __syncthreads();
-    it = s_nx[0];
+    if (it >= it1) {  // more blocks than items in this span
+      if (tid == 0) s_nx[0] = grab();
+      __syncthreads();
+      it = s_nx[0];
+    }
     lim = hi;
   }
   Item nxt = it < lim ? a.items[it] : Item{};

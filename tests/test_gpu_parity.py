@@ -980,3 +980,37 @@ def test_wide_items_with_short_chunks(torch_cuda, rows):
         assert st["recall"] == 1.0 and info["items"] > info["narrow_items"]
     db.close()
 
+
+
+@pytest.mark.parametrize("frames", [17, 33, 70, 1100])
+@pytest.mark.parametrize("d", [64, 256])
+def test_wide_items_cut_for_the_batch(torch_cuda, frames, d):
+    # few wide regions: their items are cut down to single steps (17 frames:
+    # one group and one frame; 33 and 70: runs of unequal groups; 1,100: more
+    # than one item's frames), on chunk remainders of both wide row counts
+    rng = np.random.default_rng(26)
+    sizes = np.array([333, 129, 64] + [40] * 6)
+    region_of = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    n = len(region_of)
+    feats = rng.standard_normal((n, d)).astype(np.float32)
+    feats[:526] *= 0.2  # three regions near the origin, kept by every frame
+    feats[526:] += 0.6
+    xy = rng.uniform(0, 40, size=(n, 2))
+    q = (feats[rng.integers(0, 526, frames)]
+         + 0.05 * rng.standard_normal((frames, d))).astype(np.float32)
+    mirrors = hloc.MIRROR_BF16 | hloc.MIRROR_FP8
+    say(f"[case] three regions kept by {frames} frames, d {d}")
+    db = make_db(feats, xy, region_of, len(sizes), mirrors=mirrors)
+    outs = {p: run_device(torch_cuda, db, q, 9, 3, precision=p) for p in ("fp32", "bf16", "fp8")}
+    info = db.info()
+    regs = db.last_regions()
+    db.close()
+    ora = oracle.localize(feats, xy, region_of, len(sizes), q, np.arange(frames + 1), 9, 3,
+                          (0.5, 1, 0.0, 0))
+    st = judge_frames(outs["fp32"]["idx"], outs["fp32"]["dist"], regs, ora, feats, region_of,
+                      len(sizes), q, 9)
+    say(f"[ok] {st} info={info}")
+    assert st["recall"] == 1.0 and info["items"] > info["narrow_items"]
+    for p in ("bf16", "fp8"):
+        for key in outs[p]:
+            assert outs[p][key].tobytes() == outs["fp32"][key].tobytes(), (p, key)
