@@ -506,6 +506,7 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
     rb.err_coef = coef * lo_fp32;
   }
   rb.nq = p.nq;
+  rb.long_bands = fmt == HLOC_FP8;
   rb.idx_out = idx;
   rb.dist_out = dist;
   rb.frame_stat = as<int4>(ws->fstat);

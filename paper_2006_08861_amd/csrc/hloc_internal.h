@@ -314,6 +314,7 @@ struct SelRerankArgs {
   double lo_nmax;          // largest |d~|
   double lo_coef;
   int32_t nq;
+  int32_t long_bands;      // fine: the screen's error bound leaves hundreds of rows per band
   int64_t *idx_out;        // fine: nq x m original indices
   float *dist_out;         // fine: nq x m
   int32_t *reg_out;        // coarse: nq x m region ids

@@ -1,5 +1,8 @@
-// Top candidates per frame ("select top candidates", Algorithm 1), one block
-// per frame, in one kernel:
+// Top candidates per frame ("select top candidates", Algorithm 1), in one
+// kernel: k_select_frame (W waves per frame) for lists that fit a wave's
+// lanes, k_select_rerank (one block per frame) past them (more than 64 region
+// slots or survivor positions). Both do the same three things; the block
+// kernel's way:
 //   1. select: the L + 1 smallest (screen word, position) pairs, the word
 //      being the float bits of the screen distance (the bits of a
 //      non-negative float order like its value). The words are cached in
@@ -235,7 +238,7 @@ __device__ __forceinline__ double wave_sum8_f64(double (&acc)[kRowBatch]) {
 // chunks per round trip (more registers); otherwise one chunk at a time, and
 // LEAN (1024-thread blocks, at most 128 VGPRs) fetches FP64 rows in halves.
 // The sums are the same either way.
-template <bool LEAN, bool PAIR>
+template <bool LEAN, bool PAIR, bool F32>
 __device__ __forceinline__ void rerank_batch(const SelRerankArgs &a, const float *qrow,
                                              const uint32_t (&row)[kRowBatch],
                                              double (&acc)[kRowBatch]) {
@@ -244,7 +247,7 @@ __device__ __forceinline__ void rerank_batch(const SelRerankArgs &a, const float
   const int tail = a.dp & 255;  // remaining values (multiple of 16)
 #pragma unroll
   for (int r = 0; r < kRowBatch; ++r) acc[r] = 0.0;
-  if (PAIR && a.src32 && (a.dp & 511) == 0) {
+  if (PAIR && F32 && (a.dp & 511) == 0) {
     for (int c = 0; c < nch; c += 2) {
       const int col0 = c * 256 + lane * 4, col1 = col0 + 256;
       float4 y[2], v[2][kRowBatch];
@@ -276,7 +279,7 @@ __device__ __forceinline__ void rerank_batch(const SelRerankArgs &a, const float
     if (c == nch && (tail == 0 || col >= a.dp)) break;
     const float4 y = *reinterpret_cast<const float4 *>(qrow + col);
     const double y0 = y.x, y1 = y.y, y2 = y.z, y3 = y.w;
-    if (a.src32) {
+    if (F32) {
       float4 v[kRowBatch];
 #pragma unroll
       for (int r = 0; r < kRowBatch; ++r)
@@ -346,7 +349,8 @@ __device__ void rerank_rows(const SelRerankArgs &a, const float *qrow, const uin
     const uint32_t rw = (lane & 7) == 0 && sidx < s1 ? srow[sidx] : kNoRow;
     const uint32_t tie = rw != kNoRow && a.tie_of ? (uint32_t)a.tie_of[rw] : rw;
     double acc[kRowBatch];
-    rerank_batch<LEAN, PAIR>(a, qrow, row, acc);
+    if (a.src32) rerank_batch<LEAN, PAIR, true>(a, qrow, row, acc);
+    else rerank_batch<LEAN, PAIR, false>(a, qrow, row, acc);
     const double d = wave_sum8_f64(acc);
     if ((lane & 7) == 0 && sidx < s1) {
       if (rw == kNoRow) {
@@ -1011,27 +1015,6 @@ __global__ __launch_bounds__(BLOCK) void k_select_rerank(SelRerankArgs a) {
   }
 }
 
-// Key mode in one wave per frame: the coarse stage after the fused coarse
-// product when a frame has at most kWaveKeys keys. Its keys are few (the
-// kept quads of each lane group and split), so a whole block per frame would
-// mostly wait at barriers; here each wave takes one frame on its own (four
-// frames per block, no block barrier) and follows the rules of
-// k_select_rerank's key mode: the L smallest (word, position) pairs survive,
-// the (L+1)-th decides the deferral and the certificate, the FP64 distances
-// come from the same per-row arithmetic (rerank_rows), and the band is
-// re-scored the same way, so the regions are the ones the block kernel
-// would return. A band beyond kWaveRows rows defers the frame to the dense
-// screen (exact as well).
-constexpr int kWaveKeys = 256;  // keys per frame held by one wave (4 per lane)
-constexpr int kWaveRows = 64;   // rows re-scored per frame by one wave
-constexpr int kWaveFrames = 4;  // frames (waves) per block
-struct WaveSel {
-  uint32_t krow[kWaveKeys];     // source row of each key
-  uint64_t sort_hi[kWaveRows];  // FP64 distance bits
-  uint32_t sort_lo[kWaveRows];  // tie ids
-  uint32_t srow[kWaveRows];     // rows to re-score
-};
-
 // Orders the wave's LDS accesses before and after (no block barrier).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1039,164 +1022,414 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Sorts sort_hi / sort_lo[0, cnt) (cnt <= 64, distinct pairs) by rank: lane t
-// counts the entries ordered before entry t.
-__device__ __forceinline__ void wave_sort_pairs(WaveSel &sh, int cnt) {
-  const int lane = lane_id();
-  uint64_t hi = kKeyNone;
-  uint32_t lo = 0xFFFFFFFFu;
-  int rank = 0;
-  if (lane < cnt) {
-    hi = sh.sort_hi[lane];
-    lo = sh.sort_lo[lane];
-    for (int j = 0; j < cnt; ++j) {
-      const uint64_t yh = sh.sort_hi[j];
-      const uint32_t yl = sh.sort_lo[j];
-      rank += (yh < hi) | ((yh == hi) & (yl < lo));
-    }
-  }
-  wave_sync();
-  if (lane < cnt) {
-    sh.sort_hi[rank] = hi;
-    sh.sort_lo[rank] = lo;
-  }
-  wave_sync();
+// ------------------------------------------------------------ frame kernel
+// The common case of the selection (up to kFrameL survivor positions, up to
+// kFrameSlots region slots), W waves per frame, with no word cache and few
+// barriers:
+//   * every lane keeps the two smallest words of the positions it reads (the
+//     first kFrameRegs of them stay in registers for the band pass, the rest
+//     are read again); the survivors are the L smallest of those, taken out
+//     one by one with a DPP minimum over the wave, first per wave, then over
+//     the waves' lists. A lane that held three of the L smallest gives one of
+//     them up, which is as exact: the certificate does not ask which
+//     positions were re-scored first;
+//   * the survivors' rows are re-scored in FP64 (rerank_batch: the block
+//     kernel's arithmetic), and the m best (distance, tie id) of them sorted
+//     by counting ranks;
+//   * tau = the m-th distance + the screen's error bound: every position not
+//     yet re-scored with a word up to tau is (the band), kBandBlocks blocks
+//     (or kBandRows rows) at a time, and a row ordered before the m-th best so
+//     far enters the merge. Nothing above tau can enter the m best.
+// Key mode: a band that reaches the words the key lists may have dropped
+// (their smallest bound) defers the frame.
+// The block kernel spends most of its instructions on histograms, scans and
+// sorts over the block (16,700 wave instructions a frame on 2M x 512 bf16 rows,
+// 2,600 of them the re-score) and its word cache is sized for the largest
+// region list, so that the same batch took 1.27 or 3.27 ms by the region
+// sizes drawn (1,024 threads alone on a compute unit from 4,096 blocks on).
+// Here a frame needs some 10 KB of LDS whatever the regions. Block kernel ->
+// this one: 32,768 frames of that shape 1275 (3270) -> 815 us, 2,048 frames on
+// 500k x 512 bf16 107 -> 63, fp8 673 -> 376, 256 frames on 200k x 256 fp32
+// 25.7 -> 13.8, every row searched 44 -> 19; coarse stage, 2,048 frames 61 ->
+// 31, 256 frames 15.3 -> 11.2. What is left is the rows' way through L2 (2 KB
+// each, 110 a frame with bf16 rows, 527 with fp8 rows).
+constexpr int kFrameL = 64;       // survivor positions, one per lane
+constexpr int kFrameSlots = 64;   // region slots, one per lane
+constexpr int kFrameRegs = 8;     // positions per lane held in registers
+constexpr int kBandBlocks = 32;   // blocks re-scored per band round
+constexpr int kBandRows = 256;    // rows (coarse stage) per band round
+enum FrameMode { kFineBlocks, kCoarseWords, kCoarseKeys };
+
+__host__ __device__ constexpr int frame_list(int L, bool blocks) {
+  return blocks ? (L > kBandBlocks ? L : kBandBlocks) : kBandRows;
+}
+constexpr size_t frame_lds_bytes(int W, int L, int m, bool blocks) {
+  const size_t list = (size_t)frame_list(L, blocks), rows = list * (blocks ? kBlockRows : 1);
+  return (rows + 2 * (size_t)m + (size_t)W * L) * 8 + (rows + 2 * (size_t)m + list + 8 + W) * 4;
 }
 
-__global__ __launch_bounds__(64 * kWaveFrames) void k_select_keys(SelRerankArgs a) {
-  __shared__ WaveSel s_all[kWaveFrames];
-  const int w = wave_id(), lane = lane_id();
-  const int ng = (a.nq + kWaveFrames - 1) / kWaveFrames;
-  const int f = xcd_frame((int)blockIdx.x, ng) * kWaveFrames + w;
-  if (f >= a.nq) return;  // (the whole wave; no block barrier follows)
-  WaveSel &sh = s_all[w];
-  const int n = a.n_fixed, L = a.L, m = a.m;
-  constexpr int KPL = kWaveKeys / 64;  // keys per lane
-  // the keys and bounds, requested together
-  const uint64_t *kf = a.keys + (int64_t)f * n;
-  uint64_t kk[KPL];
+template <int W>
+__device__ __forceinline__ void frame_sync() {
+  if (W == 1) wave_sync();
+  else __syncthreads();
+}
+
+// Minimum over the wave, the same in every lane (row shifts, then the row
+// broadcasts; lane 63 ends up with all of them).
+__device__ __forceinline__ uint32_t wave_min_dpp(uint32_t v) {
+#define HLOC_MIN_STEP(CTRL, ROWS)                                                        \
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFFu, (int)v, CTRL, ROWS, \
+                                                   0xf, false))
+  HLOC_MIN_STEP(0x111, 0xf);
+  HLOC_MIN_STEP(0x112, 0xf);
+  HLOC_MIN_STEP(0x114, 0xf);
+  HLOC_MIN_STEP(0x118, 0xf);
+  HLOC_MIN_STEP(0x142, 0xa);
+  HLOC_MIN_STEP(0x143, 0xc);
+#undef HLOC_MIN_STEP
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Takes the `want` smallest words out of the lanes' pairs (m1 <= m2) in
+// order; lane t receives the t-th word and its payload. Returns how many
+// there were.
+__device__ __forceinline__ int take_smallest(uint32_t m1, uint32_t p1, uint32_t m2, uint32_t p2,
+                                             int want, uint32_t &word, uint32_t &payload) {
+  const int lane = lane_id();
+  int t = 0;
+  for (; t < want; ++t) {
+    const uint32_t mn = wave_min_dpp(m1);
+    if (mn == kWordNone) break;
+    const int src = __ffsll((unsigned long long)__ballot(m1 == mn)) - 1;
+    const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)p1, src);
+    if (lane == t) {
+      word = mn;
+      payload = p;
+    }
+    if (lane == src) {
+      m1 = m2;
+      p1 = p2;
+      m2 = kWordNone;
+    }
+  }
+  return t;
+}
+
+template <int W, int MODE>
+__global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_frame(SelRerankArgs a) {
+  constexpr bool kBlocks = MODE == kFineBlocks, kKeys = MODE == kCoarseKeys;
+  constexpr int kUnit = kBlocks ? kBlockRows : 1;
+  extern __shared__ uint64_t frame_mem[];
+  if ((int)blockIdx.x >= a.nq) return;
+  if (a.frame_list && (int)blockIdx.x >= *a.frame_count) return;
+  const int f = a.frame_list ? a.frame_list[blockIdx.x] : xcd_frame(blockIdx.x, a.nq);
+  const int tid = threadIdx.x, w = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave_id());
+  const int lane = lane_id();
+  const int L = a.L, m = a.m;
+  const int list_cap = frame_list(L, kBlocks), rows_cap = list_cap * kUnit;
+  uint64_t *new_hi = frame_mem, *srt_hi = new_hi + rows_cap, *wkeys = srt_hi + 2 * m;
+  uint32_t *new_lo = reinterpret_cast<uint32_t *>(wkeys + W * L), *srt_lo = new_lo + rows_cap;
+  uint32_t *list = srt_lo + 2 * m;
+  int *ctr = reinterpret_cast<int *>(list + list_cap);  // [0] new rows, [1] band, [8 + w] band of wave w
+  if (tid == 0) ctr[0] = ctr[1] = 0;
+  // words (key mode: and their rows), requested together with the count
+  const uint32_t *words = kKeys ? nullptr : a.cand + (int64_t)f * a.cap;
+  const uint64_t *keys = kKeys ? a.keys + (int64_t)f * a.n_fixed : nullptr;
+  uint32_t rw[kFrameRegs], rp[kFrameRegs];  // word, payload (position; key mode: row)
 #pragma unroll
-  for (int u = 0; u < KPL; ++u) {
-    const int i = u * 64 + lane;
-    kk[u] = i < n ? kf[i] : kKeyNone;
+  for (int u = 0; u < kFrameRegs; ++u) {
+    const int i = (u * W + w) * 64 + lane;
+    if (kKeys) {
+      const uint64_t kk = i < a.n_fixed ? keys[i] : kKeyNone;
+      rw[u] = (uint32_t)(kk >> 32);
+      rp[u] = (uint32_t)kk;
+    } else {
+      rw[u] = i < a.cap ? words[i] : kWordNone;
+      rp[u] = (uint32_t)i;
+    }
   }
   uint64_t bound = kKeyNone;
-  for (int i = lane; i < a.n_bounds; i += 64) {
-    const uint64_t b = a.bounds[(int64_t)f * a.n_bounds + i];
-    bound = b < bound ? b : bound;
+  if (kKeys)
+    for (int i = lane; i < a.n_bounds; i += 64) {
+      const uint64_t b = a.bounds[(int64_t)f * a.n_bounds + i];
+      bound = b < bound ? b : bound;
+    }
+  // region slots, one per lane
+  int so = INT32_MAX, sr = 0, sl = 0;
+  if (kBlocks && lane < a.nslots) {
+    so = a.slot_off[(int64_t)f * a.nslots + lane];
+    sr = a.slot_row[(int64_t)f * a.nslots + lane];
+    sl = a.slot_len[(int64_t)f * a.nslots + lane];
   }
+  const int n = a.n_cand ? a.n_cand[f] : a.n_fixed;
   const float qn2 = a.qn2[f];
-  // entries (word << 32 | position) of the valid keys (kKeyNone otherwise)
-  uint64_t ent[KPL];
-  int nv = 0;
-#pragma unroll
-  for (int u = 0; u < KPL; ++u) {
-    const int i = u * 64 + lane;
-    const uint32_t wd = (uint32_t)(kk[u] >> 32);
-    const bool valid = i < n && wd != kWordNone;
-    ent[u] = valid ? ((uint64_t)wd << 32) | (uint32_t)i : kKeyNone;
-    sh.krow[i] = (uint32_t)kk[u];
-    nv += valid;
-  }
-  const int nvalid = wave_sum_i32(nv);
-  bound = wave_min_u64(bound);
-  const bool rejected = nvalid > L;
-  const uint32_t bw = (uint32_t)(bound >> 32);
-  auto defer = [&]() {
-    if (lane == 0) a.defer_list[atomicAdd(a.defer_count, 1)] = f;
-  };
-  if (bound != kKeyNone && !rejected) {
-    defer();
-    return;
-  }
-  // the survivors in (word, position) order: the wave minimum, taken out of
-  // its lane, nsurv times; then the word tw of the best rejected pair
-  // without taking it out
-  const int nsurv = min(L, nvalid);
-  wave_sync();  // krow written
-  for (int t = 0; t < nsurv; ++t) {
-    uint64_t lm = ent[0];
-#pragma unroll
-    for (int u = 1; u < KPL; ++u) lm = ent[u] < lm ? ent[u] : lm;
-    const uint64_t mn = wave_min_u64(lm);
-#pragma unroll
-    for (int u = 0; u < KPL; ++u)
-      if (ent[u] == mn) ent[u] = kKeyNone;
-    if (lane == 0) sh.srow[t] = sh.krow[(uint32_t)mn];
-  }
-  uint32_t tw = kWordNone;
-  if (rejected) {
-    uint64_t lm = ent[0];
-#pragma unroll
-    for (int u = 1; u < KPL; ++u) lm = ent[u] < lm ? ent[u] : lm;
-    tw = (uint32_t)(wave_min_u64(lm) >> 32);
-  }
-  if (rejected && bound != kKeyNone && tw > bw) {
-    defer();
-    return;
-  }
-  wave_sync();  // srow written
-  const float *qrow = a.qp + (int64_t)f * a.dp;
-  const int nrow = nsurv;
-  rerank_rows<false, false>(a, qrow, sh.srow, sh.sort_hi, sh.sort_lo, nrow, 0, kRowBatch);
-  wave_sync();
-  wave_sort_pairs(sh, nrow);
-  // certificate (the block kernel's, every lane alike)
-  bool band = false;
-  uint32_t tau_w = 0;
-  if (rejected && m > 0) {
-    const double rejd = (double)__uint_as_float(tw);
+  double err;
+  {
     const double qn = sqrt((double)qn2) * (1.0 + 1e-6);
-    double e = a.err_coef * (qn + a.max_norm) * (qn + a.max_norm);
+    err = a.err_coef * (qn + a.max_norm) * (qn + a.max_norm);
     if (a.q_err) {
       const double qe = a.q_err[f], ql = a.q_lon[f];
-      e += a.lo_coef * (ql * a.lo_dmax + qe * a.lo_nmax + qe * a.lo_dmax);
+      err += a.lo_coef * (ql * a.lo_dmax + qe * a.lo_nmax + qe * a.lo_dmax);
     }
-    const uint64_t km = sh.sort_hi[m - 1];
-    const double dm = km == kKeyNone ? __builtin_inf() : __longlong_as_double((long long)km);
-    const double tau = dm * (1.0 + 1e-12) + e;
-    if (!(rejd > tau)) {
-      band = true;
-      tau_w = __float_as_uint(__double2float_ru(tau));
-      // a band reaching words the lists may have dropped is not complete
-      if (bound != kKeyNone && tau_w >= bw) {
-        defer();
-        return;
+  }
+  uint32_t m1 = kWordNone, p1 = 0, m2 = kWordNone, p2 = 0;
+  auto account = [&](uint32_t v, uint32_t p) {
+    const bool b1 = v < m1, b2 = v < m2;
+    m2 = b1 ? m1 : (b2 ? v : m2);
+    p2 = b1 ? p1 : (b2 ? p : p2);
+    m1 = b1 ? v : m1;
+    p1 = b1 ? p : p1;
+  };
+#pragma unroll
+  for (int u = 0; u < kFrameRegs; ++u) {
+    if ((u * W + w) * 64 + lane >= n) rw[u] = kWordNone;
+    account(rw[u], rp[u]);
+  }
+  const int nt = (n + 63) >> 6;  // tiles of 64 positions, wave w has tiles w, w + W, ..
+  // word and payload of a position past the registers
+  auto fetch = [&](int i, uint32_t &v, uint32_t &p) {
+    v = kWordNone;
+    p = (uint32_t)i;
+    if (i < n) {
+      if (kKeys) {
+        const uint64_t kk = keys[i];
+        v = (uint32_t)(kk >> 32);
+        p = (uint32_t)kk;
+      } else {
+        v = words[i];
       }
     }
-  }
-  int have = min(nrow, m), band_rows = 0;
-  if (band) {
-    // the band: the pairs not taken out with a word up to tau_w (all of
-    // them are at or after (tw, tpos)); their rows behind the survivors'
-    int cnt[KPL], tot = 0;
+  };
+  for (int t = kFrameRegs * W + w; t < nt; t += 4 * W) {
+    uint32_t v[4], p[4];
 #pragma unroll
-    for (int u = 0; u < KPL; ++u) {
-      const bool in = ent[u] != kKeyNone && (uint32_t)(ent[u] >> 32) <= tau_w;
+    for (int u = 0; u < 4; ++u) fetch((t + u * W) * 64 + lane, v[u], p[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) account(v[u], p[u]);
+  }
+  // the survivors: lane t < cnt holds the t-th
+  uint32_t sw = kWordNone, sp = 0;
+  int cnt = take_smallest(m1, p1, m2, p2, L, sw, sp);
+  if (W > 1) {
+    if (lane < L) wkeys[w * L + lane] = lane < cnt ? ((uint64_t)sw << 32) | sp : kKeyNone;
+    __syncthreads();
+    uint64_t k0 = lane < W * L ? wkeys[lane] : kKeyNone;
+    uint64_t k1 = lane + 64 < W * L ? wkeys[lane + 64] : kKeyNone;
+    if (k1 < k0) {
+      const uint64_t x = k0;
+      k0 = k1;
+      k1 = x;
+    }
+    sw = kWordNone;
+    cnt = take_smallest((uint32_t)(k0 >> 32), (uint32_t)k0, (uint32_t)(k1 >> 32), (uint32_t)k1, L,
+                        sw, sp);
+  }
+  const uint32_t wl =
+      cnt > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)sw, cnt - 1) : 0u;  // largest survivor word
+  // every wave writes the whole (same) list and reads its own writes
+  if (lane < cnt) list[lane] = sp;
+  wave_sync();
+  const float *qrow = a.qp + (int64_t)f * a.dp;
+  int have = 0, cur = 0;       // srt[cur][0 .. have): the best so far, sorted
+  int nlist = cnt;             // positions in the list
+  int band = -1, done = 0;     // band positions (-1: not counted yet), of them re-scored
+  uint32_t tau_w = 0;
+  int cur_tile = w, cur_rank = 0;  // several rounds: this wave's next tile, its rank there
+  int my_base = 0;
+  for (;;) {
+    // re-score the list
+    const uint64_t mh = have == m ? srt_hi[cur * m + m - 1] : kKeyNone;
+    const uint32_t ml = have == m ? srt_lo[cur * m + m - 1] : 0xFFFFFFFFu;
+    const int nbatch = kBlocks ? 2 * nlist : (nlist + kRowBatch - 1) / kRowBatch;
+    for (int h = w; h < nbatch; h += W) {
+      uint32_t row[kRowBatch];
+      int nv;
+      if (kBlocks) {
+        const int p = __builtin_amdgcn_readfirstlane((int)list[h >> 1]);
+        int row0, len;
+        if (a.nslots == 0) {
+          const int2 br = a.blk_rows[p];
+          row0 = br.x;
+          len = br.y;
+        } else {
+          // the last slot that begins at or before p
+          const uint64_t le = __ballot(so <= p);
+          const int j = 63 - __clzll((long long)le);
+          const int b = p - __builtin_amdgcn_readlane(so, j);
+          row0 = __builtin_amdgcn_readlane(sr, j) + b * kBlockRows;
+          len = min(kBlockRows, __builtin_amdgcn_readlane(sl, j) - b * kBlockRows);
+        }
+        row0 += kRowBatch * (h & 1);
+        nv = min(kRowBatch, len - kRowBatch * (h & 1));
+        if (nv <= 0) continue;
+#pragma unroll
+        for (int r = 0; r < kRowBatch; ++r) row[r] = (uint32_t)(row0 + min(r, nv - 1));
+      } else {
+        nv = min(kRowBatch, nlist - h * kRowBatch);
+#pragma unroll
+        for (int r = 0; r < kRowBatch; ++r)
+          row[r] = (uint32_t)__builtin_amdgcn_readfirstlane(
+              (int)list[h * kRowBatch + min(r, nv - 1)]);
+      }
+      // lanes 8 r .. 8 r + 7 end up holding row r's total
+      const int ri = lane >> 3;
+      const bool own = (lane & 7) == 0 && ri < nv;
+      uint32_t tie = 0;
+      if (own) {
+        tie = kBlocks ? row[0] + (uint32_t)ri : list[h * kRowBatch + ri];
+        if (a.tie_of) tie = (uint32_t)a.tie_of[tie];
+      }
+      double acc[kRowBatch];
+      rerank_batch<false, false, kBlocks>(a, qrow, row, acc);
+      const uint64_t d = (uint64_t)__double_as_longlong(wave_sum8_f64(acc));
+      const bool keep = own && pair_less(d, tie, mh, ml);
+      const uint64_t bal = __ballot(keep);
+      if (bal) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&ctr[0], __popcll(bal));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (keep) {
+          const int slot = base + __popcll(bal & ((1ull << lane) - 1ull));
+          new_hi[slot] = d;
+          new_lo[slot] = tie;
+        }
+      }
+    }
+    frame_sync<W>();
+    // merge the new rows into the best m: G lanes per entry count the
+    // entries before it
+    const int few = ctr[0], tot = have + few;
+    if (few > 0) {
+      constexpr int kThreads = 64 * W;
+      int G = 1;
+      while (G < 16 && 2 * G * tot <= kThreads) G *= 2;
+      const int part = tid & (G - 1);
+      const uint64_t *sh = srt_hi + cur * m;
+      const uint32_t *sl2 = srt_lo + cur * m;
+      uint64_t *oh = srt_hi + (1 - cur) * m;
+      uint32_t *ol = srt_lo + (1 - cur) * m;
+      for (int e0 = 0; e0 < tot; e0 += kThreads / G) {
+        const int e = e0 + tid / G;
+        uint64_t hi = kKeyNone;
+        uint32_t lo = 0xFFFFFFFFu;
+        if (e < few) {
+          hi = new_hi[e];
+          lo = new_lo[e];
+        } else if (e < tot) {
+          hi = sh[e - few];
+          lo = sl2[e - few];
+        }
+        int rank = 0;
+#pragma unroll 4
+        for (int j = part; j < few; j += G) rank += pair_less(new_hi[j], new_lo[j], hi, lo);
+#pragma unroll 4
+        for (int j = part; j < have; j += G) rank += pair_less(sh[j], sl2[j], hi, lo);
+        for (int o = 1; o < G; o <<= 1) rank += __shfl_xor(rank, o);
+        if (part == 0 && e < tot && rank < m) {
+          oh[rank] = hi;
+          ol[rank] = lo;
+        }
+      }
+      cur = 1 - cur;
+      have = min(tot, m);
+      frame_sync<W>();
+      if (tid == 0) ctr[0] = 0;
+    }
+    if (band < 0) {
+      // certificate: what is within the error bound of the m-th distance
+      const double dm =
+          have == m ? __longlong_as_double((long long)srt_hi[cur * m + m - 1]) : __builtin_inf();
+      tau_w = __float_as_uint(__double2float_ru(dm * (1.0 + 1e-12) + err));
+      if (kKeys) {
+        const uint32_t bw = (uint32_t)(wave_min_u64(bound) >> 32);
+        if (bw != kWordNone && tau_w >= bw) {
+          if (tid == 0) a.defer_list[atomicAdd(a.defer_count, 1)] = f;
+          return;
+        }
+      }
+    } else {
+      done += nlist;
+    }
+    if (band >= 0 && done >= band) break;
+    // positions of the band among 64 words
+    auto in_band = [&](uint32_t v, uint32_t p) {
+      bool in = v != kWordNone && v <= tau_w;
+      if (__ballot(in && v <= wl)) {
+        bool mine = false;
+        for (int t = 0; t < cnt; ++t) mine |= (uint32_t)__builtin_amdgcn_readlane((int)sp, t) == p;
+        in &= !mine;
+      }
+      return in;
+    };
+    if (band < 0) {
+      int wc = 0;
+      auto place = [&](uint32_t v, uint32_t p) {
+        const bool in = in_band(v, p);
+        const uint64_t bal = __ballot(in);
+        if (!bal) return;
+        int base = wc;
+        if (W > 1) {
+          if (lane == 0) base = atomicAdd(&ctr[1], __popcll(bal));
+          base = __builtin_amdgcn_readfirstlane(base);
+        }
+        const int slot = base + __popcll(bal & ((1ull << lane) - 1ull));
+        if (in && slot < list_cap) list[slot] = p;
+        wc += __popcll(bal);
+      };
+#pragma unroll
+      for (int u = 0; u < kFrameRegs; ++u)
+        if ((u * W + w) < nt) place(rw[u], rp[u]);
+      for (int t = kFrameRegs * W + w; t < nt; t += W) {
+        uint32_t v, p;
+        fetch(t * 64 + lane, v, p);
+        place(v, p);
+      }
+      if (W == 1) {
+        band = wc;
+        wave_sync();
+      } else {
+        if (lane == 0) ctr[8 + w] = wc;
+        __syncthreads();
+        band = ctr[1];
+        for (int i = 0; i < w; ++i) my_base += ctr[8 + i];
+      }
+      if (band == 0) break;
+      if (tid == 0 && a.stat_fallback) atomicAdd(a.stat_fallback, 1);
+      if (band <= list_cap) {
+        nlist = band;
+        continue;
+      }
+      cur_rank = my_base;
+      frame_sync<W>();
+    }
+    // more than one round: the band's positions by rank (wave by wave, in
+    // tile order), [done, done + list_cap) of them
+    const int end = min(band, done + list_cap);
+    for (; cur_tile < nt && cur_rank < end; cur_tile += W) {
+      uint32_t v, p;
+      fetch(cur_tile * 64 + lane, v, p);
+      const bool in = in_band(v, p);
       const uint64_t bal = __ballot(in);
-      cnt[u] = in ? tot + __popcll(bal & ((1ull << lane) - 1ull)) : -1;
-      tot += __popcll(bal);
+      const int rank = cur_rank + __popcll(bal & ((1ull << lane) - 1ull));
+      if (in && rank >= done && rank < end) list[rank - done] = p;
+      if (cur_rank + __popcll(bal) > end) break;  // the rest of this tile: the next round
+      cur_rank += __popcll(bal);
     }
-    if (nrow + tot > kWaveRows) {
-      defer();
-      return;
-    }
-#pragma unroll
-    for (int u = 0; u < KPL; ++u)
-      if (cnt[u] >= 0) sh.srow[nrow + cnt[u]] = sh.krow[(uint32_t)ent[u]];
-    wave_sync();
-    rerank_rows<false, false>(a, qrow, sh.srow, sh.sort_hi, sh.sort_lo, nrow + tot, nrow, kRowBatch);
-    wave_sync();
-    wave_sort_pairs(sh, nrow + tot);
-    have = min(nrow + tot, m);
-    band_rows = tot;
-    if (lane == 0 && a.stat_fallback) atomicAdd(a.stat_fallback, 1);
+    nlist = end - done;
+    frame_sync<W>();
   }
-  if (lane == 0 && a.frame_stat)
-    a.frame_stat[f] = make_int4(n, nrow + band_rows, band_rows, band ? 1 : 0);
-  for (int i = lane; i < m; i += 64) {
-    const bool ok = i < have && sh.sort_hi[i] != kKeyNone;
-    a.reg_out[(int64_t)f * m + i] = ok ? (int32_t)sh.sort_lo[i] : -1;
+  if (tid == 0 && a.frame_stat)
+    a.frame_stat[f] = make_int4(n, (cnt + band) * kUnit, band * kUnit,
+                                (band > 0 ? 1 : 0) | (band > list_cap ? 2 : 0));
+  for (int i = tid; i < m; i += 64 * W) {
+    const bool ok = i < have;
+    if (kBlocks) {
+      a.idx_out[(int64_t)f * m + i] = ok ? (int64_t)srt_lo[cur * m + i] : -1;
+      a.dist_out[(int64_t)f * m + i] =
+          ok ? (float)__longlong_as_double((long long)srt_hi[cur * m + i]) : __builtin_inff();
+    } else {
+      a.reg_out[(int64_t)f * m + i] = ok ? (int32_t)srt_lo[cur * m + i] : -1;
+    }
   }
 }
 
@@ -1225,6 +1458,41 @@ hipError_t prepare_select_kernels() {
   return e;
 }
 
+// Waves per frame. A wave alone repeats nothing and never waits for another,
+// so batches that fill the chip with single frames want few; below that, and
+// where a frame re-scores many rows (the quarter-size rows leave about 430 in
+// the band), more waves share one frame's rows. Measured (us; 1 / 2 / 4 / 8
+// waves): fine, 32,768 frames of 2M x 512 bf16 rows 1083 / 814 / 839 / 1099;
+// 2,048 frames, 500k x 512, bf16 87 / 67 / 63 / 73, fp8 1673 / 945 / 545 / 375;
+// 1,265 frames of 200k x 256 fp32 rows 95 / 58 / 37 / 36; 256 frames of them
+// 41 / 25 / 17 / 14. Coarse, keys, 32,768 frames 172 / 292 / 509 / -; 2,048
+// frames 35 / 37 / 42 / -; words, 1,265 frames 16 / 14 / 21 / -; 256 frames
+// 13 / 12 / 11 / 13. The lists of all waves are merged in two registers per
+// lane: W * L <= 128.
+int frame_waves(const SelRerankArgs &a) {
+  int W;
+  if (a.blocks) W = a.long_bands ? (a.nq >= 8192 ? 4 : 8) : a.nq >= 4096 ? 2 : a.nq >= 1536 ? 4 : 8;
+  else W = a.nq >= 2048 ? 1 : a.nq >= 1024 ? 2 : 4;
+  while (W * a.L > 128) W /= 2;
+  return W;
+}
+
+template <int MODE>
+hipError_t launch_frame(const SelRerankArgs &a, hipStream_t s) {
+  const int W = frame_waves(a);
+  const dim3 grid(a.nq), block(64 * W);
+  const uint32_t lds = (uint32_t)frame_lds_bytes(W, a.L, a.m, MODE == kFineBlocks);
+  switch (W) {
+    case 1: return launch_kernel(k_select_frame<1, MODE>, grid, block, lds, s, a);
+    case 2: return launch_kernel(k_select_frame<2, MODE>, grid, block, lds, s, a);
+    case 4: return launch_kernel(k_select_frame<4, MODE>, grid, block, lds, s, a);
+    default: break;
+  }
+  if constexpr (MODE == kFineBlocks)
+    return launch_kernel(k_select_frame<8, MODE>, grid, block, lds, s, a);
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_select_rerank(SelRerankArgs a, hipStream_t s) {
   if (a.nq <= 0) return hipSuccess;
   const int unit = a.blocks ? kBlockRows : 1;
@@ -1244,11 +1512,11 @@ hipError_t launch_select_rerank(SelRerankArgs a, hipStream_t s) {
   } else {
     a.cache = (int32_t)std::min<int64_t>(a.cap, kWordCache);
   }
-  // key mode with few keys per frame (the coarse stage of large batches):
-  // one wave per frame
-  if (a.keys && a.reg_out && a.n_fixed <= kWaveKeys && a.L <= kWaveRows)
-    return launch_kernel(k_select_keys, dim3((unsigned)((a.nq + kWaveFrames - 1) / kWaveFrames)),
-                         dim3(64 * kWaveFrames), 0, s, a);
+  // the frame kernel, unless its lists do not hold the survivors or the slots
+  if (a.L <= kFrameL && a.m >= 1 && a.nslots <= kFrameSlots) {
+    if (a.blocks) return launch_frame<kFineBlocks>(a, s);
+    return a.keys ? launch_frame<kCoarseKeys>(a, s) : launch_frame<kCoarseWords>(a, s);
+  }
   // frames with many candidates: the word cache takes most of the LDS, so the
   // block is alone on its compute unit; 1024 threads use all of it
   if (a.cap > kBigFrame)

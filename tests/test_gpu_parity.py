@@ -1014,3 +1014,45 @@ def test_wide_items_cut_for_the_batch(torch_cuda, frames, d):
     for p in ("bf16", "fp8"):
         for key in outs[p]:
             assert outs[p][key].tobytes() == outs["fp32"][key].tobytes(), (p, key)
+
+
+@pytest.mark.parametrize("k,n_reg", [(1, 1), (13, 5), (40, 28), (100, 29), (256, 60), (16, 61),
+                                     (16, 64), (16, 65)])
+def test_selection_list_edges(torch_cuda, k, n_reg):
+    # the selection's lists at their limits (survivor positions, region slots,
+    # waves per frame) and past them: one call of 4,100 frames (few waves per
+    # frame), calls of 2,000 and of 300 (more) give every frame the same bits
+    # in every screen precision, and 40 frames match the oracle. 900 identical
+    # rows make bands of several rounds.
+    rng = np.random.default_rng(27)
+    sizes = rng.integers(1, 120, 130)
+    sizes[5] = 900
+    region_of = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    n, d, R = len(region_of), 64, len(sizes)
+    feats = rng.standard_normal((n, d)).astype(np.float32)
+    same = np.flatnonzero(region_of == 5)
+    feats[same] = feats[same[0]]
+    xy = rng.uniform(0, 40, size=(n, 2))
+    src = rng.integers(0, n, 4100)
+    src[::50] = same[0]
+    q = (feats[src] + 0.2 * rng.standard_normal((4100, d))).astype(np.float32)
+    db = make_db(feats, xy, region_of, R, mirrors=hloc.MIRROR_BF16 | hloc.MIRROR_FP8)
+    ref = None
+    for precision in ("fp32", "bf16", "fp8"):
+        say(f"[case] k={k} n_reg={n_reg} {precision}")
+        full = run_device(torch_cuda, db, q, k, n_reg, precision=precision)
+        ref = ref or full
+        for key in full:
+            assert full[key].tobytes() == ref[key].tobytes(), (precision, key)
+        for step in (2000, 300):
+            part = run_device(torch_cuda, db, q[:step], k, n_reg, precision=precision)
+            for key in part:
+                assert part[key].tobytes() == full[key][:step].tobytes(), (precision, step, key)
+    regs = db.last_regions()
+    db.close()
+    ora = oracle.localize(feats, xy, region_of, R, q[:40], np.arange(41), k, n_reg,
+                          (0.5, 1, 0.0, 0))
+    st = judge_frames(ref["idx"][:40], ref["dist"][:40], regs[:40], ora, feats, region_of, R,
+                      q[:40], k)
+    say(f"[ok] {st}")
+    assert st["recall"] == 1.0
