@@ -143,6 +143,15 @@ int make_plan(const hloc_db *db, int32_t nq, int32_t k, int32_t n_regions, int32
   p.items_bound = std::min(b1, b2);
   if (p.items_bound > INT32_MAX || (int64_t)nq * p.cap2 > ((int64_t)1 << 40))
     return fail(HLOC_EINVAL, "batch too large for one call (nq %d)", nq);
+  // Small batches screen straight from the block table: no schedule kernels
+  // and no launch for wide items, against rows read again for every 16 frames
+  // of a region.
+  {
+    const double rows = p.exhaustive ? (double)db->n : p.nr * db->kept_rows;
+    p.direct = 2.0 * nq * rows * db->dp <= kDirectFlops &&
+               (p.exhaustive || (int64_t)nq * db->R <= kDirectSlots) &&
+               db->n_blocks <= (int64_t)1 << 26;  // (times kDirectSplits: 31 bits)
+  }
   const int32_t max_blocks = db->num_cu * db->tile_blocks;
   p.grid2 = screen_grid(p.items_bound, db->dp, max_blocks);
   const int64_t dense_items =
@@ -180,21 +189,26 @@ int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *byte
     CHK(fit(ws->cbounds, (size_t)nq * p.csplits * 4 * sizeof(uint64_t)));
     CHK(fit(ws->cdefer, (size_t)nq * sizeof(int32_t)));
   }
-  if (!p.exhaustive) CHK(fit(ws->cand1, (size_t)nq * db->R * sizeof(uint32_t)));
-  CHK(fit(ws->regions, (size_t)nq * nr * sizeof(int32_t)));
+  if (!p.exhaustive) {
+    size_t need = p.direct ? coarse_list_bytes(nq, db->R) : (size_t)nq * db->R * sizeof(uint32_t);
+    if (p.reserve)
+      need = std::max(need, coarse_list_bytes(std::min<int64_t>(nq, kDirectSlots / db->R), db->R));
+    CHK(fit(ws->cand1, need));
+  }
+  const int64_t kept = p.exhaustive ? 1 : nq * nr;  // (the exhaustive search lists no regions)
+  CHK(fit(ws->regions, (size_t)kept * sizeof(int32_t)));
   CHK(fit(ws->rcount, (size_t)db->R * sizeof(int32_t)));
-  CHK(fit(ws->rfill, (size_t)db->R * sizeof(int32_t)));
   CHK(fit(ws->vord, (size_t)db->R * sizeof(int32_t)));
   CHK(fit(ws->rq_off, (size_t)(db->R + 1) * sizeof(int32_t)));
   CHK(fit(ws->item_off, (size_t)(db->R + 1) * sizeof(int32_t)));
-  CHK(fit(ws->cand_off, (size_t)nq * nr * sizeof(int32_t)));
-  CHK(fit(ws->slot_row, (size_t)nq * nr * sizeof(int32_t)));
-  CHK(fit(ws->slot_len, (size_t)nq * nr * sizeof(int32_t)));
+  CHK(fit(ws->cand_off, (size_t)kept * sizeof(int32_t)));
+  CHK(fit(ws->slot_row, (size_t)kept * sizeof(int32_t)));
+  CHK(fit(ws->slot_len, (size_t)kept * sizeof(int32_t)));
   CHK(fit(ws->n_cand, (size_t)nq * sizeof(int32_t)));
   CHK(fit(ws->n_rows, (size_t)nq * sizeof(int32_t)));
   CHK(fit(ws->fstat, (size_t)nq * sizeof(int4)));
   CHK(fit(ws->misc, kMiscInts * sizeof(int32_t)));
-  CHK(fit(ws->rq, (size_t)nq * nr * sizeof(int2)));
+  CHK(fit(ws->rq, (size_t)(p.exhaustive ? nq : nq * nr) * sizeof(int2)));
   CHK(fit(ws->items, (size_t)std::max<int64_t>(p.items_bound, 1) * sizeof(Item)));
   CHK(fit(ws->cand2, (size_t)nq * std::max<int64_t>(p.cap2, 1) * sizeof(uint32_t)));
   if (db->lp[HLOC_BF16].rows || db->lp[HLOC_FP8].rows) {
@@ -252,16 +266,21 @@ struct Phaser {
   ~Phaser() { end(); }
 };
 
-int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req_offsets,
+int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *req_offsets,
                   const int32_t *req_k, int64_t *idx, float *dist, double *xy, int32_t *tile,
                   int32_t *flags, hipStream_t s, const int32_t *req_frames, int32_t n_frames,
                   int32_t label, int32_t label_frames) {
   const hloc_db *db = ws->db;
   const bool want_agg = xy || tile || flags;
+  Plan p = plan;
+  if (ws->fixed && p.direct && !p.exhaustive && ws->cand1.cap < coarse_list_bytes(p.nq, db->R))
+    p.direct = false;
   CHK(ensure_workspace(ws, p, want_agg && !(xy && tile && flags)));
   ws->last_nq = p.nq;
   ws->last_nr = p.nr;
   ws->last_kp = p.kp;
+  ws->last_direct = p.direct;
+  ws->last_all = p.exhaustive;
   int32_t *misc = as<int32_t>(ws->misc);
   if (p.nq == 0) {
     HIPCHK(launch_fill_i32(misc, kMiscInts, 0, s));
@@ -282,7 +301,8 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
   float *c_scale = as<float>(coarse_bf16 ? ws->c_scale : ws->q_scale);
   float *c_err = as<float>(coarse_bf16 ? ws->c_err : ws->q_err);
   float *c_lon = as<float>(coarse_bf16 ? ws->c_lon : ws->q_lon);
-  HIPCHK(launch_prep_queries(q, p.nq, db->d, db->dp, qp, qn2, misc, s));
+  HIPCHK(launch_prep_queries(q, p.nq, db->d, db->dp, qp, qn2, misc, as<int32_t>(ws->rcount),
+                             p.exhaustive ? 0 : db->R, s));
   if (fmt)
     HIPCHK(launch_frames_to_lp(fmt, qp, p.nq, db->dp, ws->q_lp.p, as<float>(ws->q_scale),
                                as<float>(ws->q_err), as<float>(ws->q_lon), s));
@@ -296,6 +316,21 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
   const double coef = (db->dp + 16) * kUnit32 * 1.001;
   const bool masked = (label >= 0 || label_frames > 0) && db->rlabel;
   const bool coarse_lp = cfmt && cpm->reps;
+  // what the coarse selection leaves for the fine stage (with an item list,
+  // the places go where the fine screen's words will be: each region has at
+  // least one block)
+  SlotArgs so{};
+  so.reg_start = db->reg_start;
+  so.off = as<int32_t>(ws->cand_off);
+  so.row = as<int32_t>(ws->slot_row);
+  so.len = as<int32_t>(ws->slot_len);
+  so.n_cand = as<int32_t>(ws->n_cand);
+  so.n_rows = as<int32_t>(ws->n_rows);
+  so.count = as<int32_t>(ws->rcount);
+  if (p.direct && !p.exhaustive)
+    so.rq = reinterpret_cast<int2 *>(static_cast<char *>(ws->cand1.p) + coarse_word_bytes(p.nq, db->R));
+  so.rq_stride = p.nq;
+  so.place = as<int32_t>(ws->cand2);
   // The dense coarse stage: every frame's word against every representative,
   // then the words-mode select (FP64 re-score of the best, certificate).
   // With a frame list, only the listed frames (those the fused product's
@@ -356,6 +391,7 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
     }
     ra.nq = p.nq;
     ra.reg_out = regions;
+    ra.slots = so;
     ra.stat_fallback = misc + 1;
     ra.frame_list = list;
     ra.frame_count = count;
@@ -409,17 +445,14 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
     ra.err_coef = coef * 1.01;
     ra.nq = p.nq;
     ra.reg_out = regions;
+    ra.slots = so;
     ra.stat_fallback = misc + 1;
     HIPCHK(launch_select_rerank(ra, s));
     ph.begin(HLOC_PHASE_COARSE_DEFER);
     CHK(coarse_words(as<int32_t>(ws->cdefer), misc + 10));
   } else if (!p.exhaustive) {
     CHK(coarse_words(nullptr, nullptr));
-  } else {
-    HIPCHK(launch_broadcast_ids(db->nonempty_ids, p.nr, p.nq, regions, s));
   }
-  ph.begin(HLOC_PHASE_SCHED);
-  int32_t *cand_off = as<int32_t>(ws->cand_off), *n_cand = as<int32_t>(ws->n_cand);
   // wide regions: chunks the wide kernel of this screen takes
   const bool rs = fmt && lp_wide_rs(fmt, db->dp);
   const int32_t wide_rows = rs ? kWideRowsRs : std::min(db->tile_rows, kWideRows);
@@ -438,13 +471,13 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
   // unit)
   cut.steps_scale =
       rs || lds_wide ? 1.f / ((float)(cut.W << cut.log_gu) * (float)(2 * 2 * db->num_cu)) : 1e30f;
-  HIPCHK(launch_sched(regions, p.nq, p.nr, db->R, db->reg_start, cut,
-                      as<int32_t>(ws->rcount), as<int32_t>(ws->rfill), as<int32_t>(ws->vord),
-                      as<int32_t>(ws->rq_off),
-                      as<int32_t>(ws->item_off), cand_off, as<int32_t>(ws->slot_row),
-                      as<int32_t>(ws->slot_len), n_cand,
-                      as<int32_t>(ws->n_rows), misc + 0, as<int2>(ws->rq), as<Item>(ws->items),
-                      s));
+  if (!p.direct) {
+    ph.begin(HLOC_PHASE_SCHED);
+    HIPCHK(launch_sched(regions, p.nq, p.nr, db->R, db->reg_start, cut,
+                        p.exhaustive ? nullptr : as<int32_t>(ws->rcount), so.place, so.off,
+                        as<int32_t>(ws->vord), as<int32_t>(ws->rq_off), as<int32_t>(ws->item_off),
+                        misc + 0, as<int2>(ws->rq), as<Item>(ws->items), s));
+  }
   ph.begin(HLOC_PHASE_SCREEN);
   ScreenArgs sb{};
   sb.rows = db->rows;
@@ -467,10 +500,23 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
     sb.row_scale = lpm->scale;
     sb.q_scale = as<float>(ws->q_scale);
   }
-  HIPCHK(fmt ? launch_screen_lp(fmt, sb, p.grid2, s) : launch_screen_f32(sb, p.grid2, s));
-  ph.begin(HLOC_PHASE_SCREEN_WIDE);
-  HIPCHK(fmt ? launch_screen_wide_lp(fmt, sb, p.grid2, db->num_cu, s)
-             : launch_screen_wide_f32(sb, p.grid2, db->num_cu, s));
+  if (p.direct) {
+    sb.nq = p.nq;
+    sb.blk_tab = db->blk_tab;
+    sb.n_blk = (int32_t)db->n_blocks;
+    sb.region_count = so.count;
+    sb.rq = so.rq;
+    sb.rq_stride = so.rq_stride;
+    sb.all_frames = p.exhaustive;
+    sb.splits = std::min((p.nq + kGroup - 1) / kGroup, kDirectSplits);
+    const int32_t blocks = db->num_cu * db->tile_blocks;
+    HIPCHK(fmt ? launch_screen_direct_lp(fmt, sb, blocks, s) : launch_screen_direct(sb, blocks, s));
+  } else {
+    HIPCHK(fmt ? launch_screen_lp(fmt, sb, p.grid2, s) : launch_screen_f32(sb, p.grid2, s));
+    ph.begin(HLOC_PHASE_SCREEN_WIDE);
+    HIPCHK(fmt ? launch_screen_wide_lp(fmt, sb, p.grid2, db->num_cu, s)
+               : launch_screen_wide_f32(sb, p.grid2, db->num_cu, s));
+  }
   ph.begin(HLOC_PHASE_SELECT);
   SelRerankArgs rb{};
   rb.cand = as<uint32_t>(ws->cand2);
@@ -481,11 +527,12 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
   // serves every frame
   rb.blocks = 1;
   rb.nslots = p.exhaustive ? 0 : p.nr;
-  rb.slot_off = cand_off;
+  rb.slot_off = so.off;
   rb.slot_row = as<int32_t>(ws->slot_row);
   rb.slot_len = as<int32_t>(ws->slot_len);
-  rb.blk_rows = db->blk_rows;
-  rb.n_cand = n_cand;
+  rb.blk_tab = db->blk_tab;
+  rb.n_cand = p.exhaustive ? nullptr : so.n_cand;
+  rb.n_fixed = (int32_t)p.cap2;
   rb.L = (p.kp + kBlockRows - 1) / kBlockRows;  // survivor blocks: at least k' rows
   rb.m = p.k;
   rb.src32 = db->rows;
@@ -577,7 +624,7 @@ void drop_graph(hloc_ws *ws) {
 template <class F>
 void for_each_buf(hloc_ws *ws, F f) {
   WsBuf *bufs[] = {&ws->vord,     &ws->qp,       &ws->qn2,      &ws->cand1,    &ws->regions, &ws->rcount,
-                   &ws->rfill,    &ws->rq_off,   &ws->item_off, &ws->cand_off, &ws->n_cand,
+                   &ws->rq_off,   &ws->item_off, &ws->cand_off, &ws->n_cand,
                    &ws->misc,     &ws->rq,       &ws->items,    &ws->cand2,   &ws->agg_xy,
                    &ws->agg_tile, &ws->agg_flags, &ws->s_q,     &ws->s_off,   &ws->s_idx,
                    &ws->s_dist,   &ws->s_xy,     &ws->s_tile,   &ws->s_flags, &ws->q_lp,
@@ -643,12 +690,11 @@ void free_db_data(hloc_db *db) {
   dev_free(db->tiles);
   dev_free(db->norm_max);
   dev_free(db->reg_start);
-  dev_free(db->nonempty_ids);
   dev_free(db->rlabel);
   dev_free(db->rep64);
   dev_free(db->rep32);
   dev_free(db->rep_n2);
-  dev_free(db->blk_rows);
+  dev_free(db->blk_tab);
   if (db->stream) (void)hipStreamDestroy(db->stream);
   db->stream = nullptr;
 }
@@ -702,7 +748,9 @@ int info_of(hloc_ws *ws, int64_t *out, int32_t n) {
   int32_t misc[16] = {0};
   if (ws->misc.p) HIPCHK(hipMemcpy(misc, ws->misc.p, sizeof misc, hipMemcpyDeviceToHost));
   int64_t total = 0, fine_fb = 0, max_n = 0, chunked = 0, band = 0, rows = 0;
-  if (ws->last_nq > 0 && ws->n_rows.p) {
+  if (ws->last_all) {
+    total = (int64_t)ws->last_nq * ws->db->n;
+  } else if (ws->last_nq > 0 && ws->n_rows.p) {
     std::vector<int32_t> nc(ws->last_nq);
     HIPCHK(hipMemcpy(nc.data(), ws->n_rows.p, nc.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
     for (int32_t v : nc) total += v;
@@ -719,8 +767,23 @@ int info_of(hloc_ws *ws, int64_t *out, int32_t n) {
       chunked += (r.w >> 1) & 1;
     }
   }
-  const int64_t vals[11] = {misc[0], misc[1], fine_fb, max_n,   ws->last_kp, total,
-                            misc[4], chunked, band,    rows,    misc[10]};
+  int64_t items = misc[0], narrow = misc[4];
+  if (ws->last_direct && ws->last_nq > 0 && ws->db->has_regions) {
+    // no item list: (16-row block, 16-frame group) pairs stand for it
+    const auto &st = ws->db->h_reg_start;
+    std::vector<int32_t> rc(st.size() - 1, ws->last_nq);
+    if (!ws->last_all)
+      HIPCHK(hipMemcpy(rc.data(), ws->rcount.p, rc.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    items = narrow = 0;
+    for (size_t r = 0; r < rc.size(); ++r) {
+      const int64_t u = (st[r + 1] - st[r] + kBlockRows - 1) / kBlockRows *
+                        ((rc[r] + kGroup - 1) / kGroup);
+      items += u;
+      if (rc[r] <= kGroup) narrow += u;
+    }
+  }
+  const int64_t vals[11] = {items,  misc[1], fine_fb, max_n, ws->last_kp, total,
+                            narrow, chunked, band,    rows,  misc[10]};
   for (int32_t i = 0; i < std::min(n, 11); ++i) out[i] = vals[i];
   return HLOC_OK;
 }
@@ -835,11 +898,10 @@ int hloc_set_regions(hloc_db *db, const int32_t *region_of, int32_t n_regions_to
   db->n_labels = 0;
   db->h_label_nonempty.clear();
   dev_free(db->reg_start);
-  dev_free(db->nonempty_ids);
   dev_free(db->rep64);
   dev_free(db->rep32);
   dev_free(db->rep_n2);
-  dev_free(db->blk_rows);
+  dev_free(db->blk_tab);
   for (LpMirror &m : db->lp) free_lp(m, true);
   db->has_regions = false;
   int rc;
@@ -861,24 +923,21 @@ int hloc_set_regions(hloc_db *db, const int32_t *region_of, int32_t n_regions_to
   dev_free(db->rows);
   db->rows = new_rows;
   db->h_perm = new_perm;
-  std::vector<int32_t> ids;
-  for (int32_t r = 0; r < R; ++r)
-    if (sizes[r] > 0) ids.push_back(r);
   // 16-row blocks of every region in id order (the exhaustive search's
   // candidate list)
-  std::vector<int2> blk;
+  std::vector<int4> blk;
   blk.reserve((size_t)(n / kBlockRows + R));
   for (int32_t r = 0; r < R; ++r)
     for (int64_t b = start[r]; b < start[r + 1]; b += kBlockRows)
-      blk.push_back(make_int2((int)b, (int)std::min<int64_t>(kBlockRows, start[r + 1] - b)));
-  if ((rc = dev_alloc(&db->reg_start, (size_t)R + 1)) || (rc = dev_alloc(&db->nonempty_ids, ids.size())) ||
+      blk.push_back(make_int4((int)b, (int)std::min<int64_t>(kBlockRows, start[r + 1] - b), r,
+                              (int)((b - start[r]) / kBlockRows)));
+  if ((rc = dev_alloc(&db->reg_start, (size_t)R + 1)) ||
       (rc = dev_alloc(&db->rep64, (size_t)R * db->dp)) || (rc = dev_alloc(&db->rep32, (size_t)R * db->dp)) ||
-      (rc = dev_alloc(&db->rep_n2, (size_t)R)) || (rc = dev_alloc(&db->blk_rows, blk.size())))
+      (rc = dev_alloc(&db->rep_n2, (size_t)R)) || (rc = dev_alloc(&db->blk_tab, blk.size())))
     return rc;
-  HIPCHK(hipMemcpy(db->blk_rows, blk.data(), blk.size() * sizeof(int2), hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(db->blk_tab, blk.data(), blk.size() * sizeof(int4), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(db->perm, new_perm.data(), (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(db->reg_start, start.data(), (size_t)(R + 1) * sizeof(int64_t), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(db->nonempty_ids, ids.data(), ids.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   HIPCHK(hipMemsetAsync(db->norm_max, 0, kNormSlots * sizeof(float), db->stream));
   HIPCHK(launch_row_norms(db->rows, n, db->dp, db->row_n2, db->norm_max, db->stream));
   for (int fmt : {HLOC_BF16, HLOC_FP8}) {
@@ -926,7 +985,7 @@ int hloc_set_regions(hloc_db *db, const int32_t *region_of, int32_t n_regions_to
     db->lp[fmt].rep_norm = v[3];
   }
   db->R = R;
-  db->R_nonempty = (int32_t)ids.size();
+  db->R_nonempty = (int32_t)std::count_if(sizes.begin(), sizes.end(), [](int64_t z) { return z > 0; });
   db->h_reg_start = start;
   std::vector<int64_t> desc(sizes);
   std::sort(desc.begin(), desc.end(), std::greater<int64_t>());
@@ -938,6 +997,8 @@ int hloc_set_regions(hloc_db *db, const int32_t *region_of, int32_t n_regions_to
     db->h_desc_blocks[r + 1] = db->h_desc_blocks[r] + (desc[r] + kBlockRows - 1) / kBlockRows;
   }
   db->n_blocks = (int64_t)blk.size();
+  db->kept_rows = 0.0;
+  for (int32_t r = 0; r < R; ++r) db->kept_rows += (double)sizes[r] * (double)sizes[r] / (double)n;
   db->max_region = desc.empty() ? 0 : desc[0];
   db->chunks_fine = count_chunks(db, std::min(db->tile_rows, kWideRows));
   db->has_regions = true;
@@ -993,6 +1054,7 @@ int hloc_ws_reserve(hloc_ws *ws, int32_t nq_max, int32_t nreq_max, int32_t k_max
   if (nreq_max < 0) return fail(HLOC_EINVAL, "nreq_max must be >= 0");
   Plan p;
   CHK(make_plan(ws->db, nq_max, k_max, n_regions_max, nreq_max, HLOC_FP32, &p));
+  p.reserve = true;
   DeviceGuard g(ws->db->device);
   if (g.err != hipSuccess) return fail(HLOC_EDEVICE, "hipSetDevice failed");
   return ensure_workspace(ws, p, true);
@@ -1170,6 +1232,12 @@ int hloc_query_batch_static_async(hloc_db *db, const float *q, int32_t nq, int32
   size_t used = 0;
   const Carve carve{base};
   CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
+  if (used > (size_t)HLOC_STATIC_SCRATCH_BYTES && p.direct) {
+    // the schedule's item list takes less than the direct screen's frame lists
+    p.direct = false;
+    used = 0;
+    CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
+  }
   if (used > (size_t)HLOC_STATIC_SCRATCH_BYTES)
     return fail(HLOC_EINVAL,
                 "the batch needs %zu bytes of scratch memory, above the %zu bytes of the static "
@@ -1372,6 +1440,14 @@ int hloc_last_regions(hloc_db *db, int32_t *out, int32_t *nq, int32_t *n_regions
   DeviceGuard g(db->device);
   if (g.err != hipSuccess) return fail(HLOC_EDEVICE, "hipSetDevice failed");
   HIPCHK(hipDeviceSynchronize());
+  if (ws->last_all) {
+    // every non-empty region, in id order, for each frame
+    int32_t *o = out;
+    for (int32_t f = 0; f < ws->last_nq; ++f)
+      for (int32_t r = 0; r < db->R; ++r)
+        if (db->h_reg_start[r + 1] > db->h_reg_start[r]) *o++ = r;
+    return HLOC_OK;
+  }
   HIPCHK(hipMemcpy(out, ws->regions.p, (size_t)ws->last_nq * ws->last_nr * sizeof(int32_t),
                    hipMemcpyDeviceToHost));
   return HLOC_OK;

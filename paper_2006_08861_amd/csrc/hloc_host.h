@@ -51,6 +51,19 @@ constexpr int kOversample = 16;     // extra rows re-scored in FP64 by the fine 
 constexpr int kRowsCoarse = 64;     // rows (representatives) per coarse work item
 constexpr int kRowsFine = 64;       // rows per fine work item
 constexpr int kWideDenseFrames = 512;  // batches from which the coarse screen uses the wide kernels
+// Fine screens without an item list: (region, frame) slots of the frame lists
+// at most, floating-point operations up to which they are used, and waves that
+// share a block's groups of frames.
+// The list costs a scan and a placing launch and one for the wide items (16 us
+// together with little to do); without it a block's rows are read again for
+// every 16 frames (36 and 60 TFLOP/s on fp32 and bf16 rows where the wide
+// kernels reach 82 and 230): even at about 1.3 GFLOP. Measured, schedule and
+// screens: 256 frames on 200k x 256 fp32 49 -> 36 us (0.2 GFLOP), 1,265 frames
+// 71 -> 57 (1.1), one frame on 10k x 256 17 -> 5.6; 2,048 frames on 500k x 512
+// bf16 235 -> 850 (51), so that stays with the list.
+constexpr int64_t kDirectSlots = (int64_t)1 << 22;
+constexpr double kDirectFlops = 1.5e9;
+constexpr int kDirectSplits = 16;
 constexpr double kUnit32 = 5.9604644775390625e-08;  // 2^-24
 
 template <class T>
@@ -86,7 +99,7 @@ constexpr int kNormSlots = 10;  // largest-norm slots of a database (see hloc_db
 struct hloc_ws {
   hloc_db *db = nullptr;
   hipStream_t stream = nullptr;  // own stream (graph capture, host-pointer calls)
-  hloc::WsBuf qp, qn2, cand1, regions, rcount, rfill, vord, rq_off, item_off, cand_off, n_cand, misc, rq,
+  hloc::WsBuf qp, qn2, cand1, regions, rcount, vord, rq_off, item_off, cand_off, n_cand, misc, rq,
       items, cand2, agg_xy, agg_tile, agg_flags, q_lp, q_scale, q_err, q_lon, slot_row, slot_len, n_rows,
       fstat,                        // fine select's per-frame statistics
       c_lp, c_scale, c_err, c_lon,  // bf16 frame copy for the coarse screen of fp8 queries
@@ -97,6 +110,8 @@ struct hloc_ws {
       cdefer;                       // frames its keys could not decide
   hloc::WsBuf s_q, s_off, s_idx, s_dist, s_xy, s_tile, s_flags;  // staging of host-pointer calls
   int32_t last_nq = 0, last_nr = 0, last_kp = 0;
+  bool fixed = false;  // buffers keep their sizes (a server's slot)
+  bool last_direct = false, last_all = false;  // the last batch: no item list, every region kept
   bool prof_on = false;
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used = 0;
@@ -129,16 +144,17 @@ struct hloc_db {
   bool has_regions = false;
   int32_t R = 0, R_nonempty = 0;
   int64_t max_region = 0;
+  double kept_rows = 0.0;              // mean size of a row's region: rows of a typical kept region
   int64_t *reg_start = nullptr;
   std::vector<int64_t> h_reg_start;
   std::vector<int64_t> h_desc_prefix;  // sum of the j largest region sizes, j = 0..R
   std::vector<int64_t> h_desc_blocks;  // sum of the j largest regions' 16-row block counts
   int64_t n_blocks = 0;                // 16-row blocks over all regions
-  int2 *blk_rows = nullptr;            // per block, regions in id order: (first row, rows)
+  int4 *blk_tab = nullptr;             // per block, regions in id order: first row, rows, region,
+                                       // block of the region
   int64_t chunks_fine = 0;             // sum over regions of ceil(size / min(tile_rows, 64))
   int32_t tile_rows = hloc::kRowsFine; // rows per narrow fine work item (multiple of 16, <= 128)
   int32_t tile_blocks = 8;             // blocks per compute unit of the screen launches
-  int32_t *nonempty_ids = nullptr;
   double *rep64 = nullptr;
   float *rep32 = nullptr;
   float *rep_n2 = nullptr;
@@ -158,6 +174,8 @@ namespace hloc {
 struct Plan {
   int32_t nq, k, nr, L1, kp, nreq, precision;
   bool exhaustive;
+  bool direct;  // the fine screen walks the block table instead of an item list
+  bool reserve = false;  // sizes buffers for smaller batches too, whose frame lists may be larger
   // the coarse stage as the fused bf16 product (short key lists per frame)
   // instead of the dense screen's frame x region words
   bool coarse_keys;
@@ -190,6 +208,15 @@ struct Carve {
 // its size, 256-byte aligned) and advances *bytes past them.
 int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *bytes = nullptr,
                      const Carve *carve = nullptr);
+// Bytes of the coarse words, and of the frame lists of a direct screen behind
+// them (the same buffer: a workspace sized for a batch has room for both for
+// batches of a third of it).
+inline size_t coarse_word_bytes(int64_t nq, int64_t R) {
+  return ((size_t)nq * R * sizeof(uint32_t) + 255) / 256 * 256;
+}
+inline size_t coarse_list_bytes(int64_t nq, int64_t R) {
+  return coarse_word_bytes(nq, R) + (size_t)nq * R * sizeof(int2);
+}
 // Enqueues one batch on stream s. req_k (device, nreq entries, or NULL) gives
 // each request's candidates per frame for the aggregation (<= p.k).
 // req_frames (device, n_frames entries, or NULL): request r pools the batch

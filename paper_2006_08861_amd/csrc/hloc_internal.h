@@ -64,11 +64,12 @@ inline int next_pow2_host(int v) {
 }
 
 // One unit of fine-screen work: rows [row_begin, row_begin + nrows) of one
-// region (absolute row indices; chunk_row = offset of the chunk inside its
-// region) against frames rq[q0 .. q0 + gq), gq <= kListFrames.
+// region (absolute row indices; block = the chunk's first 16-row block, added
+// to the offset in each rq entry) against frames rq[q0 .. q0 + gq), gq <=
+// kListFrames.
 struct Item {
   int32_t row_begin;
-  int32_t chunk_row;
+  int32_t block;
   int32_t q0;
   int32_t nrows_gq;  // nrows << 16 | gq
 };
@@ -109,6 +110,17 @@ struct ScreenArgs {
   // entry, one per XCD span of the items (NULL: each block takes a fixed
   // share of its span)
   int32_t *item_ctr;
+  // direct mode (no item list): block b of the database's block table (first
+  // row, rows, region, block of the region) against the frames that keep its
+  // region, 16 at a time: rq[region * rq_stride ..], region_count[region] of
+  // them; with all_frames every frame, whose list is the block table itself.
+  // A wave takes every `splits`-th group of 16.
+  const int4 *blk_tab;
+  int32_t n_blk;
+  const int32_t *region_count;
+  int64_t rq_stride;
+  int32_t all_frames;
+  int32_t splits;
 };
 
 // Work item of the wide screens: a chunk of rows against up to kListFrames
@@ -116,8 +128,14 @@ struct ScreenArgs {
 // (chunk it % nchunks of all rows against frames from (it / nchunks) *
 // kItemFrames).
 struct WideItem {
-  int row_begin, chunk_row, nrows, gq, q0, f0;
+  int row_begin, chunk_row, nrows, gq, q0, f0;  // chunk_row: list items, the first block
 };
+
+// Direct mode: pairs of one split. With a multiple of 32 waves (eight XCDs of
+// four-wave blocks) all splits of a block run on one XCD and share its rows.
+__host__ __device__ inline uint32_t direct_pitch(int32_t n_blk) {
+  return ((uint32_t)n_blk + 31) / 32 * 32;
+}
 
 // Items [*lo, return value) of a wide screen launch.
 __device__ __forceinline__ int wide_range(const ScreenArgs &a, int *lo) {
@@ -144,7 +162,7 @@ __device__ __forceinline__ WideItem wide_item(const ScreenArgs &a, int it) {
   } else {
     const Item itm = a.items[it];
     w.row_begin = itm.row_begin;
-    w.chunk_row = itm.chunk_row;
+    w.chunk_row = itm.block;
     w.nrows = itm.nrows_gq >> 16;
     w.gq = itm.nrows_gq & 0xFFFF;
     w.q0 = itm.q0;
@@ -163,7 +181,7 @@ __device__ __forceinline__ void wide_frame(const ScreenArgs &a, const WideItem &
     *off = (int64_t)(*fr) * a.cap + w.chunk_row;
   } else {
     *fr = e.x;
-    *off = (int64_t)e.x * a.cap + e.y + w.chunk_row / kBlockRows;
+    *off = (int64_t)e.x * a.cap + e.y + w.chunk_row;
   }
 }
 
@@ -171,6 +189,65 @@ __device__ __forceinline__ void wide_frame(const ScreenArgs &a, const WideItem &
 // dense mode).
 __device__ __forceinline__ int2 wide_entry(const ScreenArgs &a, const WideItem &w, int j) {
   return !a.dense && j < w.gq ? a.rq[w.q0 + j] : make_int2(0, 0);
+}
+
+// Direct mode: the wave's (block, split) pairs, at most 64, are looked up
+// together (lane l: pair wave + l * waves), then f(table entry, entry of lane
+// i's frame, frames left) is called for each group of 16 frames of each pair,
+// the next group's entries requested before. i: lane's frame of a group. An
+// entry is (frame, offset of the region in its list); past the frames left a
+// valid one, never stored.
+template <class F>
+__device__ __forceinline__ void direct_groups(const ScreenArgs &a, int i, F f) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave =
+      __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  const uint32_t v = wave + (uint32_t)lane * (gridDim.x * 4);  // (64 waves of pairs: < 2^31)
+  const uint32_t n = direct_pitch(a.n_blk);
+  int4 t = make_int4(0, 0, 0, 0);
+  int b = 0, y = 0, cnt = 0;
+  if (v < n * (uint32_t)a.splits) {
+    y = (int)(v / n);
+    b = (int)(v - y * n);
+    if (b < a.n_blk) {
+      t = a.blk_tab[b];
+      cnt = a.all_frames ? a.nq : a.region_count[t.z];
+    }
+  }
+  uint64_t todo = __ballot(cnt > y * kGroup);
+  if (!todo) return;
+  // the current pair (uniform) and its next group
+  int4 ct = t;
+  int cb = 0, cc = 0, grp = 0;
+  auto next_pair = [&]() {
+    const int l = __ffsll((unsigned long long)todo) - 1;
+    todo &= todo - 1;
+    ct = make_int4(__builtin_amdgcn_readlane(t.x, l), __builtin_amdgcn_readlane(t.y, l),
+                   __builtin_amdgcn_readlane(t.z, l), __builtin_amdgcn_readlane(t.w, l));
+    cb = __builtin_amdgcn_readlane(b, l);
+    cc = __builtin_amdgcn_readlane(cnt, l);
+    grp = __builtin_amdgcn_readlane(y, l) * kGroup;
+  };
+  auto entry = [&]() {
+    const int j = min(grp + i, cc - 1);
+    return a.all_frames ? make_int2(j, cb - ct.w) : a.rq[ct.z * a.rq_stride + j];
+  };
+  next_pair();
+  int2 e = entry();
+  for (;;) {
+    const int4 pt = ct;
+    const int2 pe = e;
+    const int left = cc - grp;
+    grp += a.splits * kGroup;
+    bool more = true;
+    if (grp >= cc) {
+      more = todo != 0;
+      if (more) next_pair();
+    }
+    if (more) e = entry();
+    f(pt, pe, left);
+    if (!more) break;
+  }
 }
 
 // Per-batch counters of a workspace (cleared by the prep kernel): [0] items,
@@ -182,10 +259,11 @@ constexpr int kItemCtrStride = 32;
 constexpr int kMiscItemCtr = 32;
 constexpr int kMiscInts = kMiscItemCtr + 8 * kItemCtrStride;
 
-// Padded copy and squared norm of each frame; block 0 also clears
-// zero[0 .. kMiscInts).
+// Padded copy and squared norm of each frame; also clears zero[0 ..
+// kMiscInts) and counts[0 .. n_counts).
 hipError_t launch_prep_queries(const float *q, int32_t nq, int32_t d, int32_t dp, float *qp,
-                               float *qn2, int32_t *zero, hipStream_t s);
+                               float *qn2, int32_t *zero, int32_t *counts, int32_t n_counts,
+                               hipStream_t s);
 // Dense screen, or the narrow list items (every list item where no register
 // kernel exists for the padded length); then the wide list items.
 hipError_t launch_screen_f32(const ScreenArgs &a, int32_t grid, hipStream_t s);
@@ -213,17 +291,37 @@ hipError_t launch_frames_to_lp(int32_t fmt, const float *qp, int32_t nq, int32_t
 // Blocks to launch for `items` work items of the screen at padded length dp.
 int32_t screen_grid(int64_t items, int32_t dp, int32_t max_blocks);
 
+// Fine screen of small batches without an item list (ScreenArgs: direct mode).
+hipError_t launch_screen_direct(const ScreenArgs &a, int32_t max_blocks, hipStream_t s);
+hipError_t launch_screen_direct_lp(int32_t fmt, const ScreenArgs &a, int32_t max_blocks,
+                                   hipStream_t s);
+// A wave per (block, split), at most 64 of them per wave (one per lane); whole
+// rounds of the XCDs (the pairs stay below 2^31: make_plan).
+inline int32_t direct_grid(const ScreenArgs &a, int32_t max_blocks) {
+  const int64_t v = (int64_t)direct_pitch(a.n_blk) * a.splits;
+  const int64_t g = std::max<int64_t>((v + 255) / 256, std::min<int64_t>((v + 3) / 4, max_blocks));
+  return (int32_t)((g + 7) / 8 * 8);
+}
+
 // Scheduling of the fine screen.
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
-hipError_t launch_broadcast_ids(const int32_t *ids, int32_t nr, int32_t nq, int32_t *regions,
-                                hipStream_t s);
+// What the coarse selection leaves for the fine stage, per frame f and
+// kept-region slot j (nr of them): off[f][j] the first of the slot's 16-row
+// blocks in the frame's block list, row[f][j] the region's first row,
+// len[f][j] its rows; n_cand[f] the frame's block count, n_rows[f] its
+// candidate rows. Each frame also takes a place among the frames of its
+// regions (count[r] of them, zero on entry): rq[r * rq_stride + place] =
+// (frame, off), or with rq = NULL place[f][j].
+struct SlotArgs {
+  const int64_t *reg_start;  // NULL: nothing is left
+  int32_t *off, *row, *len, *n_cand, *n_rows, *count;
+  int2 *rq;
+  int64_t rq_stride;
+  int32_t *place;
+};
 // Work items into items[0 .. n_items[0]): narrow ones (frames of regions kept
-// by at most kGroup frames) first, n_items[4] of them, then wide ones. Per
-// frame f and kept-region slot j: cand_off[f][j] the first of the slot's
-// 16-row blocks in the frame's block list, slot_row[f][j] the region's first
-// row, slot_len[f][j] its rows; n_cand[f] the frame's block count, n_rows[f]
-// its candidate rows. An rq
-// entry is (frame, cand_off of the region in that frame).
+// by at most kGroup frames) first, n_items[4] of them, then wide ones. An rq
+// entry is (frame, offset of the region in that frame's list).
 // How the items are cut: narrow chunks hold T rows; wide chunks W rows, or
 // with WM > 1 up to WM runs of W rows, against whole units of 2^log_gu groups
 // of kGroup frames (the groups the wide kernel's block takes at once). With S
@@ -233,13 +331,13 @@ struct SchedCut {
   int32_t T, W, WM, log_gu, max_steps, max_items;
   float steps_scale;
 };
+// rcount, place, off: as the coarse selection left them; rcount NULL: every
+// frame keeps every region (rq then holds nq entries, one per frame).
 hipError_t launch_sched(const int32_t *regions, int32_t nq, int32_t nr, int32_t R,
-                        const int64_t *reg_start, const SchedCut &sc, int32_t *rcount,
-                        int32_t *rfill,
-                        int32_t *vord, int32_t *rq_off, int32_t *item_off, int32_t *cand_off,
-                        int32_t *slot_row, int32_t *slot_len, int32_t *n_cand, int32_t *n_rows,
-                        int32_t *n_items,
-                        int2 *rq, Item *items, hipStream_t s);
+                        const int64_t *reg_start, const SchedCut &sc, const int32_t *rcount,
+                        const int32_t *place, const int32_t *off, int32_t *vord, int32_t *rq_off,
+                        int32_t *item_off, int32_t *n_items, int2 *rq, Item *items,
+                        hipStream_t s);
 
 // Coarse screen fused with the start of the selection (coarse_gemm.hip): a
 // bf16 MFMA product of frames and representatives whose epilogue keeps, per
@@ -283,7 +381,7 @@ hipError_t launch_coarse_gemm(CoarseGemmArgs a, hipStream_t s);
 // Positions map to source rows through the frame's region slots (slot j: the
 // rows from slot_row[f][j] on, at positions from slot_off[f][j] on; in block
 // mode slot_len[f][j] is the slot's row count), or, with
-// nslots = 0, are the rows themselves (block mode: blocks of blk_rows, every
+// nslots = 0, are the rows themselves (block mode: blocks of blk_tab, every
 // non-empty region in id order).
 struct SelRerankArgs {
   const uint32_t *cand;
@@ -296,7 +394,7 @@ struct SelRerankArgs {
   int32_t n_fixed;
   int32_t blocks;            // positions are 16-row blocks
   const int32_t *slot_len;   // block mode: nq x nslots rows of each slot's region
-  const int2 *blk_rows;      // block mode, nslots = 0: (first row, rows) of each block
+  const int4 *blk_tab;       // block mode, nslots = 0: first row, rows (x, y) of each block
   int32_t L;               // positions re-scored in FP64 (rows: <= kMaxSurvivors)
   int32_t m;               // results per frame (<= 256, <= L)
   const float *src32;      // fp32 source rows (fine stage) or NULL
@@ -318,6 +416,7 @@ struct SelRerankArgs {
   int64_t *idx_out;        // fine: nq x m original indices
   float *dist_out;         // fine: nq x m
   int32_t *reg_out;        // coarse: nq x m region ids
+  SlotArgs slots;          // coarse: what the fine stage needs of them
   int32_t *stat_fallback;  // count of frames whose certificate failed (or NULL)
   // per frame, written once by the frame's block or wave (or NULL): candidate
   // count, rows re-scored in FP64 (survivors and band), band rows, flags (1:
@@ -370,13 +469,11 @@ hipError_t prepare_screen_kernels();  // also the low-precision screens
 hipError_t prepare_screen_lp_kernels();
 hipError_t prepare_select_kernels();
 hipError_t prepare_aggregate_kernels();
-hipError_t prepare_sched_kernels();
 hipError_t prepare_coarse_gemm_kernels();
 inline hipError_t prepare_kernels() {
   hipError_t e = prepare_screen_kernels();
   if (e == hipSuccess) e = prepare_coarse_gemm_kernels();
   if (e == hipSuccess) e = prepare_select_kernels();
-  if (e == hipSuccess) e = prepare_sched_kernels();
   if (e == hipSuccess) e = prepare_aggregate_kernels();
   return e;
 }

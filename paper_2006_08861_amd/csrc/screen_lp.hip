@@ -271,12 +271,12 @@ __global__ __launch_bounds__(256) void k_screen_lp(ScreenArgs a) {
       off = (int64_t)fr * a.cap + chunk_row;
     } else {
       row_begin = nx.row_begin;
-      chunk_row = nx.chunk_row;
+      chunk_row = nx.block;
       nrows = nx.nrows_gq >> 16;
       gq = nx.nrows_gq & 0xFFFF;
       if (i < gq) {
         fr = ne.x;
-        off = (int64_t)ne.x * a.cap + ne.y + chunk_row / kBlockRows;
+        off = (int64_t)ne.x * a.cap + ne.y + chunk_row;
       }
       if (itn < hi) nx = a.items[itn];
     }
@@ -329,6 +329,39 @@ __global__ __launch_bounds__(256) void k_screen_lp(ScreenArgs a) {
       if (i < (nx.nrows_gq & 0xFFFF)) ne = a.rq[nx.q0 + i];
     }
   }
+}
+
+// Fine screen without an item list (direct mode), as the fp32 one.
+template <int FMT, int NS>
+__global__ __launch_bounds__(256) void k_screen_direct_lp(ScreenArgs a) {
+  constexpr int ROWU4 = 4 * NS;
+  const int lane = lane_id(), i = lane & 15, g = lane >> 4;
+  const uint4 *rows = static_cast<const uint4 *>(a.rows_lp);
+  const uint4 *frames = static_cast<const uint4 *>(a.q_lp);
+  direct_groups(a, i, [&](int4 t, int2 e, int left) {
+    const int row0 = 4 * g;
+    const uint4 *rp = rows + (int64_t)(t.x + min(i, t.y - 1)) * ROWU4 + g;
+    const uint4 *qp = frames + (int64_t)e.x * ROWU4 + g;
+    uint4 av[NS], bv[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) av[s] = rp[4 * s];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) bv[s] = qp[4 * s];
+    const float qn = a.qn2[e.x];
+    const float qs = FMT == HLOC_FP8 ? a.q_scale[e.x] : 1.f;
+    v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) acc = lp_mfma<FMT>(av[s], bv[s], acc);
+    uint32_t wd[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = t.x + min(row0 + r, t.y - 1);
+      const float rs = FMT == HLOC_FP8 ? a.row_scale[row] : 1.f;
+      wd[r] = row0 + r < t.y ? lp_word<FMT>(qn, a.row_n2[row], acc[r], qs, rs) : 0xFFFFFFFFu;
+    }
+    const uint32_t m = block_min16(wd);
+    if (i < left && g == 0) a.cand[(int64_t)e.x * a.cap + e.y + t.w] = m;
+  });
 }
 
 // Wide list items, as the fp32 wide screen: the chunk's rows (and fp8 scales)
@@ -540,7 +573,7 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
     } else if (itn < lim) {
       nxt = a.items[itn];
     }
-    const int row_begin = cur.row_begin, chunk_row = cur.chunk_row, q0 = cur.q0;
+    const int row_begin = cur.row_begin, block0 = cur.block, q0 = cur.q0;
     const int nrows = cur.nrows_gq >> 16, gq = cur.nrows_gq & 0xFFFF;
     const int nrun = (nrows + kWideRowsRs - 1) / kWideRowsRs;
     const int ng = (gq + kGroup - 1) / kGroup;
@@ -637,7 +670,7 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
     const int2 e = s_e[(K) * kGroup + i];                                        \
     const float qn = s_qn[(K) * kGroup + i], qs = s_qs[(K) * kGroup + i];        \
     const bool fok = (K) * kGroup + i < gq;                                      \
-    const int blk = (chunk_row + c * kWideRowsRs) / kBlockRows;                  \
+    const int blk = block0 + c * (kWideRowsRs / kBlockRows);                     \
     _Pragma("unroll") for (int h = 0; h < 2; ++h) {                              \
       if (c * kWideRowsRs + 32 * w + 16 * h < nrows) { /* (uniform) */           \
         uint32_t wd[4];                                                          \
@@ -757,6 +790,38 @@ hipError_t launch_screen_lp(int32_t fmt, const ScreenArgs &a, int32_t grid, hipS
   if (a.rows_per_item % 16 != 0) return hipErrorInvalidValue;
   if (fmt == HLOC_BF16) return launch_lp_fmt<HLOC_BF16>(a, grid, 0, s);
   if (fmt == HLOC_FP8) return launch_lp_fmt<HLOC_FP8>(a, grid, 0, s);
+  return hipErrorInvalidValue;
+}
+
+template <int FMT>
+hipError_t launch_direct_lp(const ScreenArgs &a, int32_t max_blocks, hipStream_t s) {
+  const dim3 grid(direct_grid(a, max_blocks));
+  switch (lp_pieces(FMT, a.dp)) {
+#define HLOC_LP_CASE(N) \
+  case N:               \
+    return launch_kernel(k_screen_direct_lp<FMT, N>, grid, dim3(256), 0, s, a);
+    HLOC_LP_CASE(1)
+    HLOC_LP_CASE(2)
+    HLOC_LP_CASE(3)
+    HLOC_LP_CASE(4)
+    HLOC_LP_CASE(5)
+    HLOC_LP_CASE(6)
+    HLOC_LP_CASE(8)
+    HLOC_LP_CASE(10)
+    HLOC_LP_CASE(12)
+    HLOC_LP_CASE(16)
+#undef HLOC_LP_CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_screen_direct_lp(int32_t fmt, const ScreenArgs &a, int32_t max_blocks,
+                                   hipStream_t s) {
+  if (a.n_blk <= 0 || a.nq <= 0) return hipSuccess;
+  if (a.splits < 1) return hipErrorInvalidValue;
+  if (fmt == HLOC_BF16) return launch_direct_lp<HLOC_BF16>(a, max_blocks, s);
+  if (fmt == HLOC_FP8) return launch_direct_lp<HLOC_FP8>(a, max_blocks, s);
   return hipErrorInvalidValue;
 }
 

@@ -552,7 +552,7 @@ __device__ __forceinline__ uint32_t block_row(const SelRerankArgs &a, const int3
                                               int nslots, uint32_t p, int t) {
   int row0, len;
   if (nslots == 0) {
-    const int2 br = a.blk_rows[p];
+    const int4 br = a.blk_tab[p];
     row0 = br.x;
     len = br.y;
   } else {
@@ -597,6 +597,44 @@ __device__ __forceinline__ int xcd_frame(int b, int n) {
   constexpr int kXcd = 8;
   const int x = b % kXcd, j = b / kXcd, q = n / kXcd, r = n % kXcd;
   return x * q + min(x, r) + j;
+}
+
+// Coarse stage, one wave: the frame's kept regions (id(j), -1: none, j < m)
+// with their places in its block list and among their regions' frames.
+template <class Id>
+__device__ __forceinline__ void leave_slots(const SlotArgs &o, int f, int m, Id id) {
+  if (!o.reg_start) return;
+  const int lane = lane_id();
+  int base = 0, rows = 0;
+  for (int j0 = 0; j0 < m; j0 += 64) {
+    const int j = j0 + lane;
+    const int r = j < m ? id(j) : -1;
+    int r0 = 0, sz = 0, pos = 0;
+    if (r >= 0) {
+      pos = atomicAdd(&o.count[r], 1);
+      r0 = (int)o.reg_start[r];
+      sz = (int)(o.reg_start[r + 1] - r0);
+    }
+    const int nb = (sz + kBlockRows - 1) / kBlockRows;
+    const int inc = wave_incl_scan(nb);
+    const int64_t s = (int64_t)f * m + j;
+    if (j < m) {
+      o.off[s] = base + inc - nb;
+      o.row[s] = r0;
+      o.len[s] = sz;
+      if (r >= 0) {
+        if (o.rq) o.rq[r * o.rq_stride + pos] = make_int2(f, base + inc - nb);
+        else o.place[s] = pos;
+      }
+    }
+    base += __builtin_amdgcn_readlane(inc, 63);
+    rows += sz;
+  }
+  rows = wave_sum_i32(rows);
+  if (lane == 0) {
+    o.n_cand[f] = base;
+    o.n_rows[f] = rows;
+  }
 }
 
 template <int BLOCK>
@@ -1013,6 +1051,10 @@ __global__ __launch_bounds__(BLOCK) void k_select_rerank(SelRerankArgs a) {
           ok ? (float)__longlong_as_double((long long)sh.sort_hi[i]) : __builtin_inff();
     }
   }
+  if (a.reg_out && w == 0)
+    leave_slots(a.slots, f, a.m, [&](int j) {
+      return j < have && sh.sort_hi[j] != kKeyNone ? (int)sh.sort_lo[j] : -1;
+    });
 }
 
 // Orders the wave's LDS accesses before and after (no block barrier).
@@ -1248,7 +1290,7 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
         const int p = __builtin_amdgcn_readfirstlane((int)list[h >> 1]);
         int row0, len;
         if (a.nslots == 0) {
-          const int2 br = a.blk_rows[p];
+          const int4 br = a.blk_tab[p];
           row0 = br.x;
           len = br.y;
         } else {
@@ -1431,6 +1473,8 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
       a.reg_out[(int64_t)f * m + i] = ok ? (int32_t)srt_lo[cur * m + i] : -1;
     }
   }
+  if (!kBlocks && w == 0)
+    leave_slots(a.slots, f, m, [&](int j) { return j < have ? (int)srt_lo[cur * m + j] : -1; });
 }
 
 constexpr size_t select_lds_bytes(int nslots, int cache) {
@@ -1501,7 +1545,7 @@ hipError_t launch_select_rerank(SelRerankArgs a, hipStream_t s) {
   if (a.nslots < 0 || a.nslots > kMaxSlots || (a.nslots > 0 && (!a.slot_off || !a.slot_row)))
     return hipErrorInvalidValue;
   if (a.blocks && ((a.nslots > 0 && !a.slot_len) ||
-                   (a.nslots == 0 && !a.blk_rows)))
+                   (a.nslots == 0 && !a.blk_tab)))
     return hipErrorInvalidValue;
   if (a.keys) {
     // key mode: every word and its source row cached, no slots, rows

@@ -131,6 +131,7 @@ int make_slot(hloc_server *srv, const Plan &full, Slot &s) {
   const int32_t F = srv->cfg.max_batch_frames, k = srv->cfg.k;
   CHK(new_ws(db, &s.ws));
   CHK(ensure_workspace(s.ws, full, false));
+  s.ws->fixed = true;
   CHK(slot_alloc(&s.d_q, &s.h_q, (size_t)F * db->d));
   CHK(slot_alloc(&s.d_off, &s.h_off, (size_t)F + 1));
   CHK(slot_alloc(&s.d_k, &s.h_k, (size_t)F + 1));
@@ -299,6 +300,7 @@ int hloc_server_create(hloc_db *db, const hloc_server_config *cfg, hloc_server *
   if (c.hbm_budget_bytes < 0) return fail(HLOC_EINVAL, "hbm_budget_bytes must be >= 0");
   Plan full;
   CHK(make_plan(db, c.max_batch_frames, c.k, c.n_regions, c.max_batch_frames, c.precision, &full));
+  full.direct = false;  // (smaller batches find room for its lists behind their coarse words)
   DeviceGuard g(db->device);
   if (g.err != hipSuccess) return fail(HLOC_EDEVICE, "hipSetDevice failed");
   hloc_server *srv = new (std::nothrow) hloc_server();

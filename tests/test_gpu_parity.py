@@ -1056,3 +1056,43 @@ def test_selection_list_edges(torch_cuda, k, n_reg):
                       q[:40], k)
     say(f"[ok] {st}")
     assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("n_reg", [3, 9])
+@pytest.mark.parametrize("precision,d", [("fp32", 30), ("fp32", 64), ("fp32", 200), ("fp32", 256),
+                                         ("fp32", 512), ("fp32", 700), ("bf16", 64), ("bf16", 160),
+                                         ("bf16", 512), ("fp8", 128), ("fp8", 384), ("fp8", 512)])
+def test_item_list_and_direct_screen_agree(torch_cuda, precision, d, n_reg):
+    # one batch past the direct screen's work (an item list, wide regions kept
+    # by thousands of frames; n_reg 9: every region) and the same frames in
+    # batches of 1, 16, 17, 33 and 500 (no list): the same bits, and the first
+    # 40 frames match the oracle
+    rng = np.random.default_rng(28)
+    sizes = np.array([333, 129, 64, 40, 1, 40, 15, 40, 17])
+    region_of = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    n, R = len(region_of), len(sizes)
+    feats = rng.standard_normal((n, d)).astype(np.float32)
+    feats[:526] *= 0.2
+    feats[526:] += 0.6
+    xy = rng.uniform(0, 40, size=(n, 2))
+    rows = n if n_reg == R else n_reg * float((sizes ** 2).sum()) / n
+    nq = int(1.6e9 / (2 * rows * ((d + 31) // 32 * 32))) + 300
+    q = (feats[rng.integers(0, 526, nq)] + 0.05 * rng.standard_normal((nq, d))).astype(np.float32)
+    say(f"[case] {nq} frames, d {d}, {precision}, n_reg {n_reg}")
+    db = make_db(feats, xy, region_of, R, mirrors=MIRRORS[precision])
+    full = run_device(torch_cuda, db, q, 9, n_reg, precision=precision)
+    info = db.info()
+    assert info["items"] > info["narrow_items"]
+    at = 0
+    for step in (1, 16, 17, 33, 500):
+        part = run_device(torch_cuda, db, q[at:at + step], 9, n_reg, precision=precision)
+        for key in part:
+            assert part[key].tobytes() == full[key][at:at + step].tobytes(), (step, key)
+        at += step
+    db.close()
+    ora = oracle.localize(feats, xy, region_of, R, q[:40], np.arange(41), 9, n_reg,
+                          (0.5, 1, 0.0, 0))
+    st = judge_frames(full["idx"][:40], full["dist"][:40], None, ora, feats, region_of, R,
+                      q[:40], 9)
+    say(f"[ok] {st} info={info}")
+    assert st["recall"] == 1.0
