@@ -1096,3 +1096,26 @@ def test_item_list_and_direct_screen_agree(torch_cuda, precision, d, n_reg):
                       q[:40], 9)
     say(f"[ok] {st} info={info}")
     assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("spread,agg", [(0.05, (0.3, 10, 3.0, 20)), (30.0, (0.3, 10, 3.0, 20)),
+                                        (600.0, (0.3, 64, 0.0, 99)), (600.0, (0.3, 64, 3.0, 50)),
+                                        (3.0, (0.5, 1, 0.0, 0))])
+@pytest.mark.parametrize("many", [False, True])
+def test_aggregation_table_sizes(torch_cuda, spread, agg, many):
+    # requests pooling 0, 256, 512, 768 and 4,096 candidates (the limits of the
+    # small table and of the large one) from one tile to all distinct tiles,
+    # with tests that pass at once, late or never; more requests than compute
+    # units take the one-wave kernel and its list, fewer the large kernel
+    rng = np.random.default_rng(29)
+    n, d, k = 5000, 16, 256
+    region_of = (np.arange(n) // 500).astype(np.int32)
+    feats = rng.standard_normal((n, d)).astype(np.float32)
+    xy = rng.uniform(0, spread, size=(n, 2))
+    counts = [16, 0, 2, 3, 1, 16, 15, 2] + [1] * (300 if many else 20)
+    offs = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    q = rng.standard_normal((offs[-1], d)).astype(np.float32)
+    st, info, out = check_all(torch_cuda, feats, xy, region_of, 10, q, k, 2, offs=offs, agg=agg,
+                              name=f"pools over {spread} m, many={many}")
+    assert st["recall"] == 1.0
+    assert out["flags"][1] == 2
