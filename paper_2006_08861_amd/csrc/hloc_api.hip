@@ -219,7 +219,6 @@ int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *byte
   }
   if (db->lp[HLOC_FP8].rows && db->lp[HLOC_BF16].reps) {
     CHK(fit(ws->c_lp, (size_t)nq * db->dp * 2));
-    CHK(fit(ws->c_scale, (size_t)nq * sizeof(float)));
     CHK(fit(ws->c_err, (size_t)nq * sizeof(float)));
     CHK(fit(ws->c_lon, (size_t)nq * sizeof(float)));
   }
@@ -298,16 +297,29 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   const int cfmt = coarse_bf16 ? HLOC_BF16 : fmt;
   const LpMirror *cpm = cfmt ? &db->lp[cfmt] : nullptr;
   void *c_lp = coarse_bf16 ? ws->c_lp.p : ws->q_lp.p;
-  float *c_scale = as<float>(coarse_bf16 ? ws->c_scale : ws->q_scale);
   float *c_err = as<float>(coarse_bf16 ? ws->c_err : ws->q_err);
   float *c_lon = as<float>(coarse_bf16 ? ws->c_lon : ws->q_lon);
-  HIPCHK(launch_prep_queries(q, p.nq, db->d, db->dp, qp, qn2, misc, as<int32_t>(ws->rcount),
-                             p.exhaustive ? 0 : db->R, s));
-  if (fmt)
-    HIPCHK(launch_frames_to_lp(fmt, qp, p.nq, db->dp, ws->q_lp.p, as<float>(ws->q_scale),
-                               as<float>(ws->q_err), as<float>(ws->q_lon), s));
-  if (coarse_bf16 && !p.exhaustive)
-    HIPCHK(launch_frames_to_lp(HLOC_BF16, qp, p.nq, db->dp, c_lp, c_scale, c_err, c_lon, s));
+  PrepArgs pa{};
+  pa.q = q;
+  pa.nq = p.nq;
+  pa.d = db->d;
+  pa.dp = db->dp;
+  pa.period = label_frames;
+  pa.qp = qp;
+  pa.qn2 = qn2;
+  pa.zero = misc;
+  pa.counts = as<int32_t>(ws->rcount);
+  pa.n_counts = p.exhaustive ? 0 : db->R;
+  pa.lp = ws->q_lp.p;
+  pa.scale = as<float>(ws->q_scale);
+  pa.err = as<float>(ws->q_err);
+  pa.lon = as<float>(ws->q_lon);
+  if (coarse_bf16 && !p.exhaustive) {
+    pa.c_lp = c_lp;
+    pa.c_err = c_err;
+    pa.c_lon = c_lon;
+  }
+  HIPCHK(launch_prep_frames(fmt, pa, s));
   // fp32 accumulation of rounded products: |q~||d~| <= 1.004 |q||d| for bf16,
   // <= (1 + 2^-4)^2 |q||d| for fp8 (relative rounding of at most 2^-4 per
   // value; subnormals are absolute and covered by the rounding-error terms)
@@ -358,7 +370,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
       sa.rows_lp = cpm->reps;
       sa.q_lp = c_lp;
       sa.row_scale = cpm->rep_scale;
-      sa.q_scale = c_scale;
+      sa.q_scale = as<float>(ws->q_scale);
       HIPCHK(wide_dense ? launch_screen_wide_lp(cfmt, sa, p.grid1, db->num_cu, s)
                         : launch_screen_lp(cfmt, sa, p.grid1, s));
     } else {
@@ -629,8 +641,8 @@ void for_each_buf(hloc_ws *ws, F f) {
                    &ws->agg_tile, &ws->agg_flags, &ws->s_q,     &ws->s_off,   &ws->s_idx,
                    &ws->s_dist,   &ws->s_xy,     &ws->s_tile,   &ws->s_flags, &ws->q_lp,
                    &ws->q_scale,  &ws->q_err,    &ws->q_lon,   &ws->slot_row, &ws->slot_len, &ws->n_rows, &ws->fstat,
-                   &ws->c_lp,     &ws->c_scale,  &ws->c_err,   &ws->c_lon,   &ws->agg_big,
-                   &ws->lab_off,  &ws->lab_list, &ws->lab_q,  &ws->ckeys,
+                   &ws->c_lp,     &ws->c_err,   &ws->c_lon,   &ws->agg_big,
+                   &ws->lab_off,  &ws->lab_list,  &ws->ckeys,
                    &ws->cslots,   &ws->cbounds,  &ws->cdefer};
   for (WsBuf *b : bufs) f(*b);
 }
@@ -1157,12 +1169,7 @@ int hloc_query_labels_async(hloc_db *db, const float *q, int32_t nq, int32_t k,
     // label-major slabs of idx and dist in one pass
     Plan pl;
     CHK(make_plan(db, nq * P, k, n_regions, nreq, precision, &pl));
-    const size_t fbytes = (size_t)nq * db->d * sizeof(float);
-    CHK(ws_ensure(ws, ws->lab_q, fbytes * (size_t)P));
-    for (int32_t p = 0; p < P; ++p)
-      HIPCHK(hipMemcpyAsync(static_cast<char *>(ws->lab_q.p) + fbytes * (size_t)p, q, fbytes,
-                            hipMemcpyDeviceToDevice, s));
-    CHK(enqueue_query(ws, pl, as<float>(ws->lab_q), nullptr, nullptr, idx, dist, nullptr,
+    CHK(enqueue_query(ws, pl, q, nullptr, nullptr, idx, dist, nullptr,
                       nullptr, nullptr, s, nullptr, 0, -1, nq));
   } else {
     // one search per label, each writing its nq x k slab of idx and dist

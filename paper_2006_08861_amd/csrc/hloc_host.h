@@ -102,10 +102,9 @@ struct hloc_ws {
   hloc::WsBuf qp, qn2, cand1, regions, rcount, vord, rq_off, item_off, cand_off, n_cand, misc, rq,
       items, cand2, agg_xy, agg_tile, agg_flags, q_lp, q_scale, q_err, q_lon, slot_row, slot_len, n_rows,
       fstat,                        // fine select's per-frame statistics
-      c_lp, c_scale, c_err, c_lon,  // bf16 frame copy for the coarse screen of fp8 queries
+      c_lp, c_err, c_lon,           // bf16 frame copy for the coarse screen of fp8 queries
       agg_big,                      // requests for the large-list aggregation kernel
       lab_off, lab_list,            // frame lists of a query over subspace labels
-      lab_q,                        // its frames once per label
       ckeys, cslots, cbounds,       // key lists of the fused coarse product
       cdefer;                       // frames its keys could not decide
   hloc::WsBuf s_q, s_off, s_idx, s_dist, s_xy, s_tile, s_flags;  // staging of host-pointer calls
@@ -223,7 +222,8 @@ inline size_t coarse_list_bytes(int64_t nq, int64_t R) {
 // frames req_frames[req_offsets[r] .. req_offsets[r+1]-1] instead of the
 // frames req_offsets[r] .. req_offsets[r+1]-1.
 // label >= 0: the coarse selection keeps only regions with that label;
-// label_frames > 0: frame f keeps only regions labelled f / label_frames.
+// label_frames > 0: q holds label_frames frames, frame f of the batch is row
+// f % label_frames of it and keeps only regions labelled f / label_frames.
 int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req_offsets,
                   const int32_t *req_k, int64_t *idx, float *dist, double *xy, int32_t *tile,
                   int32_t *flags, hipStream_t s, const int32_t *req_frames = nullptr,

@@ -259,11 +259,22 @@ constexpr int kItemCtrStride = 32;
 constexpr int kMiscItemCtr = 32;
 constexpr int kMiscInts = kMiscItemCtr + 8 * kItemCtrStride;
 
-// Padded copy and squared norm of each frame; also clears zero[0 ..
-// kMiscInts) and counts[0 .. n_counts).
-hipError_t launch_prep_queries(const float *q, int32_t nq, int32_t d, int32_t dp, float *qp,
-                               float *qn2, int32_t *zero, int32_t *counts, int32_t n_counts,
-                               hipStream_t s);
+// Preparation of a batch's frames: padded copy and squared norm of each,
+// low-precision copies, and cleared counters.
+struct PrepArgs {
+  const float *q;       // frames of d values
+  int32_t nq, d, dp;
+  int32_t period;       // > 0: frame f is row f % period of q
+  float *qp, *qn2;      // nq x dp, nq
+  int32_t *zero;        // kMiscInts counters to clear
+  int32_t *counts;      // n_counts more
+  int32_t n_counts;
+  void *lp;             // the fine screen's copy, its scale (fp8) and norms
+  float *scale, *err, *lon;
+  void *c_lp;           // bf16 copy for the coarse screen of fp8 queries, or NULL
+  float *c_err, *c_lon;
+};
+hipError_t launch_prep_frames(int32_t fmt, const PrepArgs &a, hipStream_t s);
 // Dense screen, or the narrow list items (every list item where no register
 // kernel exists for the padded length); then the wide list items.
 hipError_t launch_screen_f32(const ScreenArgs &a, int32_t grid, hipStream_t s);
@@ -284,10 +295,6 @@ bool lp_wide_rs(int32_t fmt, int32_t dp);
 // per-row norms of the rounding error and of the rounded row.
 hipError_t launch_rows_to_lp(int32_t fmt, const float *src, int64_t n, int32_t dp, void *dst,
                              float *scale, float *max_err, float *max_norm, hipStream_t s);
-// The same for the padded frames, with per-frame norms of the rounding error
-// (q_err) and of the rounded frame (q_lon).
-hipError_t launch_frames_to_lp(int32_t fmt, const float *qp, int32_t nq, int32_t dp, void *dst,
-                               float *scale, float *q_err, float *q_lon, hipStream_t s);
 // Blocks to launch for `items` work items of the screen at padded length dp.
 int32_t screen_grid(int64_t items, int32_t dp, int32_t max_blocks);
 

@@ -20,38 +20,6 @@ namespace hloc {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_prep_queries(const float *__restrict__ q, int nq, int d,
-                                                      int dp, float *__restrict__ qp,
-                                                      float *__restrict__ qn2,
-                                                      int32_t *__restrict__ zero,
-                                                      int32_t *__restrict__ counts,
-                                                      int n_counts) {
-  if (blockIdx.x == 0 && zero)
-    for (int t = threadIdx.x; t < kMiscInts; t += 256) zero[t] = 0;
-  for (int t = blockIdx.x * 256 + threadIdx.x; t < n_counts; t += gridDim.x * 256) counts[t] = 0;
-  const int f = blockIdx.x * 4 + wave_id();
-  const int lane = lane_id();
-  if (f >= nq) return;
-  const float *src = q + (int64_t)f * d;
-  float *dst = qp + (int64_t)f * dp;
-  float acc = 0.f;
-  for (int c = lane; c < dp; c += 64) {
-    const float v = c < d ? src[c] : 0.f;
-    dst[c] = v;
-    acc = fmaf(v, v, acc);
-  }
-  acc = wave_sum_f32(acc);
-  if (lane == 0) qn2[f] = acc;
-}
-
-hipError_t launch_prep_queries(const float *q, int32_t nq, int32_t d, int32_t dp, float *qp,
-                               float *qn2, int32_t *zero, int32_t *counts, int32_t n_counts,
-                               hipStream_t s) {
-  if (nq <= 0) return hipSuccess;
-  return launch_kernel(k_prep_queries, dim3((nq + 3) / 4), dim3(256), 0, s, q, nq, d, dp, qp, qn2,
-                       zero, counts, n_counts);
-}
-
 template <bool DENSE>
 __global__ __launch_bounds__(256) void k_screen_f32(ScreenArgs a) {
   extern __shared__ float4 qs4[];  // kGroup x (dp + 4) floats, 16-byte aligned

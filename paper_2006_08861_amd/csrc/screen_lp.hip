@@ -130,43 +130,63 @@ hipError_t launch_rows_to_lp(int32_t fmt, const float *src, int64_t n, int32_t d
   return hipErrorInvalidValue;
 }
 
-// Per-frame copies for the low-precision screens: the same rounding as the
-// rows (fp8: a scale per frame), and the norms of the rounding error (q_err)
-// and of the rounded frame (q_lon), rounded up. One wave per frame.
-template <int FMT>
-__global__ void k_frames_to_lp(const float *__restrict__ qp, int nq, int dp, void *dst_,
-                               float *__restrict__ scale, float *__restrict__ q_err,
-                               float *__restrict__ q_lon) {
-  const int f = blockIdx.x * 4 + wave_id(), lane = lane_id();
-  if (f >= nq) return;
-  const float *r = qp + (int64_t)f * dp;
+// One frame per wave, its values in registers (4 consecutive ones per lane
+// and 256-value chunk): padded fp32 copy and squared norm and, for the low-
+// precision screens, the copy rounded the same way as the rows (fp8: with a
+// scale per frame) with the norms of the rounding error (q_err) and of the
+// rounded frame (q_lon), rounded up. FMT: the fine screen's copy (0: none);
+// COARSE: a bf16 copy beside it for the coarse screen. One launch and one read
+// of the frames instead of two or three (32,768 frames x 512 to bf16 54 -> 32
+// us, 2,048 frames to fp8 and bf16 18 -> 8.3).
+constexpr int kPrepDim = HLOC_MAX_DIM;  // padded length at most (a multiple of 32)
+static_assert(kPrepDim <= 1024, "four chunks of 256 values");
+
+template <int FMT, int CH>
+__device__ __forceinline__ void frame_copy(const float4 (&v)[CH], int f, int dp, void *dst,
+                                           float *__restrict__ scale, float *__restrict__ q_err,
+                                           float *__restrict__ q_lon) {
+  const int lane = lane_id();
   double e2 = 0.0, n2 = 0.0;
+  auto add = [&](double t, float x) {
+    e2 = fma(t - (double)x, t - (double)x, e2);
+    n2 = fma(t, t, n2);
+  };
   if (FMT == HLOC_BF16) {
-    uint16_t *o = static_cast<uint16_t *>(dst_) + (int64_t)f * dp;
-    for (int c = lane; c < dp; c += 64) {
-      const uint16_t h = bf16_rne(r[c]);
-      o[c] = h;
-      const double t = (double)bf16_to_f32(h);
-      e2 = fma(t - (double)r[c], t - (double)r[c], e2);
-      n2 = fma(t, t, n2);
+    uint16_t *o = static_cast<uint16_t *>(dst) + (int64_t)f * dp;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int c = 256 * u + 4 * lane;
+      if (c >= dp) continue;
+      const ushort4 h = make_ushort4(bf16_rne(v[u].x), bf16_rne(v[u].y), bf16_rne(v[u].z),
+                                     bf16_rne(v[u].w));
+      *reinterpret_cast<ushort4 *>(o + c) = h;
+      add((double)bf16_to_f32(h.x), v[u].x);
+      add((double)bf16_to_f32(h.y), v[u].y);
+      add((double)bf16_to_f32(h.z), v[u].z);
+      add((double)bf16_to_f32(h.w), v[u].w);
     }
   } else {
-    uint8_t *o = static_cast<uint8_t *>(dst_) + (int64_t)f * dp;
+    uint8_t *o = static_cast<uint8_t *>(dst) + (int64_t)f * dp;
     float amax = 0.f;
-    for (int c = lane; c < dp; c += 64) amax = fmaxf(amax, fabsf(r[c]));
+#pragma unroll
+    for (int u = 0; u < CH; ++u)
+      amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[u].x), fabsf(v[u].y)),
+                               fmaxf(fabsf(v[u].z), fabsf(v[u].w))));
     for (int o2 = 32; o2 > 0; o2 >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o2));
     const float sc = amax > 0.f ? amax / kFp8Max : 1.f;
     const float inv = amax > 0.f ? kFp8Max / amax : 1.f;
     if (lane == 0) scale[f] = sc;
-    for (int c = 2 * lane; c < dp; c += 128) {
-      const uint32_t p = fp8_pair(clamp_fp8(r[c] * inv), clamp_fp8(r[c + 1] * inv));
-      o[c] = (uint8_t)p;
-      o[c + 1] = (uint8_t)(p >> 8);
-      const double t0 = (double)fp8_to_f32(p & 0xFF) * sc, t1 = (double)fp8_to_f32(p >> 8) * sc;
-      e2 = fma(t0 - (double)r[c], t0 - (double)r[c], e2);
-      e2 = fma(t1 - (double)r[c + 1], t1 - (double)r[c + 1], e2);
-      n2 = fma(t0, t0, n2);
-      n2 = fma(t1, t1, n2);
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int c = 256 * u + 4 * lane;
+      if (c >= dp) continue;
+      const uint32_t p = fp8_pair(clamp_fp8(v[u].x * inv), clamp_fp8(v[u].y * inv)) |
+                         fp8_pair(clamp_fp8(v[u].z * inv), clamp_fp8(v[u].w * inv)) << 16;
+      *reinterpret_cast<uint32_t *>(o + c) = p;
+      add((double)fp8_to_f32(p & 0xFF) * sc, v[u].x);
+      add((double)fp8_to_f32(p >> 8 & 0xFF) * sc, v[u].y);
+      add((double)fp8_to_f32(p >> 16 & 0xFF) * sc, v[u].z);
+      add((double)fp8_to_f32(p >> 24) * sc, v[u].w);
     }
   }
   e2 = wave_sum_f64(e2);
@@ -177,17 +197,63 @@ __global__ void k_frames_to_lp(const float *__restrict__ qp, int nq, int dp, voi
   }
 }
 
-hipError_t launch_frames_to_lp(int32_t fmt, const float *qp, int32_t nq, int32_t dp, void *dst,
-                               float *scale, float *q_err, float *q_lon, hipStream_t s) {
-  if (nq <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((nq + 3) / 4));
+template <int FMT, bool COARSE, int CH>
+__global__ __launch_bounds__(256) void k_prep_frames(PrepArgs a) {
+  if (blockIdx.x == 0)
+    for (int t = threadIdx.x; t < kMiscInts; t += 256) a.zero[t] = 0;
+  for (int t = blockIdx.x * 256 + threadIdx.x; t < a.n_counts; t += gridDim.x * 256) a.counts[t] = 0;
+  const int f = blockIdx.x * 4 + wave_id(), lane = lane_id();
+  if (f >= a.nq) return;
+  const float *src = a.q + (int64_t)(a.period > 0 ? f % a.period : f) * a.d;
+  // whole 16-byte loads where every row starts on 16 bytes
+  const bool vec = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
+  float4 v[CH];
+#pragma unroll
+  for (int u = 0; u < CH; ++u) {
+    const int c = 256 * u + 4 * lane;
+    v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (vec) {
+      if (c < a.d) v[u] = *reinterpret_cast<const float4 *>(src + c);
+    } else {
+      if (c < a.d) v[u].x = src[c];
+      if (c + 1 < a.d) v[u].y = src[c + 1];
+      if (c + 2 < a.d) v[u].z = src[c + 2];
+      if (c + 3 < a.d) v[u].w = src[c + 3];
+    }
+  }
+  float acc = 0.f;
+#pragma unroll
+  for (int u = 0; u < CH; ++u) {
+    const int c = 256 * u + 4 * lane;
+    if (c < a.dp) *reinterpret_cast<float4 *>(a.qp + (int64_t)f * a.dp + c) = v[u];
+    acc = fmaf(v[u].x, v[u].x, acc);
+    acc = fmaf(v[u].y, v[u].y, acc);
+    acc = fmaf(v[u].z, v[u].z, acc);
+    acc = fmaf(v[u].w, v[u].w, acc);
+  }
+  acc = wave_sum_f32(acc);
+  if (lane == 0) a.qn2[f] = acc;
+  if constexpr (FMT != 0) frame_copy<FMT, CH>(v, f, a.dp, a.lp, a.scale, a.err, a.lon);
+  if constexpr (COARSE) frame_copy<HLOC_BF16, CH>(v, f, a.dp, a.c_lp, nullptr, a.c_err, a.c_lon);
+}
+
+template <int CH>
+hipError_t launch_prep_ch(int32_t fmt, const PrepArgs &a, hipStream_t s) {
+  const dim3 grid((unsigned)((a.nq + 3) / 4)), block(256);
+  if (fmt == 0) return launch_kernel(k_prep_frames<0, false, CH>, grid, block, 0, s, a);
   if (fmt == HLOC_BF16)
-    return launch_kernel(k_frames_to_lp<HLOC_BF16>, grid, dim3(256), 0, s, qp, nq, dp, dst, scale,
-                         q_err, q_lon);
-  if (fmt == HLOC_FP8)
-    return launch_kernel(k_frames_to_lp<HLOC_FP8>, grid, dim3(256), 0, s, qp, nq, dp, dst, scale,
-                         q_err, q_lon);
-  return hipErrorInvalidValue;
+    return launch_kernel(k_prep_frames<HLOC_BF16, false, CH>, grid, block, 0, s, a);
+  if (fmt != HLOC_FP8) return hipErrorInvalidValue;
+  return a.c_lp ? launch_kernel(k_prep_frames<HLOC_FP8, true, CH>, grid, block, 0, s, a)
+                : launch_kernel(k_prep_frames<HLOC_FP8, false, CH>, grid, block, 0, s, a);
+}
+
+hipError_t launch_prep_frames(int32_t fmt, const PrepArgs &a, hipStream_t s) {
+  if (a.nq <= 0) return hipSuccess;
+  if (a.dp > kPrepDim) return hipErrorInvalidValue;
+  if (a.dp <= 256) return launch_prep_ch<1>(fmt, a, s);
+  if (a.dp <= 512) return launch_prep_ch<2>(fmt, a, s);
+  return launch_prep_ch<4>(fmt, a, s);
 }
 
 // One 16-byte piece of a row against the same piece of a frame.
