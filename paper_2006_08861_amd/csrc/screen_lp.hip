@@ -551,32 +551,44 @@ __global__ __launch_bounds__(256) void k_screen_wide_lp(ScreenArgs a) {
 // the whole padded length), so each row is read from memory once per item
 // and every LDS read of a frame piece feeds both row tiles (two MFMAs for
 // bf16, four for fp8). The item's frame entries are staged in LDS once; its
-// frame groups then stream through the two buffers run after run: while one
-// (run, group) step is multiplied, the next step's group is read into
-// registers (across a run boundary that is group 0 again) and written to the
-// other buffer after the multiply. The last step of a run requests the next
-// run's rows as soon as its multiply has read the current ones; it is
-// written apart from the run's other steps so that no other step has row
-// loads in flight, and the multiply of a step never waits for the next
-// step's frame group. An item's set-up requests its entries, then its first
+// frame groups then stream through the two buffers run after run (across a
+// run boundary comes group 0 again): while one (run, group) step is
+// multiplied, the group after the next is requested into one of two register
+// sets and the next one, in the other set since the step before, is written to
+// the other buffer. A run's rows are requested after the last step of the run
+// before; its first step is written apart so that no other step finds row
+// loads in flight. An item's set-up requests its entries, then its first
 // frame group, its first run and the entries' norms together; the next
 // item's descriptor is requested one item ahead.
 // The epilogue takes, per frame and row tile, the smallest of the tile's 16
-// screen words (the block word) and stores it at the frame's block position.
+// screen words (the block word) and stores it at the frame's block position;
+// |q|^2 is added to the smallest of the lane's four rows only, and the two
+// tiles share one lane swap (64 -> 40 vector instructions a step beside 16
+// multiplies at 256 values).
+// Measured with those, the second register set and the bank swizzle below:
+// 2,048 frames on 200k x 256 bf16, every row, 361 -> 291 us (720 TFLOP/s, 37 ->
+// 46 % of the matrix rate: barriers and the epilogue); 32,768 frames on 2M x 512
+// 796 -> 708 (it reads 3.4 GB at 4.8 TB/s, rows once per 512 frames of a region);
+// 2,048 frames on 500k x 512 137 -> 125; fp8 90 -> 77. Without the second set
+// 304, 765, 131 and 77; with the request pinned to the step's start (more
+// registers, a wave fewer) 315, 717, 135 and 78.
 // Items are dealt to the XCDs in contiguous runs (blocks go to the eight
 // XCDs round-robin): the chunks of one region, which stage the same frames,
 // run on one XCD and find them in its L2.
 constexpr int kRsAhead = 4;  // frame pieces in flight ahead of the multiplies
 
 template <int FMT, int NS>
-__global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
+__global__ __launch_bounds__(256, 2) void k_screen_wide_rs(ScreenArgs a) {
   constexpr int ROWU4 = 4 * NS;                 // 16-byte pieces per row
-  constexpr int LDF = ROWU4 + 1;                // padded frame row in LDS
+  // piece x of frame j lies at j * ROWU4 + (x ^ j): the 16 lanes that an LDS
+  // read serves at once (of lanes l: 0-3, 12-15, 20-27 and the like) then hit
+  // distinct banks, where rows padded by one piece had one pair collide, four
+  // cycles on each read of eight
   constexpr int TPF = 256 / kGroup;             // threads staging one frame
   static_assert(ROWU4 % TPF == 0, "whole pieces per thread");
   constexpr int PERF = ROWU4 / TPF;             // pieces per thread per group
   constexpr int U = kListFrames / 256;          // item entries per thread
-  extern __shared__ v4u s_fr[];                 // 2 x kGroup x LDF
+  extern __shared__ v4u s_fr[];                 // 2 x kGroup x ROWU4
   // the item's frames: rq entries, squared norms, scales (read once per item)
   __shared__ int2 s_e[kListFrames];
   __shared__ float s_qn[kListFrames], s_qs[kListFrames];
@@ -643,10 +655,9 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
     const int nrows = cur.nrows_gq >> 16, gq = cur.nrows_gq & 0xFFFF;
     const int nrun = (nrows + kWideRowsRs - 1) / kWideRowsRs;
     const int ng = (gq + kGroup - 1) / kGroup;
-    const int nst = nrun * ng;  // (run, group) steps, groups inner
     v4u av[2][NS];
     float rn[2][4], rs[2][4];
-    v4u pv[PERF];
+    v4u pva[PERF], pvb[PERF];
     // the wave's rows of run C (clamped to the item's last row; words of rows
     // past it are no candidates), then their norms and scales
 #define HLOC_RS_ROWS(C)                                                          \
@@ -660,19 +671,20 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
     _Pragma("unroll") for (int r = 0; r < 4; ++r) {                              \
       const int row = (C) * kWideRowsRs + 32 * w + 16 * h + 4 * g + r;           \
       const int grow = row_begin + min(row, nrows - 1);                          \
-      rn[h][r] = row < nrows ? a.row_n2[grow] : __builtin_inff();                \
+      const float n2 = a.row_n2[grow];                                           \
+      rn[h][r] = row < nrows ? n2 : __builtin_inff();                            \
       rs[h][r] = FMT == HLOC_FP8 ? a.row_scale[grow] : 1.f;                      \
     }                                                                            \
   }
-#define HLOC_RS_FETCH_FRAME(FR)                                                  \
+#define HLOC_RS_FETCH_FRAME(PV, FR)                                              \
   {                                                                              \
     const v4u *fp = frames + (int64_t)(FR) * ROWU4 + sc;                         \
-    _Pragma("unroll") for (int u = 0; u < PERF; ++u) pv[u] = fp[TPF * u];        \
+    _Pragma("unroll") for (int u = 0; u < PERF; ++u) PV[u] = fp[TPF * u];        \
   }
-#define HLOC_RS_STAGE(BUF)                                                       \
+#define HLOC_RS_STAGE(PV, BUF)                                                   \
   {                                                                              \
     _Pragma("unroll") for (int u = 0; u < PERF; ++u)                             \
-        s_fr[((BUF) * kGroup + sj) * LDF + sc + TPF * u] = pv[u];                \
+        s_fr[((BUF) * kGroup + sj) * ROWU4 + ((sc ^ sj) + TPF * u)] = PV[u];     \
   }
     __syncthreads();  // the previous item's entries and frames are no longer read
     if (dyn) {
@@ -690,7 +702,7 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
         e[u] = j < gq ? a.rq[q0 + j] : make_int2(0, 0);
       }
       // the first group, the first run and the entries' norms together
-      HLOC_RS_FETCH_FRAME(ef.x)
+      HLOC_RS_FETCH_FRAME(pva, ef.x)
       float qv[U], sv[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -708,55 +720,100 @@ __global__ __launch_bounds__(256) void k_screen_wide_rs(ScreenArgs a) {
           s_qs[j] = sv[u];
         }
       }
-      HLOC_RS_STAGE(0)
+      HLOC_RS_STAGE(pva, 0)
     }
     __syncthreads();
-    // one (run c, group K) step; LAST: the run's last group
-#define HLOC_RS_STEP(K, LAST)                                                    \
+    int gn = ng > 1 ? 1 : 0;  // group of the next step
+    HLOC_RS_FETCH_FRAME(pva, s_e[gn * kGroup + sj].x)
+    // piece 4 s + g of the lane's frame
+    int sw[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sw[u] = (4 * u + g) ^ i;
+#define HLOC_RS_PIECE(S) (sw[(S) & 3] + 16 * ((S) >> 2))
+    // One (run c, group K) step. P holds the next step's group (requested a
+    // step ago), Q receives the one after it; both wrap around to group 0 at
+    // the run's end (past the item's last step they are not used). P is
+    // staged as soon as the multiply is done, when only Q's loads are younger,
+    // so nothing waits for Q.
+#define HLOC_RS_STEP(K, P, Q)                                                    \
   {                                                                              \
     const int buf = st & 1;                                                      \
-    const bool more = st + 1 < nst;                                              \
-    if (more) HLOC_RS_FETCH_FRAME(s_e[((LAST) ? 0 : (K) + 1) * kGroup + sj].x)   \
+    gn = gn + 1 < ng ? gn + 1 : 0;                                               \
+    HLOC_RS_FETCH_FRAME(Q, s_e[gn * kGroup + sj].x)                              \
     v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};             \
-    const v4u *bp = s_fr + (buf * kGroup + i) * LDF + g;                         \
+    const v4u *bp = s_fr + (buf * kGroup + i) * ROWU4;                           \
     /* frame pieces read kRsAhead steps ahead of their multiplies, the */       \
     /* order pinned: the first reads, then per k step two multiplies and */     \
     /* the next read */                                                          \
     v4u bq[NS];                                                                  \
-    _Pragma("unroll") for (int s = 0; s < kRsAhead && s < NS; ++s) bq[s] = bp[4 * s]; \
+    _Pragma("unroll") for (int s = 0; s < kRsAhead && s < NS; ++s) bq[s] = bp[HLOC_RS_PIECE(s)]; \
     __builtin_amdgcn_sched_group_barrier(0x100, kRsAhead < NS ? kRsAhead : NS, 0); \
     _Pragma("unroll") for (int s = 0; s < NS; ++s) {                             \
-      if (s + kRsAhead < NS) bq[s + kRsAhead] = bp[4 * (s + kRsAhead)];          \
+      if (s + kRsAhead < NS) bq[s + kRsAhead] = bp[HLOC_RS_PIECE(s + kRsAhead)]; \
       acc[0] = lp_mfma_v<FMT>(av[0][s], bq[s], acc[0]);                          \
       acc[1] = lp_mfma_v<FMT>(av[1][s], bq[s], acc[1]);                          \
       __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                         \
       if (s + kRsAhead < NS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  \
     }                                                                            \
-    if ((LAST) && more) HLOC_RS_ROWS(c + 1)                                      \
-    const int2 e = s_e[(K) * kGroup + i];                                        \
-    const float qn = s_qn[(K) * kGroup + i], qs = s_qs[(K) * kGroup + i];        \
-    const bool fok = (K) * kGroup + i < gq;                                      \
-    const int blk = block0 + c * (kWideRowsRs / kBlockRows);                     \
-    _Pragma("unroll") for (int h = 0; h < 2; ++h) {                              \
-      if (c * kWideRowsRs + 32 * w + 16 * h < nrows) { /* (uniform) */           \
-        uint32_t wd[4];                                                          \
-        _Pragma("unroll") for (int r = 0; r < 4; ++r)                            \
-            wd[r] = lp_word<FMT>(qn, rn[h][r], acc[h][r], qs, rs[h][r]);         \
-        const uint32_t m = block_min16(wd);                                      \
-        if (fok && g == 0) a.cand[(int64_t)e.x * a.cap + e.y + blk + 2 * w + h] = m; \
+    HLOC_RS_STAGE(P, buf ^ 1)                                                    \
+    /* the smallest |d|^2 - 2 q.d of the lane's four rows of each tile, */       \
+    /* + |q|^2, then the tiles' minima over lanes l, l ^ 16, l ^ 32, l ^ 48: */  \
+    /* one swap of both tiles leaves the first in even rows of 16 lanes and */   \
+    /* the second in odd ones; a tile whose rows are all marked (norm +inf) */   \
+    /* has no word */                                                            \
+    if ((K) == 0) {                                                              \
+      _Pragma("unroll") for (int h = 0; h < 2; ++h) {                            \
+        bool fin = false;                                                        \
+        _Pragma("unroll") for (int r = 0; r < 4; ++r) fin |= !__builtin_isinf(rn[h][r]); \
+        none[h] = __ballot(fin) == 0;                                            \
       }                                                                          \
     }                                                                            \
-    if ((LAST) && more) HLOC_RS_NORMS(c + 1)                                     \
-    if (more) HLOC_RS_STAGE(buf ^ 1)                                             \
+    const int2 e = s_e[(K) * kGroup + i];                                        \
+    const float qn = s_qn[(K) * kGroup + i], qs = s_qs[(K) * kGroup + i];        \
+    uint32_t wd[2];                                                              \
+    _Pragma("unroll") for (int h = 0; h < 2; ++h) {                              \
+      float t[4];                                                                \
+      _Pragma("unroll") for (int r = 0; r < 4; ++r)                              \
+          t[r] = FMT == HLOC_FP8 ? fmaf(acc[h][r] * rs[h][r], -2.f * qs, rn[h][r]) \
+                                 : fmaf(acc[h][r], -2.f, rn[h][r]);              \
+      const float m = fminf(fminf(t[0], t[1]), fminf(t[2], t[3])) + qn;          \
+      wd[h] = none[h] ? 0xFFFFFFFFu : __float_as_uint(fmaxf(m, 0.f));            \
+    }                                                                            \
+    const auto p16 = __builtin_amdgcn_permlane16_swap(wd[0], wd[1], false, false); \
+    const uint32_t b16 = min((uint32_t)p16[0], (uint32_t)p16[1]);                \
+    const auto p32 = __builtin_amdgcn_permlane32_swap(b16, b16, false, false);   \
+    const uint32_t word = min((uint32_t)p32[0], (uint32_t)p32[1]);               \
+    const int row = c * kWideRowsRs + 32 * w + 16 * g; /* g < 2: the lane's tile */ \
+    if ((K) * kGroup + i < gq && g < 2 && row < nrows)                           \
+      a.cand[(int64_t)e.x * a.cap + e.y + block0 + (row >> 4)] = word;           \
     __syncthreads();                                                             \
     ++st;                                                                        \
   }
     int st = 0;  // steps done
+    bool none[2] = {false, false};
     for (int c = 0; c < nrun; ++c) {
-      for (int k = 0; k + 1 < ng; ++k) HLOC_RS_STEP(k, false)
-      HLOC_RS_STEP(ng - 1, true)
+      // the run's first step (its multiply waits for the run's rows), written
+      // apart so that no other step may find row loads in flight
+      HLOC_RS_STEP(0, pva, pvb)
+      int k = 1;
+      for (; k + 1 < ng; k += 2) {
+        HLOC_RS_STEP(k, pvb, pva)
+        HLOC_RS_STEP(k + 1, pva, pvb)
+      }
+      if (k < ng) {
+        HLOC_RS_STEP(k, pvb, pva)
+      } else {
+        // an odd run leaves the next group in pvb
+#pragma unroll
+        for (int u = 0; u < PERF; ++u) pva[u] = pvb[u];
+      }
+      if (c + 1 < nrun) {
+        HLOC_RS_ROWS(c + 1)
+        HLOC_RS_NORMS(c + 1)
+      }
     }
 #undef HLOC_RS_STEP
+#undef HLOC_RS_PIECE
 #undef HLOC_RS_ROWS
 #undef HLOC_RS_NORMS
 #undef HLOC_RS_FETCH_FRAME
@@ -772,7 +829,7 @@ size_t wide_lp_lds_bytes() {
 
 template <int NS>
 constexpr size_t wide_rs_lds_bytes() {
-  return (size_t)2 * kGroup * (4 * NS + 1) * sizeof(v4u);
+  return (size_t)2 * kGroup * 4 * NS * sizeof(v4u);
 }
 constexpr int kRsBlocksPerCu = 2;  // blocks per compute unit if the occupancy query fails
 
