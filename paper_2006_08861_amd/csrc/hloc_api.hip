@@ -135,6 +135,7 @@ int make_plan(const hloc_db *db, int32_t nq, int32_t k, int32_t n_regions, int32
     p.creps = (p.creps + 31) / 32 * 32;           // whole tiles of 32
     p.csplits = (db->R + p.creps - 1) / p.creps;  // no empty range
   }
+  p.terms = lp_terms(precision, db->dp);
   p.cap2 = p.exhaustive ? db->n_blocks : db->h_desc_blocks[p.nr];
   const int32_t crow = std::min(db->tile_rows, kWideRows);  // the shorter chunks bound the items
   const int64_t maxch = (db->max_region + crow - 1) / crow;
@@ -212,7 +213,11 @@ int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *byte
   CHK(fit(ws->items, (size_t)std::max<int64_t>(p.items_bound, 1) * sizeof(Item)));
   CHK(fit(ws->cand2, (size_t)nq * std::max<int64_t>(p.cap2, 1) * sizeof(uint32_t)));
   if (db->lp[HLOC_BF16].rows || db->lp[HLOC_FP8].rows) {
-    CHK(fit(ws->q_lp, (size_t)nq * db->dp * (db->lp[HLOC_BF16].rows ? 2 : 1)));
+    // bytes per value: 2 for bf16, one per vector for fp8
+    const int fp8 = p.reserve && db->lp[HLOC_FP8].rows ? lp_terms(HLOC_FP8, db->dp)
+                    : p.precision == HLOC_FP8          ? p.terms
+                                                       : 1;
+    CHK(fit(ws->q_lp, (size_t)nq * db->dp * (db->lp[HLOC_BF16].rows ? 2 : fp8)));
     CHK(fit(ws->q_scale, (size_t)nq * sizeof(float)));
     CHK(fit(ws->q_err, (size_t)nq * sizeof(float)));
     CHK(fit(ws->q_lon, (size_t)nq * sizeof(float)));
@@ -274,6 +279,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   Plan p = plan;
   if (ws->fixed && p.direct && !p.exhaustive && ws->cand1.cap < coarse_list_bytes(p.nq, db->R))
     p.direct = false;
+  if (ws->fixed && p.terms == 2 && ws->q_lp.cap < (size_t)p.nq * db->dp * 2) p.terms = 1;
   CHK(ensure_workspace(ws, p, want_agg && !(xy && tile && flags)));
   ws->last_nq = p.nq;
   ws->last_nr = p.nr;
@@ -311,6 +317,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   pa.counts = as<int32_t>(ws->rcount);
   pa.n_counts = p.exhaustive ? 0 : db->R;
   pa.lp = ws->q_lp.p;
+  pa.terms = p.terms;
   pa.scale = as<float>(ws->q_scale);
   pa.err = as<float>(ws->q_err);
   pa.lon = as<float>(ws->q_lon);
@@ -322,8 +329,10 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   HIPCHK(launch_prep_frames(fmt, pa, s));
   // fp32 accumulation of rounded products: |q~||d~| <= 1.004 |q||d| for bf16,
   // <= (1 + 2^-4)^2 |q||d| for fp8 (relative rounding of at most 2^-4 per
-  // value; subnormals are absolute and covered by the rounding-error terms)
-  const double lo_fp32 = fmt == HLOC_FP8 ? 1.15 : 1.01;
+  // value; subnormals are absolute and covered by the rounding-error terms);
+  // two fp8 vectors per frame: twice the terms, <= (1 + 2^-4 + 2^-4 (1 + 2^-4))
+  // (1 + 2^-4) |q||d| in all
+  const double lo_fp32 = fmt != HLOC_FP8 ? 1.01 : p.terms == 2 ? 2.0 * 1.25 : 1.15;
   ph.begin(HLOC_PHASE_COARSE);
   const double coef = (db->dp + 16) * kUnit32 * 1.001;
   const bool masked = (label >= 0 || label_frames > 0) && db->rlabel;
@@ -369,6 +378,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
     if (coarse_lp) {
       sa.rows_lp = cpm->reps;
       sa.q_lp = c_lp;
+      sa.terms = cfmt == HLOC_FP8 ? p.terms : 1;
       sa.row_scale = cpm->rep_scale;
       sa.q_scale = as<float>(ws->q_scale);
       HIPCHK(wide_dense ? launch_screen_wide_lp(cfmt, sa, p.grid1, db->num_cu, s)
@@ -399,7 +409,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
       ra.lo_dmax = (double)cpm->rep_err * (1.0 + 1e-6);
       ra.lo_nmax = (double)cpm->rep_norm * (1.0 + 1e-6);
       ra.lo_coef = 2.0 * (1.0 + 1e-6);
-      ra.err_coef = coef * (cfmt == HLOC_FP8 ? 1.15 : 1.01);
+      ra.err_coef = coef * (cfmt == HLOC_FP8 ? lo_fp32 : 1.01);
     }
     ra.nq = p.nq;
     ra.reg_out = regions;
@@ -509,6 +519,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   if (fmt) {
     sb.rows_lp = lpm->rows;
     sb.q_lp = ws->q_lp.p;
+    sb.terms = p.terms;
     sb.row_scale = lpm->scale;
     sb.q_scale = as<float>(ws->q_scale);
   }
@@ -1239,9 +1250,11 @@ int hloc_query_batch_static_async(hloc_db *db, const float *q, int32_t nq, int32
   size_t used = 0;
   const Carve carve{base};
   CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
-  if (used > (size_t)HLOC_STATIC_SCRATCH_BYTES && p.direct) {
-    // the schedule's item list takes less than the direct screen's frame lists
+  // the schedule's item list takes less than the direct screen's frame lists,
+  // one fp8 vector per frame less than two
+  if (used > (size_t)HLOC_STATIC_SCRATCH_BYTES && (p.direct || p.terms == 2)) {
     p.direct = false;
+    p.terms = 1;
     used = 0;
     CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
   }

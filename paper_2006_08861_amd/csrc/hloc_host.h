@@ -174,6 +174,7 @@ struct Plan {
   int32_t nq, k, nr, L1, kp, nreq, precision;
   bool exhaustive;
   bool direct;  // the fine screen walks the block table instead of an item list
+  int32_t terms;  // fp8: vectors per frame in the fine screen (lp_terms, or 1 to take less memory)
   bool reserve = false;  // sizes buffers for smaller batches too, whose frame lists may be larger
   // the coarse stage as the fused bf16 product (short key lists per frame)
   // instead of the dense screen's frame x region words

@@ -86,6 +86,7 @@ struct ScreenArgs {
   const void *q_lp;       // low-precision copy of qp
   const float *row_scale; // fp8: per-row scale
   const float *q_scale;   // fp8: per-frame scale
+  int32_t terms;          // fp8: vectors of q_lp per frame (1 or 2), their sum is the frame
   const float *row_n2;    // nrows squared norms (+inf marks a row never to select)
   int32_t dp;             // padded row length (multiple of 32)
   const float *qp;        // frames x dp
@@ -270,6 +271,7 @@ struct PrepArgs {
   int32_t *counts;      // n_counts more
   int32_t n_counts;
   void *lp;             // the fine screen's copy, its scale (fp8) and norms
+  int32_t terms;        // fp8: vectors per frame
   float *scale, *err, *lon;
   void *c_lp;           // bf16 copy for the coarse screen of fp8 queries, or NULL
   float *c_err, *c_lon;
@@ -287,6 +289,14 @@ hipError_t launch_screen_lp(int32_t fmt, const ScreenArgs &a, int32_t grid, hipS
 hipError_t launch_screen_wide_lp(int32_t fmt, const ScreenArgs &a, int32_t grid, int32_t num_cu,
                                  hipStream_t s);
 bool lp_screen_supports(int32_t fmt, int32_t dp);
+// Vectors that stand for a frame in this screen: two e4m3 ones for fp8 up to
+// kFp8TermsDim values (past it their LDS stage would halve the blocks of a
+// compute unit). The rows' rounding and the frame's enter the error bound
+// alike; the second vector takes the frame's out, so the band that the select
+// re-scores in FP64 halves for twice the multiplies of a screen that waits for
+// memory.
+constexpr int kFp8TermsDim = 768;
+int32_t lp_terms(int32_t fmt, int32_t dp);
 // The wide list items of this low-precision screen go to the register-row
 // kernel: up to kWideRunsRs runs of kWideRowsRs rows each, instead of
 // min(T, kWideRows) rows.

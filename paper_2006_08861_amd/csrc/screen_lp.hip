@@ -141,9 +141,13 @@ hipError_t launch_rows_to_lp(int32_t fmt, const float *src, int64_t n, int32_t d
 constexpr int kPrepDim = HLOC_MAX_DIM;  // padded length at most (a multiple of 32)
 static_assert(kPrepDim <= 1024, "four chunks of 256 values");
 
+// fp8 with terms = 2: the frame as the sum of two e4m3 vectors of one scale,
+// the rounded frame and, behind it, the rounding of what that leaves out (at
+// most 2^-4 of each value, so it rounds at the same scale to 2^-8 of it).
 template <int FMT, int CH>
-__device__ __forceinline__ void frame_copy(const float4 (&v)[CH], int f, int dp, void *dst,
-                                           float *__restrict__ scale, float *__restrict__ q_err,
+__device__ __forceinline__ void frame_copy(const float4 (&v)[CH], int f, int dp, int terms,
+                                           void *dst, float *__restrict__ scale,
+                                           float *__restrict__ q_err,
                                            float *__restrict__ q_lon) {
   const int lane = lane_id();
   double e2 = 0.0, n2 = 0.0;
@@ -166,7 +170,7 @@ __device__ __forceinline__ void frame_copy(const float4 (&v)[CH], int f, int dp,
       add((double)bf16_to_f32(h.w), v[u].w);
     }
   } else {
-    uint8_t *o = static_cast<uint8_t *>(dst) + (int64_t)f * dp;
+    uint8_t *o = static_cast<uint8_t *>(dst) + (int64_t)f * terms * dp;
     float amax = 0.f;
 #pragma unroll
     for (int u = 0; u < CH; ++u)
@@ -180,13 +184,24 @@ __device__ __forceinline__ void frame_copy(const float4 (&v)[CH], int f, int dp,
     for (int u = 0; u < CH; ++u) {
       const int c = 256 * u + 4 * lane;
       if (c >= dp) continue;
-      const uint32_t p = fp8_pair(clamp_fp8(v[u].x * inv), clamp_fp8(v[u].y * inv)) |
-                         fp8_pair(clamp_fp8(v[u].z * inv), clamp_fp8(v[u].w * inv)) << 16;
-      *reinterpret_cast<uint32_t *>(o + c) = p;
-      add((double)fp8_to_f32(p & 0xFF) * sc, v[u].x);
-      add((double)fp8_to_f32(p >> 8 & 0xFF) * sc, v[u].y);
-      add((double)fp8_to_f32(p >> 16 & 0xFF) * sc, v[u].z);
-      add((double)fp8_to_f32(p >> 24) * sc, v[u].w);
+      const float x[4] = {clamp_fp8(v[u].x * inv), clamp_fp8(v[u].y * inv),
+                          clamp_fp8(v[u].z * inv), clamp_fp8(v[u].w * inv)};
+      const uint32_t h = fp8_pair(x[0], x[1]) | fp8_pair(x[2], x[3]) << 16;
+      *reinterpret_cast<uint32_t *>(o + c) = h;
+      float t[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = fp8_to_f32(h >> (8 * e) & 0xFF);
+      if (terms == 2) {
+        const uint32_t l = fp8_pair(x[0] - t[0], x[1] - t[1]) |
+                           fp8_pair(x[2] - t[2], x[3] - t[3]) << 16;
+        *reinterpret_cast<uint32_t *>(o + dp + c) = l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] += fp8_to_f32(l >> (8 * e) & 0xFF);  // (exact)
+      }
+      add((double)t[0] * sc, v[u].x);
+      add((double)t[1] * sc, v[u].y);
+      add((double)t[2] * sc, v[u].z);
+      add((double)t[3] * sc, v[u].w);
     }
   }
   e2 = wave_sum_f64(e2);
@@ -233,8 +248,8 @@ __global__ __launch_bounds__(256) void k_prep_frames(PrepArgs a) {
   }
   acc = wave_sum_f32(acc);
   if (lane == 0) a.qn2[f] = acc;
-  if constexpr (FMT != 0) frame_copy<FMT, CH>(v, f, a.dp, a.lp, a.scale, a.err, a.lon);
-  if constexpr (COARSE) frame_copy<HLOC_BF16, CH>(v, f, a.dp, a.c_lp, nullptr, a.c_err, a.c_lon);
+  if constexpr (FMT != 0) frame_copy<FMT, CH>(v, f, a.dp, a.terms, a.lp, a.scale, a.err, a.lon);
+  if constexpr (COARSE) frame_copy<HLOC_BF16, CH>(v, f, a.dp, 1, a.c_lp, nullptr, a.c_err, a.c_lon);
 }
 
 template <int CH>
@@ -306,6 +321,7 @@ __global__ __launch_bounds__(256) void k_screen_lp(ScreenArgs a) {
   const uint4 *rows = static_cast<const uint4 *>(a.rows_lp);
   const uint4 *frames = static_cast<const uint4 *>(a.q_lp);
   int lo = 0, hi, nchunks = 1;
+  const int terms = FMT == HLOC_FP8 ? a.terms : 1;
   // dense mode: frames 0 .. nq - 1, or the listed ones
   const int nqd = DENSE && a.frame_list ? *a.frame_count : a.nq;
   if (DENSE) {
@@ -351,7 +367,7 @@ __global__ __launch_bounds__(256) void k_screen_lp(ScreenArgs a) {
     for (int rb = w; rb < nrb; rb += nw) {
       const int rl = min(rb * 16 + i, nrows - 1);
       const uint4 *rp = rows + (int64_t)(row_begin + rl) * ROWU4 + g;
-      const uint4 *qp = frames + (int64_t)fr * ROWU4 + g;
+      const uint4 *qp = frames + (int64_t)fr * (terms * ROWU4) + g;
       uint4 av[NS], bv[NS];
 #pragma unroll
       for (int s = 0; s < NS; ++s) av[s] = rp[4 * s];
@@ -360,8 +376,19 @@ __global__ __launch_bounds__(256) void k_screen_lp(ScreenArgs a) {
       const float qn = a.qn2[fr];
       const float qs = FMT == HLOC_FP8 ? a.q_scale[fr] : 1.f;
       v4f acc = {0.f, 0.f, 0.f, 0.f};
+      if (FMT == HLOC_FP8 && terms == 2) {
+        uint4 cv[NS];
 #pragma unroll
-      for (int s = 0; s < NS; ++s) acc = lp_mfma<FMT>(av[s], bv[s], acc);
+        for (int s = 0; s < NS; ++s) cv[s] = qp[ROWU4 + 4 * s];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          acc = lp_mfma<FMT>(av[s], bv[s], acc);
+          acc = lp_mfma<FMT>(av[s], cv[s], acc);
+        }
+      } else {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) acc = lp_mfma<FMT>(av[s], bv[s], acc);
+      }
       // the lane's four rows are consecutive rows of its frame's list
       const int row0 = rb * 16 + 4 * g;
       uint32_t wd[4];
@@ -404,10 +431,11 @@ __global__ __launch_bounds__(256) void k_screen_direct_lp(ScreenArgs a) {
   const int lane = lane_id(), i = lane & 15, g = lane >> 4;
   const uint4 *rows = static_cast<const uint4 *>(a.rows_lp);
   const uint4 *frames = static_cast<const uint4 *>(a.q_lp);
+  const int terms = FMT == HLOC_FP8 ? a.terms : 1;
   direct_groups(a, i, [&](int4 t, int2 e, int left) {
     const int row0 = 4 * g;
     const uint4 *rp = rows + (int64_t)(t.x + min(i, t.y - 1)) * ROWU4 + g;
-    const uint4 *qp = frames + (int64_t)e.x * ROWU4 + g;
+    const uint4 *qp = frames + (int64_t)e.x * (terms * ROWU4) + g;
     uint4 av[NS], bv[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) av[s] = rp[4 * s];
@@ -416,8 +444,19 @@ __global__ __launch_bounds__(256) void k_screen_direct_lp(ScreenArgs a) {
     const float qn = a.qn2[e.x];
     const float qs = FMT == HLOC_FP8 ? a.q_scale[e.x] : 1.f;
     v4f acc = {0.f, 0.f, 0.f, 0.f};
+    if (FMT == HLOC_FP8 && terms == 2) {
+      uint4 cv[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) acc = lp_mfma<FMT>(av[s], bv[s], acc);
+      for (int s = 0; s < NS; ++s) cv[s] = qp[ROWU4 + 4 * s];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        acc = lp_mfma<FMT>(av[s], bv[s], acc);
+        acc = lp_mfma<FMT>(av[s], cv[s], acc);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) acc = lp_mfma<FMT>(av[s], bv[s], acc);
+    }
     uint32_t wd[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -442,6 +481,7 @@ __global__ __launch_bounds__(256) void k_screen_wide_lp(ScreenArgs a) {
   const int i = lane & 15, g = lane >> 4;
   const uint4 *rows = static_cast<const uint4 *>(a.rows_lp);
   const uint4 *frames = static_cast<const uint4 *>(a.q_lp);
+  const int terms = FMT == HLOC_FP8 ? a.terms : 1;
   // the chunk of the block's next item is read into registers (all of a
   // thread's pieces at once) while the current one is screened, with the rq
   // entry of each lane's frame in the wave's first group
@@ -489,10 +529,14 @@ __global__ __launch_bounds__(256) void k_screen_wide_lp(ScreenArgs a) {
       int fr = 0;
       int64_t off = 0;
       if (i < gs) wide_frame(a, wi, grp * kGroup + i, ce, &fr, &off);
-      const uint4 *qp = frames + (int64_t)fr * ROWU4 + g;
-      uint4 bv[NS];
+      const uint4 *qp = frames + (int64_t)fr * (terms * ROWU4) + g;
+      uint4 bv[NS], cv[FMT == HLOC_FP8 ? NS : 1];
 #pragma unroll
       for (int s = 0; s < NS; ++s) bv[s] = qp[4 * s];
+      if (FMT == HLOC_FP8 && terms == 2) {
+#pragma unroll
+        for (int s = 0; s < (FMT == HLOC_FP8 ? NS : 1); ++s) cv[s] = qp[ROWU4 + 4 * s];
+      }
       const float qn = a.qn2[fr];
       const float qs = FMT == HLOC_FP8 ? a.q_scale[fr] : 1.f;
       ce = wide_entry(a, wi, (grp + nw) * kGroup + i);  // the wave's next group
@@ -503,8 +547,17 @@ __global__ __launch_bounds__(256) void k_screen_wide_lp(ScreenArgs a) {
         if (rb * 16 >= nrows) continue;
         const uint4 *rp = s_rows + (rb * 16 + i) * LDR + g;
         v4f acc = {0.f, 0.f, 0.f, 0.f};
+        if (FMT == HLOC_FP8 && terms == 2) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) acc = lp_mfma<FMT>(rp[4 * s], bv[s], acc);
+          for (int s = 0; s < NS; ++s) {
+            const uint4 av = rp[4 * s];
+            acc = lp_mfma<FMT>(av, bv[s], acc);
+            acc = lp_mfma<FMT>(av, cv[FMT == HLOC_FP8 ? s : 0], acc);
+          }
+        } else {
+#pragma unroll
+          for (int s = 0; s < NS; ++s) acc = lp_mfma<FMT>(rp[4 * s], bv[s], acc);
+        }
         // the lane's four rows are consecutive rows of its frame's list
         const int row0 = rb * 16 + 4 * g;
         uint32_t wd[4];
@@ -577,18 +630,20 @@ __global__ __launch_bounds__(256) void k_screen_wide_lp(ScreenArgs a) {
 // run on one XCD and find them in its L2.
 constexpr int kRsAhead = 4;  // frame pieces in flight ahead of the multiplies
 
-template <int FMT, int NS>
+template <int FMT, int NS, int TERMS>
 __global__ __launch_bounds__(256, 2) void k_screen_wide_rs(ScreenArgs a) {
   constexpr int ROWU4 = 4 * NS;                 // 16-byte pieces per row
-  // piece x of frame j lies at j * ROWU4 + (x ^ j): the 16 lanes that an LDS
+  constexpr int FRU4 = TERMS * ROWU4;           // and per frame
+  constexpr int NSF = TERMS * NS;
+  // piece x of frame j lies at j * FRU4 + (x ^ j): the 16 lanes that an LDS
   // read serves at once (of lanes l: 0-3, 12-15, 20-27 and the like) then hit
   // distinct banks, where rows padded by one piece had one pair collide, four
   // cycles on each read of eight
   constexpr int TPF = 256 / kGroup;             // threads staging one frame
   static_assert(ROWU4 % TPF == 0, "whole pieces per thread");
-  constexpr int PERF = ROWU4 / TPF;             // pieces per thread per group
+  constexpr int PERF = FRU4 / TPF;              // pieces per thread per group
   constexpr int U = kListFrames / 256;          // item entries per thread
-  extern __shared__ v4u s_fr[];                 // 2 x kGroup x ROWU4
+  extern __shared__ v4u s_fr[];                 // 2 x kGroup x FRU4
   // the item's frames: rq entries, squared norms, scales (read once per item)
   __shared__ int2 s_e[kListFrames];
   __shared__ float s_qn[kListFrames], s_qs[kListFrames];
@@ -678,13 +733,13 @@ __global__ __launch_bounds__(256, 2) void k_screen_wide_rs(ScreenArgs a) {
   }
 #define HLOC_RS_FETCH_FRAME(PV, FR)                                              \
   {                                                                              \
-    const v4u *fp = frames + (int64_t)(FR) * ROWU4 + sc;                         \
+    const v4u *fp = frames + (int64_t)(FR) * FRU4 + sc;                          \
     _Pragma("unroll") for (int u = 0; u < PERF; ++u) PV[u] = fp[TPF * u];        \
   }
 #define HLOC_RS_STAGE(PV, BUF)                                                   \
   {                                                                              \
     _Pragma("unroll") for (int u = 0; u < PERF; ++u)                             \
-        s_fr[((BUF) * kGroup + sj) * ROWU4 + ((sc ^ sj) + TPF * u)] = PV[u];     \
+        s_fr[((BUF) * kGroup + sj) * FRU4 + ((sc ^ sj) + TPF * u)] = PV[u];      \
   }
     __syncthreads();  // the previous item's entries and frames are no longer read
     if (dyn) {
@@ -741,19 +796,19 @@ __global__ __launch_bounds__(256, 2) void k_screen_wide_rs(ScreenArgs a) {
     gn = gn + 1 < ng ? gn + 1 : 0;                                               \
     HLOC_RS_FETCH_FRAME(Q, s_e[gn * kGroup + sj].x)                              \
     v4f acc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};             \
-    const v4u *bp = s_fr + (buf * kGroup + i) * ROWU4;                           \
+    const v4u *bp = s_fr + (buf * kGroup + i) * FRU4;                            \
     /* frame pieces read kRsAhead steps ahead of their multiplies, the */       \
     /* order pinned: the first reads, then per k step two multiplies and */     \
     /* the next read */                                                          \
-    v4u bq[NS];                                                                  \
-    _Pragma("unroll") for (int s = 0; s < kRsAhead && s < NS; ++s) bq[s] = bp[HLOC_RS_PIECE(s)]; \
-    __builtin_amdgcn_sched_group_barrier(0x100, kRsAhead < NS ? kRsAhead : NS, 0); \
-    _Pragma("unroll") for (int s = 0; s < NS; ++s) {                             \
-      if (s + kRsAhead < NS) bq[s + kRsAhead] = bp[HLOC_RS_PIECE(s + kRsAhead)]; \
-      acc[0] = lp_mfma_v<FMT>(av[0][s], bq[s], acc[0]);                          \
-      acc[1] = lp_mfma_v<FMT>(av[1][s], bq[s], acc[1]);                          \
+    v4u bq[NSF];                                                                 \
+    _Pragma("unroll") for (int s = 0; s < kRsAhead && s < NSF; ++s) bq[s] = bp[HLOC_RS_PIECE(s)]; \
+    __builtin_amdgcn_sched_group_barrier(0x100, kRsAhead < NSF ? kRsAhead : NSF, 0); \
+    _Pragma("unroll") for (int s = 0; s < NSF; ++s) {                            \
+      if (s + kRsAhead < NSF) bq[s + kRsAhead] = bp[HLOC_RS_PIECE(s + kRsAhead)]; \
+      acc[0] = lp_mfma_v<FMT>(av[0][s % NS], bq[s], acc[0]);                     \
+      acc[1] = lp_mfma_v<FMT>(av[1][s % NS], bq[s], acc[1]);                     \
       __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                         \
-      if (s + kRsAhead < NS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  \
+      if (s + kRsAhead < NSF) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); \
     }                                                                            \
     HLOC_RS_STAGE(P, buf ^ 1)                                                    \
     /* the smallest |d|^2 - 2 q.d of the lane's four rows of each tile, */       \
@@ -827,9 +882,8 @@ size_t wide_lp_lds_bytes() {
   return (size_t)64 * (4 * NS + 1) * sizeof(uint4);
 }
 
-template <int NS>
-constexpr size_t wide_rs_lds_bytes() {
-  return (size_t)2 * kGroup * 4 * NS * sizeof(v4u);
+constexpr size_t wide_rs_lds_bytes(int pieces) {
+  return (size_t)2 * kGroup * 4 * pieces * sizeof(v4u);
 }
 constexpr int kRsBlocksPerCu = 2;  // blocks per compute unit if the occupancy query fails
 
@@ -848,31 +902,42 @@ int lp_pieces(int32_t fmt, int32_t dp) {
 
 bool lp_screen_supports(int32_t fmt, int32_t dp) { return lp_pieces(fmt, dp) > 0; }
 
+int32_t lp_terms(int32_t fmt, int32_t dp) { return fmt == HLOC_FP8 && dp <= kFp8TermsDim ? 2 : 1; }
+
 bool lp_wide_rs(int32_t fmt, int32_t dp) {
   const int ns = lp_pieces(fmt, dp);
   return ns > 0 && ns % 4 == 0;
+}
+
+template <int FMT, int NS, int TERMS>
+hipError_t launch_rs(const ScreenArgs &a, int32_t wide_cu, hipStream_t s) {
+  // as many blocks as the compute units hold at once (registers and LDS)
+  constexpr size_t lds = wide_rs_lds_bytes(TERMS * NS);
+  static int per_cu = 0;
+  if (per_cu == 0) {
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &occ, reinterpret_cast<const void *>(&k_screen_wide_rs<FMT, NS, TERMS>), 256, lds) !=
+            hipSuccess || occ < 1) {
+      (void)hipGetLastError();
+      occ = kRsBlocksPerCu;
+    }
+    per_cu = occ;
+  }
+  // every block resident at once, a multiple of the eight XCDs
+  const int64_t resident = std::max<int64_t>(8, (int64_t)wide_cu * per_cu / 8 * 8);
+  return launch_kernel(k_screen_wide_rs<FMT, NS, TERMS>, dim3((int32_t)resident), dim3(256),
+                       (uint32_t)lds, s, a);
 }
 
 template <int FMT, int NS>
 hipError_t launch_lp_ns(const ScreenArgs &a, int32_t grid, int32_t wide_cu, hipStream_t s) {
   if constexpr (NS % 4 == 0) {
     if (wide_cu > 0 && !a.dense) {
-      // as many blocks as the compute units hold at once (registers and LDS)
-      static int per_cu = 0;
-      if (per_cu == 0) {
-        int occ = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &occ, reinterpret_cast<const void *>(&k_screen_wide_rs<FMT, NS>), 256,
-                wide_rs_lds_bytes<NS>()) != hipSuccess || occ < 1) {
-          (void)hipGetLastError();
-          occ = kRsBlocksPerCu;
-        }
-        per_cu = occ;
+      if constexpr (FMT == HLOC_FP8 && 64 * NS <= kFp8TermsDim) {
+        if (a.terms == 2) return launch_rs<FMT, NS, 2>(a, wide_cu, s);
       }
-      // every block resident at once, a multiple of the eight XCDs
-      const int64_t resident = std::max<int64_t>(8, (int64_t)wide_cu * per_cu / 8 * 8);
-      return launch_kernel(k_screen_wide_rs<FMT, NS>, dim3((int32_t)resident), dim3(256),
-                           (uint32_t)wide_rs_lds_bytes<NS>(), s, a);
+      return launch_rs<FMT, NS, 1>(a, wide_cu, s);
     }
   }
   if (wide_cu > 0) {
@@ -981,6 +1046,8 @@ hipError_t prepare_screen_lp_kernels() {
   HLOC_LP_ATTR(F, 16)
   HLOC_LP_ATTRS(HLOC_BF16)
   HLOC_LP_ATTRS(HLOC_FP8)
+  // (the register-row kernels stay below it)
+  static_assert(wide_rs_lds_bytes(2 * kFp8TermsDim / 64) <= 64 * 1024, "frame buffers");
 #undef HLOC_LP_ATTRS
 #undef HLOC_LP_ATTR
   return hipSuccess;

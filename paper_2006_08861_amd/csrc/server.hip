@@ -300,7 +300,10 @@ int hloc_server_create(hloc_db *db, const hloc_server_config *cfg, hloc_server *
   if (c.hbm_budget_bytes < 0) return fail(HLOC_EINVAL, "hbm_budget_bytes must be >= 0");
   Plan full;
   CHK(make_plan(db, c.max_batch_frames, c.k, c.n_regions, c.max_batch_frames, c.precision, &full));
-  full.direct = false;  // (smaller batches find room for its lists behind their coarse words)
+  // smaller batches find room for the direct screen's lists behind their coarse
+  // words and for a second fp8 vector per frame
+  full.direct = false;
+  full.terms = 1;
   DeviceGuard g(db->device);
   if (g.err != hipSuccess) return fail(HLOC_EDEVICE, "hipSetDevice failed");
   hloc_server *srv = new (std::nothrow) hloc_server();
