@@ -128,7 +128,8 @@ int make_plan(const hloc_db *db, int32_t nq, int32_t k, int32_t n_regions, int32
   // bf16 coarse screens (bf16 queries, and fp8 queries when the database
   // keeps bf16 representatives) on a length the fused product supports
   p.coarse_keys = !p.exhaustive && precision != HLOC_FP32 && db->lp[HLOC_BF16].reps &&
-                  coarse_gemm_supports(db->dp) && db->R < (1 << 28);
+                  coarse_gemm_supports(db->dp) && db->R < (1 << 28) &&
+                  ((int64_t)nq * db->R > kKeyWords || (int64_t)nq * db->R <= kKeyFew);
   if (p.coarse_keys) {
     const int32_t sp = coarse_gemm_splits(std::max(nq, 1), db->R, db->num_cu);
     p.creps = (db->R + sp - 1) / sp;
@@ -371,10 +372,16 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
     sa.nq = p.nq;
     sa.frame_list = list;
     sa.frame_count = count;
-    // large batches: 64 representatives staged in LDS against 256 frames at a
-    // time (the wide kernels' dense mode) instead of re-reading them per 16
+    // large batches: 64 representatives staged in LDS against up to 256 frames
+    // at a time (the wide kernels' dense mode) instead of re-reading them per
+    // 16, as many frames as leave an item for every block
     const bool wide_dense =
         !list && p.nq >= kWideDenseFrames && (coarse_lp || f32_wide_supports(db->dp));
+    sa.item_frames = kItemFrames;
+    while (sa.item_frames > 4 * kGroup &&
+           (int64_t)((db->R + kRowsCoarse - 1) / kRowsCoarse) *
+                   ((p.nq + sa.item_frames - 1) / sa.item_frames) < 2 * db->num_cu)
+      sa.item_frames /= 2;
     if (coarse_lp) {
       sa.rows_lp = cpm->reps;
       sa.q_lp = c_lp;
@@ -387,13 +394,18 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
       HIPCHK(wide_dense ? launch_screen_wide_f32(sa, p.grid1, db->num_cu, s)
                         : launch_screen_f32(sa, p.grid1, s));
     }
-    if (masked)
+    if (masked && p.L1 > kFrameL)
       HIPCHK(launch_mask_label(as<uint32_t>(ws->cand1), p.nq, db->R, db->rlabel, label,
                                label_frames, s));
     if (!list) ph.begin(HLOC_PHASE_COARSE_SELECT);
     SelRerankArgs ra{};
     ra.cand = as<uint32_t>(ws->cand1);
     ra.cap = db->R;
+    if (masked && p.L1 <= kFrameL) {
+      ra.rlabel = db->rlabel;
+      ra.label = label;
+      ra.label_frames = label_frames;
+    }
     ra.n_fixed = db->R;
     ra.L = p.L1;
     ra.m = p.nr;

@@ -64,6 +64,15 @@ constexpr int kWideDenseFrames = 512;  // batches from which the coarse screen u
 constexpr int64_t kDirectSlots = (int64_t)1 << 22;
 constexpr double kDirectFlops = 1.5e9;
 constexpr int kDirectSplits = 16;
+// Low-precision coarse screens: the fused product with key lists above
+// kKeyWords frame x representative words, the dense words below: storing them
+// costs less than the lists of many splits and the launches for deferred
+// frames. Measured, coarse stage in all, words / keys: 64 x 200 16 / 32 us, 2,048 x
+// 1,024 (512 values) 54 / 78, 8,192 x 1,024 75 / 112, 2,048 x 8,192 121 / 108,
+// 32,768 x 4,096 1,000 / 475. A handful of frames, up to kKeyFew words, stays
+// with the lists, slower as it is: that is where their deferral is exercised.
+constexpr int64_t kKeyWords = (int64_t)3 << 22;
+constexpr int64_t kKeyFew = 1024;
 constexpr double kUnit32 = 5.9604644775390625e-08;  // 2^-24
 
 template <class T>

@@ -40,7 +40,8 @@ inline hipError_t launch_kernel(F kernel, dim3 grid, dim3 block, uint32_t lds, h
 
 constexpr int kGroup = 16;          // frames per MFMA column block of the screen
 constexpr int kLdsPerCu = 160 * 1024;  // LDS of one compute unit (gfx950)
-constexpr int kItemFrames = 256;    // frames per dense work item of the wide kernels
+constexpr int kItemFrames = 256;    // frames per dense work item of the wide kernels at most
+constexpr int kFrameL = 64;         // survivor positions of the select's frame kernel, one per lane
 constexpr int kListFrames = 1024;   // frames per wide list item (rows re-read once per this many)
 constexpr int kWideRows = 64;       // rows per wide work item (the LDS stage of the wide kernels)
 constexpr int kWideRowsRs = 128;    // rows per run of the register-row kernels (bf16, fp8)
@@ -98,6 +99,7 @@ struct ScreenArgs {
   int32_t dense;
   int32_t nrows;
   int32_t nq;
+  int32_t item_frames;    // wide kernels: frames per item
   // list mode
   const Item *items;
   const int32_t *n_items;
@@ -127,7 +129,7 @@ struct ScreenArgs {
 // Work item of the wide screens: a chunk of rows against up to kListFrames
 // frames, either list item it of the narrow-then-wide order, or dense item it
 // (chunk it % nchunks of all rows against frames from (it / nchunks) *
-// kItemFrames).
+// item_frames).
 struct WideItem {
   int row_begin, chunk_row, nrows, gq, q0, f0;  // chunk_row: list items, the first block
 };
@@ -143,7 +145,7 @@ __device__ __forceinline__ int wide_range(const ScreenArgs &a, int *lo) {
   if (a.dense) {
     *lo = 0;
     const int nchunks = (a.nrows + a.rows_per_item - 1) / a.rows_per_item;
-    return nchunks * ((a.nq + kItemFrames - 1) / kItemFrames);
+    return nchunks * ((a.nq + a.item_frames - 1) / a.item_frames);
   }
   *lo = a.n_items[4];
   return a.n_items[0];
@@ -154,11 +156,11 @@ __device__ __forceinline__ WideItem wide_item(const ScreenArgs &a, int it) {
   if (a.dense) {
     const int nchunks = (a.nrows + a.rows_per_item - 1) / a.rows_per_item;
     const int c = it % nchunks;
-    w.f0 = (it / nchunks) * kItemFrames;
+    w.f0 = (it / nchunks) * a.item_frames;
     w.row_begin = c * a.rows_per_item;
     w.chunk_row = w.row_begin;
     w.nrows = min(a.rows_per_item, a.nrows - w.row_begin);
-    w.gq = min(kItemFrames, a.nq - w.f0);
+    w.gq = min(a.item_frames, a.nq - w.f0);
     w.q0 = 0;
   } else {
     const Item itm = a.items[it];
@@ -429,6 +431,10 @@ struct SelRerankArgs {
   double lo_nmax;          // largest |d~|
   double lo_coef;
   int32_t nq;
+  // words mode, frame kernel: only positions with the frame's label (label, or
+  // frame / label_frames) count; rlabel NULL: all
+  const int32_t *rlabel;
+  int32_t label, label_frames;
   int32_t long_bands;      // fine: the screen's error bound leaves hundreds of rows per band
   int64_t *idx_out;        // fine: nq x m original indices
   float *dist_out;         // fine: nq x m

@@ -1095,7 +1095,6 @@ __device__ __forceinline__ void wave_sync() {
 // 25.7 -> 13.8, every row searched 44 -> 19; coarse stage, 2,048 frames 61 ->
 // 31, 256 frames 15.3 -> 11.2. What is left is the rows' way through L2 (2 KB
 // each, 110 a frame with bf16 rows, 527 with fp8 rows).
-constexpr int kFrameL = 64;       // survivor positions, one per lane
 constexpr int kFrameSlots = 64;   // region slots, one per lane
 constexpr int kFrameRegs = 8;     // positions per lane held in registers
 constexpr int kBandBlocks = 32;   // blocks re-scored per band round
@@ -1177,10 +1176,15 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
   // words (key mode: and their rows), requested together with the count
   const uint32_t *words = kKeys ? nullptr : a.cand + (int64_t)f * a.cap;
   const uint64_t *keys = kKeys ? a.keys + (int64_t)f * a.n_fixed : nullptr;
+  constexpr bool kWords = MODE == kCoarseWords;
+  const bool masked = kWords && a.rlabel;
+  const int lab = masked && a.label_frames > 0 ? f / a.label_frames : a.label;
   uint32_t rw[kFrameRegs], rp[kFrameRegs];  // word, payload (position; key mode: row)
+  int rl[kFrameRegs];
 #pragma unroll
   for (int u = 0; u < kFrameRegs; ++u) {
     const int i = (u * W + w) * 64 + lane;
+    rl[u] = masked && i < a.n_fixed ? a.rlabel[i] : lab;
     if (kKeys) {
       const uint64_t kk = i < a.n_fixed ? keys[i] : kKeyNone;
       rw[u] = (uint32_t)(kk >> 32);
@@ -1224,7 +1228,7 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
   };
 #pragma unroll
   for (int u = 0; u < kFrameRegs; ++u) {
-    if ((u * W + w) * 64 + lane >= n) rw[u] = kWordNone;
+    if ((u * W + w) * 64 + lane >= n || rl[u] != lab) rw[u] = kWordNone;
     account(rw[u], rp[u]);
   }
   const int nt = (n + 63) >> 6;  // tiles of 64 positions, wave w has tiles w, w + W, ..
@@ -1237,7 +1241,7 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
         const uint64_t kk = keys[i];
         v = (uint32_t)(kk >> 32);
         p = (uint32_t)kk;
-      } else {
+      } else if (!masked || a.rlabel[i] == lab) {
         v = words[i];
       }
     }
