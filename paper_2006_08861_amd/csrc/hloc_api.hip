@@ -675,6 +675,7 @@ void free_ws(hloc_ws *ws) {
   drop_graph(ws);
   for_each_buf(ws, [](WsBuf &b) { free_buf(b); });
   for (hipEvent_t e : ws->ev_pool) (void)hipEventDestroy(e);
+  if (ws->host) (void)hipHostFree(ws->host);
   if (ws->stream) (void)hipStreamDestroy(ws->stream);
   delete ws;
 }
@@ -774,6 +775,24 @@ int static_scratch(int dev, void **out) {
   }
   *out = g_scratch_ptr[dev];
   return HLOC_OK;
+}
+
+// The workspace's pinned block holds at least `bytes` (false: it cannot be had
+// and the caller copies instead).
+bool host_block(hloc_ws *ws, size_t bytes) {
+  if (ws->host && ws->host_bytes >= bytes) return true;
+  // (every call that uses the block has waited for its stream)
+  if (ws->host) (void)hipHostFree(ws->host);
+  ws->host = nullptr;
+  ws->host_bytes = 0;
+  const size_t want = std::max<size_t>(2 * bytes, 64 * 1024);
+  if (hipHostMalloc(&ws->host, want, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    ws->host = nullptr;
+    return false;
+  }
+  ws->host_bytes = want;
+  return true;
 }
 
 int info_of(hloc_ws *ws, int64_t *out, int32_t n) {
@@ -1339,6 +1358,45 @@ int hloc_query_batch(hloc_db *db, const float *q, int32_t nq, int32_t k, int32_t
   hloc_ws *ws = db->ws0;
   const bool want_agg = xy || tile || flags;
   const int64_t nqk = (int64_t)nq * k;
+  const int32_t nagg = want_agg ? nreq : 0;
+  {
+    // small calls: inputs and outputs in one pinned block
+    size_t used = 0;
+    auto place = [&](size_t bytes) {
+      const size_t at = used;
+      used += (bytes + 255) / 256 * 256;
+      return at;
+    };
+    const size_t o_q = place((size_t)nq * db->d * sizeof(float));
+    const size_t o_off = place((size_t)(nreq + 1) * sizeof(int32_t));
+    const size_t o_idx = place((size_t)nqk * sizeof(int64_t));
+    const size_t o_dist = place((size_t)nqk * sizeof(float));
+    const size_t o_xy = place((size_t)nagg * 2 * sizeof(double));
+    const size_t o_tile = place((size_t)nagg * 2 * sizeof(int32_t));
+    const size_t o_flags = place((size_t)nagg * sizeof(int32_t));
+    if (nq > 0 && used <= kHostDirectBytes && host_block(ws, used)) {
+      char *h = static_cast<char *>(ws->host);
+      std::memcpy(h + o_q, q, (size_t)nq * db->d * sizeof(float));
+      if (req_offsets) std::memcpy(h + o_off, req_offsets, (size_t)(nreq + 1) * sizeof(int32_t));
+      auto at = [&](size_t o) -> void * { return h + o; };
+      const int rc = enqueue_query(
+          ws, p, static_cast<float *>(at(o_q)),
+          req_offsets ? static_cast<int32_t *>(at(o_off)) : nullptr, nullptr,
+          static_cast<int64_t *>(at(o_idx)), static_cast<float *>(at(o_dist)),
+          want_agg ? static_cast<double *>(at(o_xy)) : nullptr,
+          want_agg ? static_cast<int32_t *>(at(o_tile)) : nullptr,
+          want_agg ? static_cast<int32_t *>(at(o_flags)) : nullptr, ws->stream);
+      // (also after an error: the block is not used before the stream is done)
+      HIPCHK(hipStreamSynchronize(ws->stream));
+      CHK(rc);
+      std::memcpy(idx, h + o_idx, (size_t)nqk * sizeof(int64_t));
+      std::memcpy(dist, h + o_dist, (size_t)nqk * sizeof(float));
+      if (xy && nagg > 0) std::memcpy(xy, h + o_xy, (size_t)nagg * 2 * sizeof(double));
+      if (tile && nagg > 0) std::memcpy(tile, h + o_tile, (size_t)nagg * 2 * sizeof(int32_t));
+      if (flags && nagg > 0) std::memcpy(flags, h + o_flags, (size_t)nagg * sizeof(int32_t));
+      return HLOC_OK;
+    }
+  }
   CHK(ws_ensure(ws, ws->s_q, (size_t)std::max<int64_t>((int64_t)nq * db->d, 1) * sizeof(float)));
   CHK(ws_ensure(ws, ws->s_off, (size_t)(nreq + 1) * sizeof(int32_t)));
   CHK(ws_ensure(ws, ws->s_idx, (size_t)std::max<int64_t>(nqk, 1) * sizeof(int64_t)));

@@ -64,6 +64,11 @@ constexpr int kWideDenseFrames = 512;  // batches from which the coarse screen u
 constexpr int64_t kDirectSlots = (int64_t)1 << 22;
 constexpr double kDirectFlops = 1.5e9;
 constexpr int kDirectSplits = 16;
+// Host-pointer calls whose inputs and outputs take at most this much go through
+// pinned memory that the kernels read and write themselves: each copy command
+// costs about 8 us, seven of them more than the kernels of one frame on 10k
+// rows. Larger ones are copied.
+constexpr size_t kHostDirectBytes = 256 * 1024;
 // Low-precision coarse screens: the fused product with key lists above
 // kKeyWords frame x representative words, the dense words below: storing them
 // costs less than the lists of many splits and the launches for deferred
@@ -117,6 +122,8 @@ struct hloc_ws {
       ckeys, cslots, cbounds,       // key lists of the fused coarse product
       cdefer;                       // frames its keys could not decide
   hloc::WsBuf s_q, s_off, s_idx, s_dist, s_xy, s_tile, s_flags;  // staging of host-pointer calls
+  void *host = nullptr;    // pinned memory of small host-pointer calls
+  size_t host_bytes = 0;
   int32_t last_nq = 0, last_nr = 0, last_kp = 0;
   bool fixed = false;  // buffers keep their sizes (a server's slot)
   bool last_direct = false, last_all = false;  // the last batch: no item list, every region kept
