@@ -69,6 +69,23 @@ def test_fft_parity(torch_cuda, length, d, nsig):
     check(x, d, got, f"len={length} d={d} nsig={nsig}")
 
 
+@pytest.mark.parametrize("length", [16, 32, 64, 128, 256, 512, 1024, 2048])
+def test_fft_signals_per_block(torch_cuda, length):
+    """Signal counts from one to past what a wave and a block of two or four
+    waves hold, to one bin, around the middle of the spectrum (where one lane
+    computes both bins of a pair) and to all of it; a row of large and one of
+    tiny values among them."""
+    full = length // 2 + 1
+    for nsig in (1, 2, 3, 5, 9, 17, 33, 65):
+        x = _signals(nsig, length, 2000 + length + nsig)
+        x[0] *= np.float32(1e30)
+        x[-1] *= np.float32(1e-30) if nsig > 1 else np.float32(1)
+        xd = torch_cuda.from_numpy(x).cuda()
+        for d in sorted({1, length // 4, length // 4 + 1, length // 2, full}):
+            got = hloc.fft_features(xd, d).cpu().numpy()
+            check(x, d, got, f"len={length} d={d} nsig={nsig}", min_exact=0.99)
+
+
 def test_fft_special_rows(torch_cuda):
     """Zeros, constants, pure tones, alternating signs, tiny and huge scales in
     one batch."""
