@@ -238,6 +238,13 @@ int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *byte
   return HLOC_OK;
 }
 
+// Frames in the pinned block of a host-pointer call: read once, not by every
+// kernel.
+bool in_host_block(const hloc_ws *ws, const void *p) {
+  const char *b = static_cast<const char *>(ws->host);
+  return b && p >= b && p < b + ws->host_bytes;
+}
+
 hipEvent_t take_event(hloc_ws *ws) {
   if (ws->ev_used == ws->ev_pool.size()) {
     hipEvent_t e;
@@ -292,7 +299,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
     HIPCHK(launch_fill_i32(misc, kMiscInts, 0, s));
     return HLOC_OK;
   }
-  float *qp = as<float>(ws->qp), *qn2 = as<float>(ws->qn2);
+  float *qp_ws = as<float>(ws->qp), *qn2 = as<float>(ws->qn2);
   int32_t *regions = as<int32_t>(ws->regions);
   Phaser ph(ws);
   ph.begin(HLOC_PHASE_PREP);
@@ -312,7 +319,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   pa.d = db->d;
   pa.dp = db->dp;
   pa.period = label_frames;
-  pa.qp = qp;
+  pa.qp = qp_ws;
   pa.qn2 = qn2;
   pa.zero = misc;
   pa.counts = as<int32_t>(ws->rcount);
@@ -327,7 +334,13 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
     pa.c_err = c_err;
     pa.c_lon = c_lon;
   }
-  HIPCHK(launch_prep_frames(fmt, pa, s));
+  // fp32 frames that need no padding stay where they are: the coarse screen of
+  // batches below the wide kernels' does the rest of the preparation
+  const bool in_place = !fmt && !p.exhaustive && label_frames == 0 && db->d == db->dp &&
+                        f32_wide_supports(db->dp) && p.nq < kWideDenseFrames &&
+                        (reinterpret_cast<uintptr_t>(q) & 15) == 0 && !in_host_block(ws, q);
+  const float *qp = in_place ? q : qp_ws;
+  if (!in_place) HIPCHK(launch_prep_frames(fmt, pa, s));
   // fp32 accumulation of rounded products: |q~||d~| <= 1.004 |q||d| for bf16,
   // <= (1 + 2^-4)^2 |q||d| for fp8 (relative rounding of at most 2^-4 per
   // value; subnormals are absolute and covered by the rounding-error terms);
@@ -372,6 +385,12 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
     sa.nq = p.nq;
     sa.frame_list = list;
     sa.frame_count = count;
+    if (in_place) {
+      sa.prep_qn2 = qn2;
+      sa.prep_zero = misc;
+      sa.prep_counts = pa.counts;
+      sa.n_counts = pa.n_counts;
+    }
     // large batches: 64 representatives staged in LDS against up to 256 frames
     // at a time (the wide kernels' dense mode) instead of re-reading them per
     // 16, as many frames as leave an item for every block

@@ -113,6 +113,12 @@ struct ScreenArgs {
   // entry, one per XCD span of the items (NULL: each block takes a fixed
   // share of its span)
   int32_t *item_ctr;
+  // dense mode, register kernel: squared norms of the frames (their qp is the
+  // caller's memory) and counters that this launch also writes, or NULL
+  float *prep_qn2;
+  int32_t *prep_zero;
+  int32_t *prep_counts;
+  int32_t n_counts;
   // direct mode (no item list): block b of the database's block table (first
   // row, rows, region, block of the region) against the frames that keep its
   // region, 16 at a time: rq[region * rq_stride ..], region_count[region] of

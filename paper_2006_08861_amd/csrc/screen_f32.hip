@@ -144,10 +144,20 @@ __global__ __launch_bounds__(256) void k_screen_f32(ScreenArgs a) {
 // frame loads and norms go out together once the item's frame list has been
 // read. HOIST (items of more than 64 rows: several row blocks per wave) loads
 // the frame operand once per item instead of once per row block.
-template <int NS, bool HOIST, bool DENSE>
+// With PREP (dense) the frames are the caller's own rows: the kernel takes
+// over what the preparation kernel does for them (counters cleared, squared
+// norms, here from the operand that every wave holds), a launch of 4 us in a
+// pass of 90.
+template <int NS, bool HOIST, bool DENSE, bool PREP = false>
 __global__ __launch_bounds__(256) void k_screen_blk(ScreenArgs a) {
   constexpr int DP = NS * 16;
   const int lane = lane_id(), w = wave_id(), nw = blockDim.x >> 6;
+  if (PREP) {
+    if (blockIdx.x == 0)
+      for (int t = threadIdx.x; t < kMiscInts; t += 256) a.prep_zero[t] = 0;
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < a.n_counts; t += gridDim.x * 256)
+      a.prep_counts[t] = 0;
+  }
   const int i = lane & 15, g = lane >> 4;
   int lo = 0, hi, nchunks = 1;
   if (DENSE) {
@@ -209,7 +219,17 @@ __global__ __launch_bounds__(256) void k_screen_blk(ScreenArgs a) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) bv[s] = qp[4 * s];
       }
-      const float qn = a.qn2[fr];
+      float qn = PREP ? 0.f : a.qn2[fr];
+      if (PREP) {
+        // the lane's quarter of its frame, then the other three
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          qn = fmaf(bv[s].x, bv[s].x,
+                    fmaf(bv[s].y, bv[s].y, fmaf(bv[s].z, bv[s].z, fmaf(bv[s].w, bv[s].w, qn))));
+        qn += __uint_as_float(lane_xor16(__float_as_uint(qn)));
+        qn += __uint_as_float(lane_xor32(__float_as_uint(qn)));
+        if (chunk_row == 0 && rb == 0 && i < gq && g == 0) a.prep_qn2[fr] = qn;
+      }
       v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
@@ -490,6 +510,12 @@ hipError_t launch_wide_t(const ScreenArgs &a, int32_t grid, int32_t num_cu, hipS
 
 template <int NS, bool DENSE>
 hipError_t launch_blk_t(const ScreenArgs &a, int32_t grid, hipStream_t s) {
+  if constexpr (DENSE) {
+    if (a.prep_qn2) {
+      if (a.rows_per_item > 64) return hipErrorInvalidValue;
+      return launch_kernel(k_screen_blk<NS, false, true, true>, dim3(grid), dim3(256), 0, s, a);
+    }
+  }
   if (a.rows_per_item > 64)
     return launch_kernel(k_screen_blk<NS, true, DENSE>, dim3(grid), dim3(256), 0, s, a);
   return launch_kernel(k_screen_blk<NS, false, DENSE>, dim3(grid), dim3(256), 0, s, a);
@@ -530,6 +556,7 @@ hipError_t prepare_screen_kernels() {
 
 hipError_t launch_screen_f32(const ScreenArgs &a, int32_t grid, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
+  if (a.prep_qn2 && !(a.dense && f32_wide_supports(a.dp))) return hipErrorInvalidValue;
   if (a.rows_per_item % 16 == 0) {
     switch (a.dp) {
 #define HLOC_WAVE_CASE(DPV)                                     \
