@@ -43,19 +43,35 @@ constexpr int kAggSmall = 512;  // pooled candidates up to which a request takes
 constexpr int kAggWaves = 4;    // waves per request of the large kernel
 
 // Optional frame list: request r pools batch frames frames[req_offsets[r] ..
-// req_offsets[r+1]-1] (n entries), NULL = the frames themselves.
+// req_offsets[r+1]-1] (n entries). With labels > 0 the batch holds `per` frames
+// once per label (frame p * per + f is frame f under label p) and a request of
+// frames req_offsets[r] .. pools each under every label: entries labels *
+// req_offsets[r] .. of a list (n = labels * per) whose entry labels * f + p is
+// that frame. Neither: the frames themselves.
 struct FrameList {
   const int32_t *frames;
   int32_t n;
+  int32_t labels, per;
+  __device__ __forceinline__ int limit(int nq) const { return frames || labels > 0 ? n : nq; }
+  __device__ __forceinline__ int at(int i) const {
+    return labels > 0 ? i % labels * per + i / labels : frames ? frames[i] : i;
+  }
 };
 
-// Pooled candidates of request req (0 for an empty or malformed request).
-__device__ __forceinline__ int pooled_of(const AggArgs &a, FrameList fl, int req) {
+// First and last + 1 list entry of request req.
+__device__ __forceinline__ int2 entries_of(const AggArgs &a, const FrameList &fl, int req) {
+  const int scale = fl.labels > 0 ? fl.labels : 1;
   const int f0 = a.req_offsets ? a.req_offsets[req] : req;
   const int f1 = a.req_offsets ? a.req_offsets[req + 1] : req + 1;
+  return make_int2(scale * f0, scale * f1);
+}
+
+// Pooled candidates of request req (0 for an empty or malformed request).
+__device__ __forceinline__ int pooled_of(const AggArgs &a, const FrameList &fl, int req) {
+  const int2 e = entries_of(a, fl, req);
   const int kr = a.req_k ? a.req_k[req] : a.k;
-  if (f0 < 0 || f1 < f0 || f1 > (fl.frames ? fl.n : a.nq) || kr < 1 || kr > a.k) return 0;
-  return (int)min<int64_t>((int64_t)(f1 - f0) * kr, (int64_t)kAggMax + 1);
+  if (e.x < 0 || e.y < e.x || e.y > fl.limit(a.nq) || kr < 1 || kr > a.k) return 0;
+  return (int)min<int64_t>((int64_t)(e.y - e.x) * kr, (int64_t)kAggMax + 1);
 }
 
 // Slots of the table for P candidates (at least twice as many).
@@ -93,7 +109,7 @@ __device__ __forceinline__ bool tile_before(int c0, uint64_t k0, int c1, uint64_
 // Algorithm 2 for one request of at most CAP candidates (or a malformed one),
 // by W waves; key / count hold agg_slots(CAP) entries.
 template <int CAP, int W>
-__device__ void aggregate_one(const AggArgs &a, FrameList fl, int req, uint64_t *key, int *count,
+__device__ void aggregate_one(const AggArgs &a, const FrameList &fl, int req, uint64_t *key, int *count,
                               AggShared &sh) {
   constexpr int kThreads = 64 * W;
   const int tid = threadIdx.x, lane = lane_id(), w = W == 1 ? 0 : wave_id();
@@ -106,8 +122,8 @@ __device__ void aggregate_one(const AggArgs &a, FrameList fl, int req, uint64_t 
       __syncthreads();
     }
   };
-  const int f0 = a.req_offsets ? a.req_offsets[req] : req;
-  const int f1 = a.req_offsets ? a.req_offsets[req + 1] : req + 1;
+  const int2 ent = entries_of(a, fl, req);
+  const int f0 = ent.x, f1 = ent.y;
   const int kr = a.req_k ? a.req_k[req] : a.k;  // candidates pooled per frame
   auto none = [&](int flag) {
     if (tid == 0) {
@@ -118,7 +134,7 @@ __device__ void aggregate_one(const AggArgs &a, FrameList fl, int req, uint64_t 
       a.flags[req] = flag;
     }
   };
-  if (f0 < 0 || f1 < f0 || f1 > (fl.frames ? fl.n : a.nq) || kr < 1 || kr > a.k ||
+  if (f0 < 0 || f1 < f0 || f1 > fl.limit(a.nq) || kr < 1 || kr > a.k ||
       (int64_t)(f1 - f0) * kr > (int64_t)CAP) {
     none(kFlagBad);
     return;
@@ -142,7 +158,7 @@ __device__ void aggregate_one(const AggArgs &a, FrameList fl, int req, uint64_t 
     for (int u = 0; u < U; ++u) {
       const int p = min(p0 + u * kThreads, P - 1), fr = p / kr;
       at[u] = p - fr * kr;
-      frame[u] = fl.frames ? fl.frames[f0 + fr] : f0 + fr;
+      frame[u] = fl.at(f0 + fr);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -327,11 +343,9 @@ hipError_t prepare_aggregate_kernels() {
   return e;
 }
 
-hipError_t launch_aggregate_frames(const AggArgs &a, const int32_t *frames, int32_t n_frames,
-                                   hipStream_t s) {
+static hipError_t launch_listed(const AggArgs &a, const FrameList &fl, hipStream_t s) {
   if (a.nreq <= 0) return hipSuccess;
   if (a.top_c < 1 || a.top_c > 64) return hipErrorInvalidValue;
-  const FrameList fl{frames, frames ? n_frames : 0};
   const int32_t cus = std::max(a.num_cu, 1);
   if (a.nreq <= cus) {
     // one round of blocks: a single launch with the large lists
@@ -343,6 +357,15 @@ hipError_t launch_aggregate_frames(const AggArgs &a, const int32_t *frames, int3
   if (e != hipSuccess) return e;
   // one resident block per compute unit at most (the table takes 98 KB of LDS)
   return launch_kernel(k_aggregate_big, dim3(cus), dim3(64 * kAggWaves), kAggLds, s, a, fl);
+}
+
+hipError_t launch_aggregate_frames(const AggArgs &a, const int32_t *frames, int32_t n_frames,
+                                   hipStream_t s) {
+  return launch_listed(a, FrameList{frames, frames ? n_frames : 0, 0, 0}, s);
+}
+
+hipError_t launch_aggregate_labels(const AggArgs &a, int32_t labels, int32_t per, hipStream_t s) {
+  return launch_listed(a, FrameList{nullptr, labels * per, labels, per}, s);
 }
 
 hipError_t launch_aggregate(const AggArgs &a, hipStream_t s) {

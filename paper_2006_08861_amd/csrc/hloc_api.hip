@@ -684,7 +684,7 @@ void for_each_buf(hloc_ws *ws, F f) {
                    &ws->s_dist,   &ws->s_xy,     &ws->s_tile,   &ws->s_flags, &ws->q_lp,
                    &ws->q_scale,  &ws->q_err,    &ws->q_lon,   &ws->slot_row, &ws->slot_len, &ws->n_rows, &ws->fstat,
                    &ws->c_lp,     &ws->c_err,   &ws->c_lon,   &ws->agg_big,
-                   &ws->lab_off,  &ws->lab_list,  &ws->ckeys,
+                   &ws->ckeys,
                    &ws->cslots,   &ws->cbounds,  &ws->cdefer};
   for (WsBuf *b : bufs) f(*b);
 }
@@ -1245,15 +1245,11 @@ int hloc_query_labels_async(hloc_db *db, const float *q, int32_t nq, int32_t k,
   }
   if (nreq == 0) return HLOC_OK;
   // every request pools its frames' lists under every label
-  CHK(ws_ensure(ws, ws->lab_off, (size_t)(nreq + 1) * sizeof(int32_t)));
-  CHK(ws_ensure(ws, ws->lab_list, (size_t)std::max<int64_t>((int64_t)nq * P, 1) * sizeof(int32_t)));
-  int32_t *lab_off = as<int32_t>(ws->lab_off), *lab_list = as<int32_t>(ws->lab_list);
-  HIPCHK(launch_label_lists(req_offsets, nreq, nq, P, lab_off, lab_list, s));
   AggArgs ag{};
   ag.idx = idx;
   ag.k = k;
   ag.nq = nq * P;
-  ag.req_offsets = lab_off;
+  ag.req_offsets = req_offsets;
   ag.req_k = nullptr;
   ag.nreq = nreq;
   ag.tile_of = db->tiles;
@@ -1267,7 +1263,7 @@ int hloc_query_labels_async(hloc_db *db, const float *q, int32_t nq, int32_t k,
   ag.big_list = as<int32_t>(ws->agg_big);
   ag.big_count = as<int32_t>(ws->misc) + 8;  // cleared by the last search's prep
   ag.num_cu = db->num_cu;
-  HIPCHK(launch_aggregate_frames(ag, lab_list, nq * P, s));
+  HIPCHK(launch_aggregate_labels(ag, P, nq, s));
   return HLOC_OK;
 }
 

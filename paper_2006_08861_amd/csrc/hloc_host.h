@@ -118,7 +118,6 @@ struct hloc_ws {
       fstat,                        // fine select's per-frame statistics
       c_lp, c_err, c_lon,           // bf16 frame copy for the coarse screen of fp8 queries
       agg_big,                      // requests for the large-list aggregation kernel
-      lab_off, lab_list,            // frame lists of a query over subspace labels
       ckeys, cslots, cbounds,       // key lists of the fused coarse product
       cdefer;                       // frames its keys could not decide
   hloc::WsBuf s_q, s_off, s_idx, s_dist, s_xy, s_tile, s_flags;  // staging of host-pointer calls
@@ -247,11 +246,12 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
                   int32_t n_frames = 0, int32_t label = -1, int32_t label_frames = 0);
 hipError_t launch_mask_label(uint32_t *words, int32_t nq, int32_t R, const int32_t *rlabel,
                              int32_t p, int32_t per, hipStream_t s);
-hipError_t launch_label_lists(const int32_t *req_offsets, int32_t nreq, int32_t nq, int32_t P,
-                              int32_t *list_off, int32_t *list, hipStream_t s);
 // The aggregation of aggregate.hip over a frame list (NULL: contiguous frames).
 hipError_t launch_aggregate_frames(const AggArgs &a, const int32_t *frames, int32_t n_frames,
                                    hipStream_t s);
+// The same over a batch that holds `per` frames once per label: a request's
+// frames under every label.
+hipError_t launch_aggregate_labels(const AggArgs &a, int32_t labels, int32_t per, hipStream_t s);
 int check_query_args(const hloc_db *db, const float *q, int32_t nq, const int32_t *req_offsets,
                      int32_t nreq, int32_t precision, const int64_t *idx, const float *dist);
 int new_ws(hloc_db *db, hloc_ws **out);

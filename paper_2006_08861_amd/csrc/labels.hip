@@ -33,24 +33,4 @@ hipError_t launch_mask_label(uint32_t *words, int32_t nq, int32_t R, const int32
                        per);
 }
 
-// Frame lists of the labelled query: the results of frame f under label p
-// are row p * nq + f of the stacked per-label lists; request r pools the
-// entries P * off[r] .. P * off[r+1] - 1, entry P * f + p naming that row.
-__global__ void k_label_lists(const int32_t *__restrict__ req_offsets, int nreq, int nq, int P,
-                              int32_t *list_off, int32_t *list) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t <= nreq) list_off[t] = P * (req_offsets ? req_offsets[t] : (int32_t)t);
-  if (t < (int64_t)nq * P) {
-    const int f = (int)(t / P), p = (int)(t % P);
-    list[t] = p * nq + f;
-  }
-}
-
-hipError_t launch_label_lists(const int32_t *req_offsets, int32_t nreq, int32_t nq, int32_t P,
-                              int32_t *list_off, int32_t *list, hipStream_t s) {
-  const int64_t n = std::max<int64_t>((int64_t)nq * P, (int64_t)nreq + 1);
-  return launch_kernel(k_label_lists, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       req_offsets, nreq, nq, P, list_off, list);
-}
-
 }  // namespace hloc

@@ -129,12 +129,23 @@ __global__ __launch_bounds__(kStreamThreads) void k_stream_windows(
 // One block per segment: the stream's new history is the last M - 1 lists of
 // (its history, its new frames); the lists that stay are read before any is
 // written.
+// The blocks past the segments copy the new frames' lists to idx (n_idx
+// values; a copy command of its own costs more than this launch).
 __global__ __launch_bounds__(256) void k_stream_update(const int32_t *seg_off,
                                                        const int32_t *seg_stream,
-                                                       const int32_t *seg_ok, int S, int M, int k,
-                                                       int64_t *lists, int32_t *count) {
+                                                       const int32_t *seg_ok, int nseg, int S,
+                                                       int M, int k, int64_t *lists,
+                                                       int32_t *count, int64_t *idx,
+                                                       int64_t n_idx) {
   extern __shared__ int64_t s_keep[];  // (M - 1) x k
   const int g = blockIdx.x;
+  if (g >= nseg) {
+    const int64_t *all = lists + (int64_t)S * (M - 1) * k;
+    for (int64_t t = (int64_t)(g - nseg) * blockDim.x + threadIdx.x; t < n_idx;
+         t += (int64_t)(gridDim.x - nseg) * blockDim.x)
+      idx[t] = all[t];
+    return;
+  }
   if (!seg_ok[g]) return;
   const int s = seg_stream[g], H = M - 1;
   const int nnew = seg_off[g + 1] - seg_off[g];
@@ -302,13 +313,13 @@ int hloc_query_streams_async(hloc_streams *st, const float *q, int32_t nq, int32
   ag.num_cu = db->num_cu;
   HIPCHK(launch_aggregate_frames(ag, st->win_list, (int32_t)std::min<int64_t>(
                                      (int64_t)nq * M, INT32_MAX), s));
-  if (H > 0)
-    HIPCHK(launch_kernel(k_stream_update, dim3(nseg), dim3(256),
+  const int64_t n_idx = idx ? (int64_t)nq * k : 0;
+  const int32_t segs = H > 0 ? nseg : 0;  // (no history to update without)
+  const int32_t copies = (int32_t)std::min<int64_t>((n_idx + 255) / 256, 1024);
+  if (segs + copies > 0)
+    HIPCHK(launch_kernel(k_stream_update, dim3(segs + copies), dim3(256),
                          (uint32_t)((size_t)H * k * sizeof(int64_t)), s, seg_offsets, seg_stream,
-                         seg_ok, S, M, k, st->lists, st->count));
-  if (idx)
-    HIPCHK(hipMemcpyAsync(idx, fresh, (size_t)nq * k * sizeof(int64_t), hipMemcpyDeviceToDevice,
-                          s));
+                         seg_ok, segs, S, M, k, st->lists, st->count, idx, n_idx));
   return HLOC_OK;
 }
 
