@@ -1515,12 +1515,15 @@ hipError_t prepare_select_kernels() {
 // 1,265 frames of 200k x 256 fp32 rows 95 / 58 / 37 / 36; 256 frames of them
 // 41 / 25 / 17 / 14. Coarse, keys, 32,768 frames 172 / 292 / 509 / -; 2,048
 // frames 35 / 37 / 42 / -; words, 1,265 frames 16 / 14 / 21 / -; 256 frames
-// 13 / 12 / 11 / 13. The lists of all waves are merged in two registers per
-// lane: W * L <= 128.
+// 13 / 12 / 11 / 13. A frame list names the few frames of a large batch that
+// the coarse keys could not decide (79 of those 32,768, each with 4,096 words
+// to read): their launch waits for one frame, not for the chip, and takes 51 /
+// 39 / 33 with the dense screen before it. The lists of all waves are merged in
+// two registers per lane: W * L <= 128.
 int frame_waves(const SelRerankArgs &a) {
   int W;
   if (a.blocks) W = a.long_bands ? (a.nq >= 8192 ? 4 : 8) : a.nq >= 4096 ? 2 : a.nq >= 1536 ? 4 : 8;
-  else W = a.nq >= 2048 ? 1 : a.nq >= 1024 ? 2 : 4;
+  else W = a.frame_list ? 4 : a.nq >= 2048 ? 1 : a.nq >= 1024 ? 2 : 4;
   while (W * a.L > 128) W /= 2;
   return W;
 }
