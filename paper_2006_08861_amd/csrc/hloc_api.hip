@@ -566,7 +566,12 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
     const int32_t blocks = db->num_cu * db->tile_blocks;
     HIPCHK(fmt ? launch_screen_direct_lp(fmt, sb, blocks, s) : launch_screen_direct(sb, blocks, s));
   } else {
-    HIPCHK(fmt ? launch_screen_lp(fmt, sb, p.grid2, s) : launch_screen_f32(sb, p.grid2, s));
+    // the exhaustive search of more than a group of frames has wide items only
+    // where there is a wide kernel: the narrow launch would find nothing to do
+    // (4.6 us of 344 for 256 frames against 200k x 256 fp32 rows)
+    const bool all_wide = p.exhaustive && p.nq > kGroup && (rs || lds_wide);
+    if (!all_wide)
+      HIPCHK(fmt ? launch_screen_lp(fmt, sb, p.grid2, s) : launch_screen_f32(sb, p.grid2, s));
     ph.begin(HLOC_PHASE_SCREEN_WIDE);
     HIPCHK(fmt ? launch_screen_wide_lp(fmt, sb, p.grid2, db->num_cu, s)
                : launch_screen_wide_f32(sb, p.grid2, db->num_cu, s));
