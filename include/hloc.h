@@ -292,7 +292,8 @@ int hloc_reserve(hloc_db *db, int32_t nq_max, int32_t nreq_max, int32_t k_max,
 
 /*
  * Per-database counters of the last query call (waits for it): out[0] work
- * items of the fine screen, out[1] frames whose coarse selection failed its
+ * items of the fine screen (batches screened without an item list: pairs of a
+ * 16-row block and a group of 16 frames), out[1] frames whose coarse selection failed its
  * certificate (so the band of uncertain regions was re-scored in FP64),
  * out[2] frames whose top-k did (the band of uncertain rows), out[3] largest
  * count of 16-row candidate blocks of a frame, out[4] survivor rows per
@@ -363,12 +364,15 @@ int hloc_ws_replay(hloc_ws *ws, void *stream);
 /*
  * Device-time profile of the query path, measured with HIP events recorded on
  * the query's stream around each phase:
- *   HLOC_PHASE_PREP      query norms and padded copy
+ *   HLOC_PHASE_PREP      query norms and copies (none where the coarse screen
+ *                        uses the frames in place)
  *   HLOC_PHASE_COARSE    coarse screen against the region representatives
  *   HLOC_PHASE_COARSE_SELECT select + FP64 re-score of the regions of each frame
- *   HLOC_PHASE_SCHED     region -> frames lists and work items
- *   HLOC_PHASE_SCREEN    fine screen of the narrow work items (and of every item
- *                        at padded lengths without a register kernel)
+ *   HLOC_PHASE_SCHED     region -> frames lists and work items (none for small
+ *                        batches, which are screened without an item list)
+ *   HLOC_PHASE_SCREEN    fine screen of small batches, or of the narrow work
+ *                        items (and of every item at padded lengths without a
+ *                        register kernel)
  *   HLOC_PHASE_SCREEN_WIDE fine screen of the wide work items (regions kept by
  *                        more than 16 frames)
  *   HLOC_PHASE_SELECT    per-frame select, FP64 rerank, certificate, exact fallback

@@ -482,7 +482,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
     ra.bounds = ca.bounds;
     ra.n_bounds = p.csplits * 4;
     ra.defer_list = as<int32_t>(ws->cdefer);
-    ra.defer_count = misc + 10;  // cleared by the prep kernel
+    ra.defer_count = misc + 10;  // cleared by the batch's first launch
     ra.L = p.L1;
     ra.m = p.nr;
     ra.src64 = db->rep64;

@@ -259,7 +259,7 @@ __device__ __forceinline__ void direct_groups(const ScreenArgs &a, int i, F f) {
   }
 }
 
-// Per-batch counters of a workspace (cleared by the prep kernel): [0] items,
+// Per-batch counters of a workspace (cleared by the batch's first launch): [0] items,
 // [1] coarse fallbacks, [4] narrow items, [5] steps per wide item, [8] large
 // aggregation lists, [10] deferred coarse frames, from [kMiscItemCtr] on the wide screen's item
 // counters, one per XCD, each on a cache line of its own: on one line the

@@ -309,7 +309,7 @@ int hloc_query_streams_async(hloc_streams *st, const float *q, int32_t nq, int32
   ag.tile = tile;
   ag.flags = flags;
   ag.big_list = as<int32_t>(st->ws->agg_big);
-  ag.big_count = as<int32_t>(st->ws->misc) + 8;  // cleared by the retrieval's prep kernel
+  ag.big_count = as<int32_t>(st->ws->misc) + 8;  // cleared by the retrieval's first launch
   ag.num_cu = db->num_cu;
   HIPCHK(launch_aggregate_frames(ag, st->win_list, (int32_t)std::min<int64_t>(
                                      (int64_t)nq * M, INT32_MAX), s));
