@@ -1098,6 +1098,40 @@ def test_item_list_and_direct_screen_agree(torch_cuda, precision, d, n_reg):
     assert st["recall"] == 1.0
 
 
+@pytest.mark.parametrize("precision,d", [("fp32", 256), ("fp32", 200), ("bf16", 256),
+                                         ("bf16", 192), ("fp8", 256)])
+def test_exhaustive_item_list_group_edge(torch_cuda, precision, d):
+    # every row searched past the direct screen's work: 16 frames have narrow
+    # items only, 17 wide ones only (at lengths with and without a wide
+    # kernel); the same bits as batches of 4 frames, which need no list, and
+    # two frames against the oracle
+    rng = np.random.default_rng(31)
+    sizes = rng.integers(1, 9000, 56)
+    sizes[-1] += 250_037 - sizes.sum()
+    region_of = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    n, R = len(region_of), len(sizes)
+    feats = rng.standard_normal((n, d), dtype=np.float32)
+    xy = rng.uniform(0, 40, size=(n, 2))
+    q = feats[rng.integers(0, n, 17)] + 0.1 * rng.standard_normal((17, d), dtype=np.float32)
+    say(f"[case] {n} rows, d {d}, {precision}")
+    db = make_db(feats, xy, region_of, R, mirrors=MIRRORS[precision])
+    parts = [run_device(torch_cuda, db, q[a:a + 4], 9, R, precision=precision)
+             for a in range(0, 17, 4)]
+    for nq in (16, 17):
+        full = run_device(torch_cuda, db, q[:nq], 9, R, precision=precision)
+        info = db.info()
+        assert info["items"] > 0
+        assert info["narrow_items"] == (info["items"] if nq == 16 else 0)
+        for key in ("idx", "dist", "xy", "tile", "flags"):
+            want = np.concatenate([x[key] for x in parts])[:nq]
+            assert full[key].tobytes() == want.tobytes(), (nq, key)
+    db.close()
+    ora = oracle.localize(feats, xy, region_of, R, q[:2], np.arange(3), 9, R, (0.5, 1, 0.0, 0))
+    st = judge_frames(full["idx"][:2], full["dist"][:2], None, ora, feats, region_of, R, q[:2], 9)
+    say(f"[ok] {st}")
+    assert st["recall"] == 1.0
+
+
 @pytest.mark.parametrize("spread,agg", [(0.05, (0.3, 10, 3.0, 20)), (30.0, (0.3, 10, 3.0, 20)),
                                         (600.0, (0.3, 64, 0.0, 99)), (600.0, (0.3, 64, 3.0, 50)),
                                         (3.0, (0.5, 1, 0.0, 0))])
