@@ -294,6 +294,7 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   ws->last_kp = p.kp;
   ws->last_direct = p.direct;
   ws->last_all = p.exhaustive;
+  ws->last_start = db->h_reg_start;
   int32_t *misc = as<int32_t>(ws->misc);
   if (p.nq == 0) {
     HIPCHK(launch_fill_i32(misc, kMiscInts, 0, s));
@@ -719,8 +720,9 @@ int new_ws(hloc_db *db, hloc_ws **out) {
 // Sum over regions of ceil(size / rows).
 int64_t count_chunks(const hloc_db *db, int32_t rows) {
   int64_t c = 0;
-  for (size_t r = 0; r + 1 < db->h_reg_start.size(); ++r)
-    c += (db->h_reg_start[r + 1] - db->h_reg_start[r] + rows - 1) / rows;
+  if (!db->h_reg_start) return 0;
+  const std::vector<int64_t> &st = *db->h_reg_start;
+  for (size_t r = 0; r + 1 < st.size(); ++r) c += (st[r + 1] - st[r] + rows - 1) / rows;
   return c;
 }
 
@@ -848,7 +850,7 @@ int info_of(hloc_ws *ws, int64_t *out, int32_t n) {
   int64_t items = misc[0], narrow = misc[4];
   if (ws->last_direct && ws->last_nq > 0 && ws->db->has_regions) {
     // no item list: (16-row block, 16-frame group) pairs stand for it
-    const auto &st = ws->db->h_reg_start;
+    const std::vector<int64_t> &st = *ws->db->h_reg_start;
     std::vector<int32_t> rc(st.size() - 1, ws->last_nq);
     if (!ws->last_all)
       HIPCHK(hipMemcpy(rc.data(), ws->rcount.p, rc.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
@@ -1064,7 +1066,7 @@ int hloc_set_regions(hloc_db *db, const int32_t *region_of, int32_t n_regions_to
   }
   db->R = R;
   db->R_nonempty = (int32_t)std::count_if(sizes.begin(), sizes.end(), [](int64_t z) { return z > 0; });
-  db->h_reg_start = start;
+  db->h_reg_start = std::make_shared<const std::vector<int64_t>>(start);
   std::vector<int64_t> desc(sizes);
   std::sort(desc.begin(), desc.end(), std::greater<int64_t>());
   db->h_desc_prefix.assign(R + 1, 0);
@@ -1178,11 +1180,12 @@ int hloc_set_region_labels(hloc_db *db, const int32_t *labels, int32_t n_labels)
   if (!labels) return fail(HLOC_EINVAL, "labels is NULL");
   if (n_labels < 1 || n_labels > HLOC_MAX_LABELS)
     return fail(HLOC_EINVAL, "n_labels must be in 1..%d (got %d)", HLOC_MAX_LABELS, n_labels);
+  const std::vector<int64_t> &start = *db->h_reg_start;
   std::vector<int32_t> nonempty((size_t)n_labels, 0);
   for (int32_t r = 0; r < db->R; ++r) {
     if (labels[r] < 0 || labels[r] >= n_labels)
       return fail(HLOC_EINVAL, "labels[%d] = %d is outside [0, %d)", r, labels[r], n_labels);
-    if (db->h_reg_start[r + 1] > db->h_reg_start[r]) ++nonempty[(size_t)labels[r]];
+    if (start[r + 1] > start[r]) ++nonempty[(size_t)labels[r]];
   }
   for (int32_t p = 0; p < n_labels; ++p)
     if (nonempty[(size_t)p] == 0)
@@ -1198,7 +1201,7 @@ int hloc_set_region_labels(hloc_db *db, const int32_t *labels, int32_t n_labels)
   // an empty region's zero representative must not be re-scored as a region)
   std::vector<int32_t> dev_labels(labels, labels + db->R);
   for (int32_t r = 0; r < db->R; ++r)
-    if (db->h_reg_start[r + 1] == db->h_reg_start[r]) dev_labels[(size_t)r] = -1;
+    if (start[r + 1] == start[r]) dev_labels[(size_t)r] = -1;
   CHK(dev_alloc(&db->rlabel, (size_t)db->R));
   HIPCHK(hipMemcpy(db->rlabel, dev_labels.data(), (size_t)db->R * sizeof(int32_t),
                    hipMemcpyHostToDevice));
@@ -1551,11 +1554,14 @@ int hloc_last_regions(hloc_db *db, int32_t *out, int32_t *nq, int32_t *n_regions
   if (g.err != hipSuccess) return fail(HLOC_EDEVICE, "hipSetDevice failed");
   HIPCHK(hipDeviceSynchronize());
   if (ws->last_all) {
-    // every non-empty region, in id order, for each frame
-    int32_t *o = out;
-    for (int32_t f = 0; f < ws->last_nq; ++f)
-      for (int32_t r = 0; r < db->R; ++r)
-        if (db->h_reg_start[r + 1] > db->h_reg_start[r]) *o++ = r;
+    // every region that was non-empty then (last_nr of them), in id order, for
+    // each frame
+    const std::vector<int64_t> &st = *ws->last_start;
+    int32_t j = 0;
+    for (size_t r = 0; r + 1 < st.size(); ++r)
+      if (st[r + 1] > st[r]) out[j++] = (int32_t)r;
+    for (int32_t f = 1; f < ws->last_nq; ++f)
+      std::copy(out, out + j, out + (int64_t)f * j);
     return HLOC_OK;
   }
   HIPCHK(hipMemcpy(out, ws->regions.p, (size_t)ws->last_nq * ws->last_nr * sizeof(int32_t),

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -126,6 +127,9 @@ struct hloc_ws {
   int32_t last_nq = 0, last_nr = 0, last_kp = 0;
   bool fixed = false;  // buffers keep their sizes (a server's slot)
   bool last_direct = false, last_all = false;  // the last batch: no item list, every region kept
+  // the regions the last batch ran on (hloc_set_regions may have replaced the
+  // database's since; what is told about the batch is still about these)
+  std::shared_ptr<const std::vector<int64_t>> last_start;
   bool prof_on = false;
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used = 0;
@@ -160,7 +164,7 @@ struct hloc_db {
   int64_t max_region = 0;
   double kept_rows = 0.0;              // mean size of a row's region: rows of a typical kept region
   int64_t *reg_start = nullptr;
-  std::vector<int64_t> h_reg_start;
+  std::shared_ptr<const std::vector<int64_t>> h_reg_start;  // the same on the host; replaced, never changed
   std::vector<int64_t> h_desc_prefix;  // sum of the j largest region sizes, j = 0..R
   std::vector<int64_t> h_desc_blocks;  // sum of the j largest regions' 16-row block counts
   int64_t n_blocks = 0;                // 16-row blocks over all regions
