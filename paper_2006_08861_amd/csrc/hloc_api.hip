@@ -848,9 +848,10 @@ int info_of(hloc_ws *ws, int64_t *out, int32_t n) {
     }
   }
   int64_t items = misc[0], narrow = misc[4];
-  if (ws->last_direct && ws->last_nq > 0 && ws->db->has_regions) {
-    // no item list: (16-row block, 16-frame group) pairs stand for it
-    const std::vector<int64_t> &st = *ws->db->h_reg_start;
+  if (ws->last_direct && ws->last_nq > 0 && ws->last_start) {
+    // no item list: (16-row block, 16-frame group) pairs stand for it, over the
+    // regions that the batch ran on (rcount holds as many)
+    const std::vector<int64_t> &st = *ws->last_start;
     std::vector<int32_t> rc(st.size() - 1, ws->last_nq);
     if (!ws->last_all)
       HIPCHK(hipMemcpy(rc.data(), ws->rcount.p, rc.size() * sizeof(int32_t), hipMemcpyDeviceToHost));

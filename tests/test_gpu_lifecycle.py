@@ -49,3 +49,27 @@ def test_last_regions_after_new_regions(torch_cuda, n_after):
     assert buf[:15].reshape(3, 5).tolist() == [[0, 1, 3, 4, 5]] * 3
     assert (buf[15:] == -7).all()
     db.close()
+
+
+@pytest.mark.parametrize("n_reg", [3, 6])
+def test_info_after_new_regions(torch_cuda, n_reg):
+    # counters of a batch without an item list, on the database's workspace and
+    # on one of the caller's, after the database went from 6 to 1,200 regions
+    # (more than its per-region buffers hold): the batch's, as before
+    feats, xy = _feats(1200, 32, 4)
+    q = torch_cuda.from_numpy(feats[:40]).cuda()
+    db = hloc.HlocDB(feats, xy)
+    db.set_regions((np.arange(1200) % 6).astype(np.int32), 6)
+    ws = hloc.Workspace(db)
+    out = ws.outputs(40, 40, 4, "cuda")
+    ws.query_async(q, 4, n_reg, None, out, torch_cuda.cuda.current_stream())
+    db.query(q, 4, n_reg)
+    before = db.info()
+    say(f"[case] {n_reg} of 6 regions, then 1,200: {before}")
+    # every region has 200 rows: 13 blocks, against groups of 16 of its frames
+    assert before["items"] >= 13 * n_reg and before["candidates"] == 40 * 200 * n_reg
+    assert ws.info() == before
+    db.set_regions(np.arange(1200, dtype=np.int32), 1200)
+    assert db.info() == before and ws.info() == before
+    ws.close()
+    db.close()
