@@ -163,6 +163,18 @@ int make_plan(const hloc_db *db, int32_t nq, int32_t k, int32_t n_regions, int32
   return HLOC_OK;
 }
 
+// Buffers of the fused coarse product for `lists` (frame, split) key lists.
+size_t key_bytes(int64_t lists) { return (size_t)lists * kCgKeys * sizeof(uint64_t); }
+size_t key_slot_bytes(int64_t lists) { return (size_t)lists * 4 * kCgKeep * sizeof(uint4); }
+size_t key_bound_bytes(int64_t lists) { return (size_t)lists * 4 * sizeof(uint64_t); }
+
+bool key_lists_fit(const hloc_ws *ws, const Plan &p) {
+  const int64_t lists = (int64_t)p.nq * p.csplits;
+  return ws->ckeys.cap >= key_bytes(lists) && ws->cslots.cap >= key_slot_bytes(lists) &&
+         ws->cbounds.cap >= key_bound_bytes(lists) &&
+         ws->cdefer.cap >= (size_t)p.nq * sizeof(int32_t);
+}
+
 int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *bytes,
                      const Carve *carve) {
   const hloc_db *db = ws->db;
@@ -186,9 +198,10 @@ int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *byte
   CHK(fit(ws->qp, (size_t)nq * db->dp * sizeof(float)));
   CHK(fit(ws->qn2, (size_t)nq * sizeof(float)));
   if (p.coarse_keys) {
-    CHK(fit(ws->ckeys, (size_t)nq * p.csplits * kCgKeys * sizeof(uint64_t)));
-    CHK(fit(ws->cslots, (size_t)nq * p.csplits * 4 * kCgKeep * sizeof(uint4)));
-    CHK(fit(ws->cbounds, (size_t)nq * p.csplits * 4 * sizeof(uint64_t)));
+    const int64_t lists = nq * p.csplits;
+    CHK(fit(ws->ckeys, key_bytes(lists)));
+    CHK(fit(ws->cslots, key_slot_bytes(lists)));
+    CHK(fit(ws->cbounds, key_bound_bytes(lists)));
     CHK(fit(ws->cdefer, (size_t)nq * sizeof(int32_t)));
   }
   if (!p.exhaustive) {
@@ -285,9 +298,17 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   const hloc_db *db = ws->db;
   const bool want_agg = xy || tile || flags;
   Plan p = plan;
-  if (ws->fixed && p.direct && !p.exhaustive && ws->cand1.cap < coarse_list_bytes(p.nq, db->R))
-    p.direct = false;
-  if (ws->fixed && p.terms == 2 && ws->q_lp.cap < (size_t)p.nq * db->dp * 2) p.terms = 1;
+  // A form may take more of a buffer than a larger batch in another form did
+  // (frame lists behind the coarse words, a second fp8 vector, key lists).
+  // Where a buffer must not grow (a server's slot is sized once; a captured
+  // graph holds the addresses) the batch takes the other form: the same
+  // results, and words, items and one vector never take more for fewer frames.
+  if (ws->fixed || ws->exec) {
+    if (p.direct && !p.exhaustive && ws->cand1.cap < coarse_list_bytes(p.nq, db->R))
+      p.direct = false;
+    if (p.terms == 2 && ws->q_lp.cap < (size_t)p.nq * db->dp * 2) p.terms = 1;
+    if (p.coarse_keys && !key_lists_fit(ws, p)) p.coarse_keys = false;
+  }
   CHK(ensure_workspace(ws, p, want_agg && !(xy && tile && flags)));
   ws->last_nq = p.nq;
   ws->last_nr = p.nr;

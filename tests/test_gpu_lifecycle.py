@@ -73,3 +73,66 @@ def test_info_after_new_regions(torch_cuda, n_reg):
     assert db.info() == before and ws.info() == before
     ws.close()
     db.close()
+
+
+def _line_db(precision, R, rows, d, seed=5):
+    feats, xy = _feats(R * rows, d, seed)
+    mirrors = {"fp32": 0, "bf16": hloc.MIRROR_BF16, "fp8": hloc.MIRROR_FP8}[precision]
+    db = hloc.HlocDB(feats, xy, mirrors=mirrors)
+    db.set_regions(np.repeat(np.arange(R), rows).astype(np.int32), R)
+    rng = np.random.default_rng(seed + 1)
+    q = feats[rng.integers(0, len(feats), 2048)]
+    return db, (q + 0.1 * rng.standard_normal(q.shape)).astype(np.float32)
+
+
+@pytest.mark.parametrize("precision,captured,R,n_reg,first,later", [
+    # 64 frames have dense coarse words; a handful takes the key lists
+    ("bf16", "bf16", 200, 5, 64, (1, 5)),
+    ("fp8", "fp8", 200, 5, 64, (1, 5)),
+    # 2,048 frames have an item list; 1,900 the frame lists of the direct
+    # screen, which take more behind fewer words
+    ("fp32", "fp32", 512, 60, 2048, (1900, 17)),
+    # an fp32 batch of an fp8 database leaves room for one vector per frame
+    ("fp8", "fp32", 200, 5, 300, (300, 2)),
+])
+def test_smaller_batch_keeps_the_captured_graph(torch_cuda, precision, captured, R, n_reg, first,
+                                                later):
+    db, q = _line_db(precision, R, 100, 64)
+    qd = torch_cuda.from_numpy(q).cuda()
+    s = torch_cuda.cuda.current_stream()
+    ws = hloc.Workspace(db)
+    out = ws.outputs(first, first, 8, "cuda")
+    ws.capture(qd[:first], 8, n_reg, None, out, captured)
+    for nq in later:
+        say(f"[case] {precision}, R {R}: {first} frames captured, then {nq}")
+        part = ws.outputs(nq, nq, 8, "cuda")
+        ws.query_async(qd[:nq], 8, n_reg, None, part, s, precision)
+        ref = db.query(qd[:nq], 8, n_reg, precision=precision)
+        for key in part:
+            assert torch_cuda.equal(part[key], ref[key]), (nq, key)
+        for v in out.values():
+            v.zero_()
+        ws.replay(s)  # raises if a buffer grew and the graph was dropped
+        ref = db.query(qd[:first], 8, n_reg, precision=captured)
+        torch_cuda.cuda.synchronize()
+        for key in out:
+            assert torch_cuda.equal(out[key], ref[key]), (nq, key)
+    ws.close()
+    db.close()
+
+
+@pytest.mark.parametrize("precision", ["bf16", "fp8"])
+def test_server_slot_takes_small_batches(torch_cuda, precision):
+    # a slot sized for 64 frames x 200 regions (dense coarse words) has no key
+    # lists for requests of 1 to 5 frames: they take words too, and give the
+    # direct call's results
+    db, q = _line_db(precision, 200, 100, 64)
+    srv = hloc.Server(db, 8, 5, precision, max_batch_frames=64, max_slots=2)
+    for f in (64, 1, 3, 5, 64):
+        say(f"[case] {precision} request of {f}")
+        got = srv.wait(srv.submit(q[:f]), f)
+        ref = db.query(q[:f], 8, 5, np.array([0, f], np.int32), precision)
+        assert (got["idx"] == ref["idx"]).all() and (got["dist"] == ref["dist"]).all()
+        assert (got["xy"] == ref["xy"][0]).all() and got["flags"] == ref["flags"][0]
+    srv.close()
+    db.close()
