@@ -885,6 +885,10 @@ size_t wide_lp_lds_bytes() {
 constexpr size_t wide_rs_lds_bytes(int pieces) {
   return (size_t)2 * kGroup * 4 * pieces * sizeof(v4u);
 }
+// static LDS of the register-row kernels: the item's frames (entry, norm,
+// scale of each) and two item numbers, padded to 16 bytes
+constexpr size_t kRsStaticLds = kListFrames * (sizeof(int2) + 2 * sizeof(float)) + 16;
+constexpr size_t kDefaultLds = 64 * 1024;
 constexpr int kRsBlocksPerCu = 2;  // blocks per compute unit if the occupancy query fails
 
 // Pieces per lane for a padded length: bf16 rows take dp / 32, fp8 rows
@@ -1024,14 +1028,35 @@ hipError_t launch_screen_wide_lp(int32_t fmt, const ScreenArgs &a, int32_t grid,
   return hipErrorInvalidValue;
 }
 
+// The register-row kernel's limit, where its static LDS and its frame buffers
+// pass the default (fp8 frames of 768 padded values as two vectors: 65,552 B).
+template <int FMT, int NS, int TERMS>
+hipError_t set_rs_lds() {
+  constexpr size_t lds = wide_rs_lds_bytes(TERMS * NS);
+  static_assert(lds + kRsStaticLds <= kLdsPerCu / kRsBlocksPerCu, "two blocks per compute unit");
+  if (lds + kRsStaticLds <= kDefaultLds) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_screen_wide_rs<FMT, NS, TERMS>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+template <int FMT, int NS>
+hipError_t set_wide_lds() {
+  if constexpr (NS % 4 == 0) {
+    hipError_t e = set_rs_lds<FMT, NS, 1>();
+    if constexpr (FMT == HLOC_FP8 && 64 * NS <= kFp8TermsDim)
+      if (e == hipSuccess) e = set_rs_lds<FMT, NS, 2>();
+    if (e != hipSuccess) return e;
+  }
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_screen_wide_lp<FMT, NS>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)wide_lp_lds_bytes<NS>());
+}
+
 // LDS limits of the wide kernels (above the 64 KB default).
 hipError_t prepare_screen_lp_kernels() {
-#define HLOC_LP_ATTR(F, N)                                                                 \
-  {                                                                                        \
-    const hipError_t e = hipFuncSetAttribute(                                              \
-        reinterpret_cast<const void *>(&k_screen_wide_lp<F, N>),                           \
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)wide_lp_lds_bytes<N>());          \
-    if (e != hipSuccess) return e;                                                         \
+#define HLOC_LP_ATTR(F, N)                   \
+  {                                          \
+    const hipError_t e = set_wide_lds<F, N>(); \
+    if (e != hipSuccess) return e;           \
   }
 #define HLOC_LP_ATTRS(F) \
   HLOC_LP_ATTR(F, 1)     \
@@ -1046,8 +1071,6 @@ hipError_t prepare_screen_lp_kernels() {
   HLOC_LP_ATTR(F, 16)
   HLOC_LP_ATTRS(HLOC_BF16)
   HLOC_LP_ATTRS(HLOC_FP8)
-  // (the register-row kernels stay below it)
-  static_assert(wide_rs_lds_bytes(2 * kFp8TermsDim / 64) <= 64 * 1024, "frame buffers");
 #undef HLOC_LP_ATTRS
 #undef HLOC_LP_ATTR
   return hipSuccess;
