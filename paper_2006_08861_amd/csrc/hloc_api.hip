@@ -328,8 +328,10 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
   // low-precision screens: the frames rounded the same way as the rows
   const int fmt = p.precision == HLOC_FP32 ? 0 : p.precision;
   const LpMirror *lpm = fmt ? &db->lp[fmt] : nullptr;
-  // the coarse screen of fp8 queries runs on bf16 copies when there are any
-  const bool coarse_bf16 = fmt == HLOC_FP8 && db->lp[HLOC_BF16].reps;
+  // the coarse screen of fp8 queries runs on bf16 copies when there are any and
+  // a bf16 kernel takes this length (the fp8 ones take rows twice as long)
+  const bool coarse_bf16 = fmt == HLOC_FP8 && db->lp[HLOC_BF16].reps &&
+                           lp_screen_supports(HLOC_BF16, db->dp);
   const int cfmt = coarse_bf16 ? HLOC_BF16 : fmt;
   const LpMirror *cpm = cfmt ? &db->lp[cfmt] : nullptr;
   void *c_lp = coarse_bf16 ? ws->c_lp.p : ws->q_lp.p;

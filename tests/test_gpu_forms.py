@@ -23,13 +23,16 @@ def torch_cuda():
     return torch
 
 
-@pytest.mark.parametrize("d,n_reg", [(640, 9), (740, 9), (768, 9), (1000, 9), (1024, 9)])
+@pytest.mark.parametrize("d,n_reg", [(640, 9), (740, 9), (768, 9), (1000, 9), (1024, 9),
+                                     (640, 3), (768, 3), (1000, 3)])
 def test_fp8_long_rows_in_wide_items(torch_cuda, d, n_reg):
     # fp8 frames as two vectors (up to 768 padded values, where the register-row
     # kernel takes more than 64 KB of LDS) and as one (above), past the direct
     # screen's work: regions kept by every frame, in chunks with remainders,
-    # give wide items; the same bits as the fp32 screens, and the first 40
-    # frames match the oracle
+    # give wide items; with three regions kept, the coarse screen has no bf16
+    # kernel of this length and runs on fp8 copies too, for many frames and for
+    # 20; the same bits as the fp32 screens, and the first 40 frames match the
+    # oracle
     rng = np.random.default_rng(41)
     sizes = np.array([333, 129, 64, 40, 1, 40, 15, 40, 17])
     region_of = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
@@ -51,6 +54,9 @@ def test_fp8_long_rows_in_wide_items(torch_cuda, d, n_reg):
     assert info["items"] > info["narrow_items"]
     for key in outs["fp8"]:
         assert torch_cuda.equal(outs["fp8"][key], outs["fp32"][key]), key
+    few = db.query(qd[:20], 9, n_reg, precision="fp8")
+    for key in few:
+        assert torch_cuda.equal(few[key], outs["fp32"][key][:20]), key
     db.close()
     ora = oracle.localize(feats, xy, region_of, R, q[:40], np.arange(41), 9, n_reg,
                           (0.5, 1, 0.0, 0))
