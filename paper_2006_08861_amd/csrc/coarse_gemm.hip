@@ -39,7 +39,7 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));  // 16-byte piece (nat
 
 constexpr int kCgWaves = 4;
 constexpr int kCgFramesPerWave = 2 * kGroup;              // two MFMA column groups
-constexpr int kCgFrames = kCgWaves * kCgFramesPerWave;    // frames per block
+static_assert(kCgFrames == kCgWaves * kCgFramesPerWave, "frames per block");
 constexpr int kCgTile = 32;                               // representatives per LDS tile
 
 // One bf16 representative piece (8 values) against a frame piece.

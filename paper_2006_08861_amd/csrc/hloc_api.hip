@@ -91,6 +91,35 @@ void dev_free(T *&p) {
 }
 
 
+// Batches of nq frames on low-precision screens take the key lists.
+bool takes_keys(const hloc_db *db, int64_t nq) {
+  return db->lp[HLOC_BF16].reps && coarse_gemm_supports(db->dp) && db->R < (1 << 28) &&
+         (nq * db->R > kKeyWords || nq * db->R <= kKeyFew);
+}
+
+// Ranges of the representatives of the fused coarse product, *reps each.
+int32_t key_splits(const hloc_db *db, int32_t nq, int32_t *reps) {
+  const int32_t sp = coarse_gemm_splits(std::max(nq, 1), db->R, db->num_cu);
+  *reps = ((db->R + sp - 1) / sp + 31) / 32 * 32;  // whole tiles of 32
+  return (db->R + *reps - 1) / *reps;              // no empty range
+}
+
+// Most (frame, split) key lists of a batch of up to nq frames: the splits fall
+// from one tile of kCgFrames frames to the next, so the last frame of each tile
+// counts, and from two tiles per compute unit on there is one split.
+int64_t most_key_lists(const hloc_db *db, int32_t nq) {
+  int64_t most = 0;
+  int32_t reps;
+  auto look = [&](int64_t f) {
+    f = std::min<int64_t>(f, nq);
+    if (f > 0 && takes_keys(db, f)) most = std::max(most, f * key_splits(db, (int32_t)f, &reps));
+  };
+  look(kKeyFew / db->R);
+  look(nq);
+  for (int64_t t = 1; t <= 2 * db->num_cu && (t - 1) * kCgFrames < nq; ++t) look(t * kCgFrames);
+  return most;
+}
+
 int make_plan(const hloc_db *db, int32_t nq, int32_t k, int32_t n_regions, int32_t nreq,
               int32_t precision, Plan *pl) {
   if (!db->has_regions) return fail(HLOC_ESTATE, "hloc_set_regions has not been called");
@@ -127,15 +156,8 @@ int make_plan(const hloc_db *db, int32_t nq, int32_t k, int32_t n_regions, int32
                   kMaxSurvivors);  // 3k behind the bf16 and fp8 screens
   // bf16 coarse screens (bf16 queries, and fp8 queries when the database
   // keeps bf16 representatives) on a length the fused product supports
-  p.coarse_keys = !p.exhaustive && precision != HLOC_FP32 && db->lp[HLOC_BF16].reps &&
-                  coarse_gemm_supports(db->dp) && db->R < (1 << 28) &&
-                  ((int64_t)nq * db->R > kKeyWords || (int64_t)nq * db->R <= kKeyFew);
-  if (p.coarse_keys) {
-    const int32_t sp = coarse_gemm_splits(std::max(nq, 1), db->R, db->num_cu);
-    p.creps = (db->R + sp - 1) / sp;
-    p.creps = (p.creps + 31) / 32 * 32;           // whole tiles of 32
-    p.csplits = (db->R + p.creps - 1) / p.creps;  // no empty range
-  }
+  p.coarse_keys = !p.exhaustive && precision != HLOC_FP32 && takes_keys(db, nq);
+  if (p.coarse_keys) p.csplits = key_splits(db, nq, &p.creps);
   p.terms = lp_terms(precision, db->dp);
   p.cap2 = p.exhaustive ? db->n_blocks : db->h_desc_blocks[p.nr];
   const int32_t crow = std::min(db->tile_rows, kWideRows);  // the shorter chunks bound the items
@@ -197,20 +219,24 @@ int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *byte
   const int64_t nq = std::max(p.nq, 1), nr = std::max(p.nr, 1);
   CHK(fit(ws->qp, (size_t)nq * db->dp * sizeof(float)));
   CHK(fit(ws->qn2, (size_t)nq * sizeof(float)));
-  if (p.coarse_keys) {
-    const int64_t lists = nq * p.csplits;
+  const int64_t lists = p.reserve ? most_key_lists(db, p.nq) : p.coarse_keys ? nq * p.csplits : 0;
+  if (lists > 0) {
     CHK(fit(ws->ckeys, key_bytes(lists)));
     CHK(fit(ws->cslots, key_slot_bytes(lists)));
     CHK(fit(ws->cbounds, key_bound_bytes(lists)));
     CHK(fit(ws->cdefer, (size_t)nq * sizeof(int32_t)));
   }
-  if (!p.exhaustive) {
-    size_t need = p.direct ? coarse_list_bytes(nq, db->R) : (size_t)nq * db->R * sizeof(uint32_t);
+  // a reservation for every region holds for calls with fewer (at most
+  // kMaxSurvivors of them) too: their coarse words and region slots
+  const bool coarse = !p.exhaustive || (p.reserve && db->R_nonempty > 1);
+  if (coarse) {
+    size_t need = p.direct ? coarse_list_bytes(nq, db->R) : coarse_word_bytes(nq, db->R);
     if (p.reserve)
       need = std::max(need, coarse_list_bytes(std::min<int64_t>(nq, kDirectSlots / db->R), db->R));
     CHK(fit(ws->cand1, need));
   }
-  const int64_t kept = p.exhaustive ? 1 : nq * nr;  // (the exhaustive search lists no regions)
+  // (the exhaustive search lists no regions)
+  const int64_t kept = coarse ? nq * std::min<int64_t>(nr, kMaxSurvivors) : 1;
   CHK(fit(ws->regions, (size_t)kept * sizeof(int32_t)));
   CHK(fit(ws->rcount, (size_t)db->R * sizeof(int32_t)));
   CHK(fit(ws->vord, (size_t)db->R * sizeof(int32_t)));
@@ -223,7 +249,7 @@ int ensure_workspace(hloc_ws *ws, const Plan &p, bool agg_internal, size_t *byte
   CHK(fit(ws->n_rows, (size_t)nq * sizeof(int32_t)));
   CHK(fit(ws->fstat, (size_t)nq * sizeof(int4)));
   CHK(fit(ws->misc, kMiscInts * sizeof(int32_t)));
-  CHK(fit(ws->rq, (size_t)(p.exhaustive ? nq : nq * nr) * sizeof(int2)));
+  CHK(fit(ws->rq, (size_t)std::max(nq, kept) * sizeof(int2)));
   CHK(fit(ws->items, (size_t)std::max<int64_t>(p.items_bound, 1) * sizeof(Item)));
   CHK(fit(ws->cand2, (size_t)nq * std::max<int64_t>(p.cap2, 1) * sizeof(uint32_t)));
   if (db->lp[HLOC_BF16].rows || db->lp[HLOC_FP8].rows) {

@@ -369,6 +369,7 @@ hipError_t launch_sched(const int32_t *regions, int32_t nq, int32_t nr, int32_t 
 // (frame, split of the representatives, lane group), the kCgKeep best quads
 // (four consecutive representatives, ranked by their smallest screen word)
 // instead of storing every word.
+constexpr int kCgFrames = 128;                 // frames per block
 constexpr int kCgKeep = 6;                     // quads kept per (frame, split, lane group)
 constexpr int kCgKeys = 4 * kCgKeep * 4;       // keys per (frame, split): 4 lane groups x quads x 4
 struct CoarseGemmArgs {

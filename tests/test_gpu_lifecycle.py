@@ -136,3 +136,33 @@ def test_server_slot_takes_small_batches(torch_cuda, precision):
         assert (got["xy"] == ref["xy"][0]).all() and got["flags"] == ref["flags"][0]
     srv.close()
     db.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "fp8"])
+def test_reserve_covers_smaller_calls(torch_cuda, precision):
+    # reserved for 2,048 frames and every region: within that, calls with fewer
+    # regions (dense coarse words, or key lists at full size: 2,048 x 6,400
+    # words), fewer frames (frame lists of the direct screen; a handful) and
+    # every region allocate nothing (each of these forms takes megabytes that
+    # were missing), and give the results of a workspace sized by each call
+    R = 6400
+    db, q = _line_db(precision, R, 2, 64)
+    qd = torch_cuda.from_numpy(q).cuda()
+    s = torch_cuda.cuda.current_stream()
+    calls = [(2048, 8), (2048, 64), (600, 8), (300, 60), (1, 8), (40, R)]
+    refs = [db.query(qd[:nq], 8, nr, precision=precision) for nq, nr in calls]
+    ws = hloc.Workspace(db)
+    outs = [ws.outputs(nq, nq, 8, "cuda") for nq, _ in calls]
+    torch_cuda.cuda.synchronize()
+    ws.reserve(2048, 2048, 8, R)
+    free = torch_cuda.cuda.mem_get_info()[0]
+    for (nq, nr), out in zip(calls, outs):
+        ws.query_async(qd[:nq], 8, nr, None, out, s, precision)
+        say(f"[case] {precision} {nq} frames, {nr} regions: "
+            f"free {torch_cuda.cuda.mem_get_info()[0] - free:+d}")
+        assert torch_cuda.cuda.mem_get_info()[0] == free, (nq, nr)
+    for ref, out in zip(refs, outs):
+        for key in out:
+            assert torch_cuda.equal(out[key], ref[key]), key
+    ws.close()
+    db.close()
