@@ -21,7 +21,11 @@ using namespace hloc;
 // the process ends. On the host the name is only a stand-in, not a device
 // address: host code uses the per-device address from hipGetSymbolAddress
 // (static_scratch below), never the name.
-static __device__ __align__(256) unsigned char scratch[HLOC_STATIC_SCRATCH_BYTES];
+// Behind it lies room for the wide screen's item counters, which are not counted
+// as a batch's scratch memory: they came later than batches that fill the array.
+constexpr size_t kStaticCounterBytes = 8 * kItemCtrStride * sizeof(int32_t);
+static __device__ __align__(256) unsigned char scratch[HLOC_STATIC_SCRATCH_BYTES +
+                                                       kStaticCounterBytes];
 
 namespace hloc {
 thread_local PhaseEvents *g_phase = nullptr;
@@ -1356,17 +1360,18 @@ int hloc_query_batch_static_async(hloc_db *db, const float *q, int32_t nq, int32
   CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
   // the schedule's item list takes less than the direct screen's frame lists,
   // one fp8 vector per frame less than two
-  if (used > (size_t)HLOC_STATIC_SCRATCH_BYTES && (p.direct || p.terms == 2)) {
+  const size_t limit = (size_t)HLOC_STATIC_SCRATCH_BYTES + kStaticCounterBytes;
+  if (used > limit && (p.direct || p.terms == 2)) {
     p.direct = false;
     p.terms = 1;
     used = 0;
     CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
   }
-  if (used > (size_t)HLOC_STATIC_SCRATCH_BYTES)
+  if (used > limit)
     return fail(HLOC_EINVAL,
                 "the batch needs %zu bytes of scratch memory, above the %zu bytes of the static "
                 "array (send fewer frames)",
-                used, (size_t)HLOC_STATIC_SCRATCH_BYTES);
+                used - kStaticCounterBytes, (size_t)HLOC_STATIC_SCRATCH_BYTES);
   return enqueue_query(&ws, p, q, req_offsets, nullptr, idx, dist, xy, tile, flags,
                        reinterpret_cast<hipStream_t>(stream));
 }

@@ -166,3 +166,20 @@ def test_reserve_covers_smaller_calls(torch_cuda, precision):
             assert torch_cuda.equal(out[key], ref[key]), key
     ws.close()
     db.close()
+
+
+def test_static_batch_that_fills_the_array(torch_cuda):
+    # 188,166 frames of 32 values against 40 regions of 40 rows, one searched:
+    # 67,108,864 bytes of scratch memory without the wide screen's item counters
+    db, q = _line_db("fp32", 40, 40, 32)
+    rng = np.random.default_rng(8)
+    q = np.tile(q, (92, 1))[:188_166]
+    q += 0.01 * rng.standard_normal(q.shape, dtype=np.float32)
+    qd = torch_cuda.from_numpy(q).cuda()
+    say(f"[case] static batch of {len(q)} frames")
+    out = db.query_static(qd, 8, 1)
+    ref = db.query(qd, 8, 1)
+    torch_cuda.cuda.synchronize()
+    for key in out:
+        assert torch_cuda.equal(out[key], ref[key]), key
+    db.close()
