@@ -42,6 +42,7 @@ constexpr int kGroup = 16;          // frames per MFMA column block of the scree
 constexpr int kLdsPerCu = 160 * 1024;  // LDS of one compute unit (gfx950)
 constexpr int kItemFrames = 256;    // frames per dense work item of the wide kernels at most
 constexpr int kFrameL = 64;         // survivor positions of the select's frame kernel, one per lane
+constexpr int kFrameBlocks = 16;    // survivor blocks of it (fine stage): eight waves of them
 constexpr int kListFrames = 1024;   // frames per wide list item (rows re-read once per this many)
 constexpr int kWideRows = 64;       // rows per wide work item (the LDS stage of the wide kernels)
 constexpr int kWideRowsRs = 128;    // rows per run of the register-row kernels (bf16, fp8)

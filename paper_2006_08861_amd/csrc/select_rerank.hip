@@ -1,7 +1,7 @@
 // Top candidates per frame ("select top candidates", Algorithm 1), in one
 // kernel: k_select_frame (W waves per frame) for lists that fit a wave's
 // lanes, k_select_rerank (one block per frame) past them (more than 64 region
-// slots or survivor positions). Both do the same three things; the block
+// slots or survivor rows, or 16 survivor blocks). Both do the same three things; the block
 // kernel's way:
 //   1. select: the L + 1 smallest (screen word, position) pairs, the word
 //      being the float bits of the screen distance (the bits of a
@@ -1065,9 +1065,9 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // ------------------------------------------------------------ frame kernel
-// The common case of the selection (up to kFrameL survivor positions, up to
-// kFrameSlots region slots), W waves per frame, with no word cache and few
-// barriers:
+// The common case of the selection (up to kFrameL survivor rows or kFrameBlocks
+// survivor blocks, up to kFrameSlots region slots), W waves per frame, with no
+// word cache and few barriers:
 //   * every lane keeps the two smallest words of the positions it reads (the
 //     first kFrameRegs of them stay in registers for the band pass, the rest
 //     are read again); the survivors are the L smallest of those, taken out
@@ -1528,6 +1528,26 @@ int frame_waves(const SelRerankArgs &a) {
   return W;
 }
 
+// Fine stage: survivor blocks that are ranked faster in the frame kernel, by
+// counting, all rows against all, than by the block kernel's sort. From 17 on
+// eight waves' lists no longer fit either. Whole calls on 200k x 512 bf16 rows,
+// 1 / 256 / 2,048 / 8,192 frames, frame kernel and block kernel: 15 blocks (k =
+// 80) 61, 98, 298, 792 and 70, 112, 317, 777 us; 19 (k = 100) 87, 133, 369, 966
+// and 77, 122, 371, 1023; 48 (k = 256) 323, 409, 884, 2479 and 107, 170, 630,
+// 1975. Between 17 and 32 the frame kernel stays
+//   - with up to 20 for batches that fill the chip (4,096 frames and more);
+//   - where the block kernel's word cache leaves it alone on a compute unit and
+//     there are two rounds of frames: all 200k x 64 bf16 rows searched, k = 100,
+//     256 / 1,024 frames 98, 254 and 77, 320;
+//   - behind the fp32 screen (17 blocks, k > 240) on lists of more than 256
+//     blocks, whose bands are long: 60 regions (780 blocks) of 200k x 64 rows, k =
+//     256, 256 frames 731 and 910, but 8 regions (104 blocks) 250 and 190.
+bool few_blocks(const SelRerankArgs &a) {
+  if (a.L <= kFrameBlocks || a.L > 2 * kFrameBlocks) return a.L <= kFrameBlocks;
+  return (a.nq >= 4096 && a.L <= 20) ||
+         (a.cap > kBigFrame ? a.nq >= 512 : !a.q_err && a.cap > 256);
+}
+
 template <int MODE>
 hipError_t launch_frame(const SelRerankArgs &a, hipStream_t s) {
   const int W = frame_waves(a);
@@ -1564,7 +1584,7 @@ hipError_t launch_select_rerank(SelRerankArgs a, hipStream_t s) {
     a.cache = (int32_t)std::min<int64_t>(a.cap, kWordCache);
   }
   // the frame kernel, unless its lists do not hold the survivors or the slots
-  if (a.L <= kFrameL && a.m >= 1 && a.nslots <= kFrameSlots) {
+  if (a.L <= kFrameL && a.m >= 1 && a.nslots <= kFrameSlots && (!a.blocks || few_blocks(a))) {
     if (a.blocks) return launch_frame<kFineBlocks>(a, s);
     return a.keys ? launch_frame<kCoarseKeys>(a, s) : launch_frame<kCoarseWords>(a, s);
   }

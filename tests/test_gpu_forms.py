@@ -63,3 +63,38 @@ def test_fp8_long_rows_in_wide_items(torch_cuda, d, n_reg):
     idx, dist = (outs["fp8"][key][:40].cpu().numpy() for key in ("idx", "dist"))
     st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:40], 9)
     assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("rows,precision,k,n_reg", [
+    (60, "fp32", 240, 28), (60, "fp32", 241, 28), (60, "fp32", 256, 60), (60, "bf16", 85, 28),
+    (60, "bf16", 86, 28), (60, "fp8", 85, 28), (60, "fp8", 107, 28), (60, "fp8", 171, 28),
+    (600, "bf16", 86, 130), (600, "fp32", 256, 130)])
+def test_selection_past_sixteen_survivor_blocks(torch_cuda, rows, precision, k, n_reg):
+    # up to 16 survivor blocks (frame kernel), 17 to 32 (either, by the frames
+    # and the length of their lists: about 10 blocks a region, and every one of
+    # 5,000) and 33 (block kernel), in batches of 1, 300, 520 and 4,100 frames:
+    # bitwise the fp32 screens' results of one batch, and 12 frames against the
+    # oracle
+    rng = np.random.default_rng(42)
+    sizes = rng.integers(1, 2 * rows, 130)
+    region_of = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    n, d, R = len(region_of), 64, len(sizes)
+    feats = rng.standard_normal((n, d)).astype(np.float32)
+    xy = rng.uniform(0, 40, size=(n, 2))
+    most = 4100 if rows == 60 else 520
+    q = feats[rng.integers(0, n, most)] + 0.2 * rng.standard_normal((most, d), dtype=np.float32)
+    say(f"[case] k={k} {precision}, {n_reg} of {R} regions, {n} rows")
+    db = hloc.HlocDB(feats, xy, mirrors=hloc.MIRROR_BF16 | hloc.MIRROR_FP8)
+    db.set_regions(region_of, R)
+    qd = torch_cuda.from_numpy(q).cuda()
+    ref = db.query(qd, k, n_reg)
+    for nq in (1, 300, 520, 4100):
+        got = db.query(qd[:nq], k, n_reg, precision=precision)
+        for key in got:
+            assert torch_cuda.equal(got[key], ref[key][:nq]), (nq, key)
+    db.close()
+    ora = oracle.localize(feats, xy, region_of, R, q[:12], np.arange(13), k, n_reg,
+                          (0.5, 1, 0.0, 0))
+    idx, dist = (ref[key][:12].cpu().numpy() for key in ("idx", "dist"))
+    st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:12], k)
+    assert st["recall"] == 1.0
