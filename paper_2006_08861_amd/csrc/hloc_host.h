@@ -168,6 +168,7 @@ struct hloc_db {
   std::vector<int64_t> h_desc_prefix;  // sum of the j largest region sizes, j = 0..R
   std::vector<int64_t> h_desc_blocks;  // sum of the j largest regions' 16-row block counts
   int64_t n_blocks = 0;                // 16-row blocks over all regions
+  double blk_mean = hloc::kBlockRows, blk_dev = 0.0;  // rows of a block: mean, standard deviation
   int4 *blk_tab = nullptr;             // per block, regions in id order: first row, rows, region,
                                        // block of the region
   int64_t chunks_fine = 0;             // sum over regions of ceil(size / min(tile_rows, 64))

@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from parity import judge_frames
-from paper_2006_08861_amd import hloc
+from paper_2006_08861_amd import hloc, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -94,6 +94,37 @@ def test_selection_past_sixteen_survivor_blocks(torch_cuda, rows, precision, k, 
             assert torch_cuda.equal(got[key], ref[key][:nq]), (nq, key)
     db.close()
     ora = oracle.localize(feats, xy, region_of, R, q[:12], np.arange(13), k, n_reg,
+                          (0.5, 1, 0.0, 0))
+    idx, dist = (ref[key][:12].cpu().numpy() for key in ("idx", "dist"))
+    st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:12], k)
+    assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("precision,k", [("fp32", 10), ("fp32", 50), ("bf16", 10), ("fp8", 10)])
+def test_survivors_of_short_blocks(torch_cuda, precision, k):
+    # regions of 20 rows (blocks of 16 and of 4), every row searched: the
+    # survivor blocks nearly always hold k rows, so few frames re-score their
+    # whole list of 2,000 blocks (a frame in forty of them would be 800 row
+    # slots a frame; with ceil((k + 16) / 16) survivors it is a frame in four);
+    # bitwise the fp32 screens' results, and 12 frames against the oracle
+    rng = np.random.default_rng(43)
+    n, d, R, nq = 20_000, 64, 1000, 600
+    feats = workload.walk_features(n, d, rng)
+    xy = workload.corridor_xy(n)
+    region_of = np.repeat(np.arange(R), n // R).astype(np.int32)
+    q = (feats[rng.integers(0, n, nq)] + 0.03 * rng.standard_normal((nq, d))).astype(np.float32)
+    db = hloc.HlocDB(feats, xy, mirrors=hloc.MIRROR_BF16 | hloc.MIRROR_FP8)
+    db.set_regions(region_of, R)
+    qd = torch_cuda.from_numpy(q).cuda()
+    ref = db.query(qd, k, R)
+    got = db.query(qd, k, R, precision=precision)
+    info = db.info()
+    say(f"[case] {precision} k={k}: {info}")
+    for key in got:
+        assert torch_cuda.equal(got[key], ref[key]), key
+    assert info["rerank_rows"] <= 2000 * nq
+    db.close()
+    ora = oracle.localize(feats, xy, region_of, R, q[:12], np.arange(13), k, R,
                           (0.5, 1, 0.0, 0))
     idx, dist = (ref[key][:12].cpu().numpy() for key in ("idx", "dist"))
     st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:12], k)
