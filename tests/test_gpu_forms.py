@@ -129,3 +129,67 @@ def test_survivors_of_short_blocks(torch_cuda, precision, k):
     idx, dist = (ref[key][:12].cpu().numpy() for key in ("idx", "dist"))
     st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:12], k)
     assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("precision", ["bf16", "fp8"])
+@pytest.mark.parametrize("labels", [0, 3])
+def test_key_lists_and_words_agree(torch_cuda, precision, labels):
+    # more than 12 M frame x representative words take the fused coarse product
+    # (1,601 frames x 8,192 regions; 600 frames under 3 labels, whose regions it
+    # masks: last tiles of 65 and 8 of 128 frames, several splits), batches of
+    # 100 frames dense words: the same bits, also as the fp32 screens. 120
+    # regions hold the same rows, so the keys cannot decide the frames near them
+    # (every tenth) and those take the words. 12 frames against the oracle.
+    rng = np.random.default_rng(44)
+    R, rows, d, k, n_reg, nq = 8192, 2, 64, 6, 3, 600 if labels else 1601
+    feats = rng.standard_normal((R * rows, d)).astype(np.float32)
+    feats[:120 * rows] = np.tile(feats[:rows], (120, 1))
+    region_of = np.repeat(np.arange(R), rows).astype(np.int32)
+    xy = rng.uniform(0, 40, size=(len(feats), 2))
+    src = rng.integers(120 * rows, len(feats), nq)
+    src[::10] = 0
+    q = (feats[src] + 0.05 * rng.standard_normal((nq, d))).astype(np.float32)
+    of = (np.arange(R) * 3 // R).astype(np.int32)
+    db = hloc.HlocDB(feats, xy, mirrors=hloc.MIRROR_BF16 | hloc.MIRROR_FP8)
+    db.set_regions(region_of, R)
+    if labels:
+        db.set_region_labels(of, labels)
+
+    def run(frames, prec):
+        fd = torch_cuda.from_numpy(frames).cuda()
+        if labels:
+            offs = torch_cuda.arange(len(frames) + 1, dtype=torch_cuda.int32, device="cuda")
+            out = db.query_labels(fd, k, n_reg, labels, offs, precision=prec)
+        else:
+            out = db.query(fd, k, n_reg, precision=prec)
+        return {key: v.cpu() for key, v in out.items()}, db.info()
+
+    say(f"[case] {precision}, {nq} frames, {labels} labels")
+    full, info = run(q, precision)
+    say(f"[ok] {info}")
+    assert info["coarse_deferred"] >= len(src[::10])
+    fp32, _ = run(q, "fp32")
+    for key in full:
+        assert torch_cuda.equal(full[key], fp32[key]), key
+    for a in range(0, nq, 100):
+        part, info = run(q[a:a + 100], precision)
+        if len(q[a:a + 100]) == 100:
+            assert info["coarse_deferred"] == 0
+        for key in part:
+            per_label = labels and key in ("idx", "dist")
+            want = full[key][:, a:a + 100] if per_label else full[key][a:a + 100]
+            assert torch_cuda.equal(part[key], want), (a, key)
+    db.close()
+    if labels:
+        ora = oracle.localize_labels(feats, xy, region_of, R, of, q[:12], np.arange(13), k, n_reg,
+                                     (0.5, 1, 0.0, 0))
+        for p in range(labels):
+            st = judge_frames(full["idx"][p, :12].numpy(), full["dist"][p, :12].numpy(), None,
+                              ora["per_label"][p], feats, region_of, R, q[:12], k)
+            assert st["recall"] == 1.0
+    else:
+        ora = oracle.localize(feats, xy, region_of, R, q[:12], np.arange(13), k, n_reg,
+                              (0.5, 1, 0.0, 0))
+        st = judge_frames(full["idx"][:12].numpy(), full["dist"][:12].numpy(), None, ora, feats,
+                          region_of, R, q[:12], k)
+        assert st["recall"] == 1.0
