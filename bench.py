@@ -267,9 +267,11 @@ FFT_KERNEL = "k_fft_magnitude"
 
 
 def fft_kernel_name(length: int) -> str:
-    """The kernel a launch of this signal length runs (four-step for L = 128
-    and 512, radix-2 in LDS otherwise)."""
-    return {128: "k_fft_magnitude_sq<8>", 512: "k_fft_magnitude_sq<16>"}.get(length, FFT_KERNEL)
+    """What the name of the kernel of a launch of this signal length begins
+    with (four-step: k_fft_magnitude_sq<R> for L = 2 R R, k_fft_magnitude_sq2<R>
+    for L = 4 R R; k_fft_magnitude below 32)."""
+    return {32: "k_fft_magnitude_sq<4>", 128: "k_fft_magnitude_sq<8>",
+            512: "k_fft_magnitude_sq<16>", 2048: "k_fft_magnitude_sq<32>"}.get(length, FFT_KERNEL)
 
 
 def fft_digest() -> str:

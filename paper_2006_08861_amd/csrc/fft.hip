@@ -92,9 +92,10 @@ __device__ __forceinline__ void dft_regs(double2 *a) {
   }
 }
 
-// sqrt(s) / 2 rounded to float, s >= 0 (or NaN): the hardware's reciprocal
-// square root, one coupled step and one residual correction leave about a
-// double's last bits, far below the float's; the library's square root
+// sqrt(s) / 2 rounded to float, s >= 0 (or NaN), by Goldschmidt's iteration from
+// the hardware's reciprocal square root: one coupled step for sqrt(s) and
+// 1 / (2 sqrt(s)) and one residual correction leave about a double's last bits,
+// far below the float's; the library's square root is correctly rounded and
 // also rescales for arguments this one cannot meet (s is 0 or above 1e-250:
 // sums of squares of float values and their differences).
 __device__ __forceinline__ float half_sqrt(double s) {
@@ -179,9 +180,8 @@ struct FftShape {
 constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
 
 template <class S>
-__global__ __launch_bounds__(64 * S::waves) void k_fft_magnitude_4s(const float *__restrict__ x,
-                                                                    int64_t nsig, int d,
-                                                                    float *__restrict__ out) {
+__device__ __forceinline__ void fft_four_step(const float *__restrict__ x, int64_t nsig, int d,
+                                              float *__restrict__ out) {
   constexpr int R1 = S::r1, R2 = S::r2;
   constexpr int n = S::n, G = S::G, B = S::B, LD = R2 + 1;
   constexpr int L1 = log2_of(R1), L2 = log2_of(R2);
@@ -284,13 +284,32 @@ __global__ __launch_bounds__(64 * S::waves) void k_fft_magnitude_4s(const float 
   }
 }
 
+// n = R R (L = 32, 128, 512, 2048) and n = 2 R R (L = 64, 256, 1024).
+template <int R>
+using FftSq = FftShape<R, R>;
+template <int R>
+using FftSq2 = FftShape<2 * R, R>;
+template <int R>
+__global__ __launch_bounds__(64 * FftSq<R>::waves) void k_fft_magnitude_sq(
+    const float *__restrict__ x, int64_t nsig, int d, float *__restrict__ out) {
+  fft_four_step<FftSq<R>>(x, nsig, d, out);
+}
+template <int R>
+__global__ __launch_bounds__(64 * FftSq2<R>::waves) void k_fft_magnitude_sq2(
+    const float *__restrict__ x, int64_t nsig, int d, float *__restrict__ out) {
+  fft_four_step<FftSq2<R>>(x, nsig, d, out);
+}
+
 template <int R1, int R2>
 hipError_t launch_fft_4s(const float *x, int64_t nsig, int d, float *out, int cus,
                          hipStream_t s) {
   using S = FftShape<R1, R2>;
+  void (*kernel)(const float *, int64_t, int, float *);
+  if constexpr (R1 == R2) kernel = k_fft_magnitude_sq<R2>;
+  else kernel = k_fft_magnitude_sq2<R2>;
   static int per_cu = 0;
   if (per_cu == 0) {
-    const void *k = reinterpret_cast<const void *>(&k_fft_magnitude_4s<S>);
+    const void *k = reinterpret_cast<const void *>(kernel);
     int occ = 0;
     if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::lds) !=
             hipSuccess ||
@@ -306,8 +325,8 @@ hipError_t launch_fft_4s(const float *x, int64_t nsig, int d, float *out, int cu
   // at a time
   const int64_t per_block = (int64_t)S::G * S::waves;
   const int64_t grid = std::min<int64_t>((nsig + per_block - 1) / per_block, (int64_t)cus * per_cu);
-  return launch_kernel(k_fft_magnitude_4s<S>, dim3((unsigned)grid), dim3(64 * S::waves),
-                       S::lds, s, x, nsig, d, out);
+  return launch_kernel(kernel, dim3((unsigned)grid), dim3(64 * S::waves), S::lds, s, x, nsig, d,
+                       out);
 }
 
 }  // namespace hloc
