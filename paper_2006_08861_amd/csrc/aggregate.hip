@@ -368,8 +368,4 @@ hipError_t launch_aggregate_labels(const AggArgs &a, int32_t labels, int32_t per
   return launch_listed(a, FrameList{nullptr, labels * per, labels, per}, s);
 }
 
-hipError_t launch_aggregate(const AggArgs &a, hipStream_t s) {
-  return launch_aggregate_frames(a, nullptr, 0, s);
-}
-
 }  // namespace hloc

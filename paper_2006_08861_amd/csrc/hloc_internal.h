@@ -492,7 +492,6 @@ struct AggArgs {
   int32_t *big_count;  // zero on entry
   int32_t num_cu;
 };
-hipError_t launch_aggregate(const AggArgs &a, hipStream_t s);
 
 // Kernel attributes (LDS limits) for the current device; called once when a
 // database is built so that no attribute is set while a graph is captured.

@@ -199,7 +199,6 @@ constexpr int kRowBatch = 8;    // survivor rows fetched together by one wave
 constexpr int kEarlyKeys = 2048;  // keys requested before the count is known
 constexpr int kRankSort = 256;  // entries up to which sort_pairs ranks instead of merging
 constexpr int kCollectRounds = 8;  // positions per lane held in registers by the collect
-constexpr bool kPairChunks = false;  // block kernel: two 256-value chunks of fp32 rows per round trip
 
 // Sums over the wave of kRowBatch (8) values per lane at once: three halving
 // exchanges (lanes 32 apart swap half of their values, then 16, then 8 apart)
@@ -234,11 +233,9 @@ __device__ __forceinline__ double wave_sum8_f64(double (&acc)[kRowBatch]) {
 // FP64 partial sums of this lane for kRowBatch source rows: the sum of
 // (q_i - d_i)^2 over the lane's values, chunk by chunk of 256 values (4
 // consecutive per lane), in column order; wave_sum8_f64 then adds the lanes.
-// With PAIR, fp32 rows of a length that is a multiple of 512 are fetched two
-// chunks per round trip (more registers); otherwise one chunk at a time, and
-// LEAN (1024-thread blocks, at most 128 VGPRs) fetches FP64 rows in halves.
-// The sums are the same either way.
-template <bool LEAN, bool PAIR, bool F32>
+// LEAN (1024-thread blocks, at most 128 VGPRs) fetches FP64 rows in halves; the
+// sums are the same either way.
+template <bool LEAN, bool F32>
 __device__ __forceinline__ void rerank_batch(const SelRerankArgs &a, const float *qrow,
                                              const uint32_t (&row)[kRowBatch],
                                              double (&acc)[kRowBatch]) {
@@ -247,33 +244,6 @@ __device__ __forceinline__ void rerank_batch(const SelRerankArgs &a, const float
   const int tail = a.dp & 255;  // remaining values (multiple of 16)
 #pragma unroll
   for (int r = 0; r < kRowBatch; ++r) acc[r] = 0.0;
-  if (PAIR && F32 && (a.dp & 511) == 0) {
-    for (int c = 0; c < nch; c += 2) {
-      const int col0 = c * 256 + lane * 4, col1 = col0 + 256;
-      float4 y[2], v[2][kRowBatch];
-      y[0] = *reinterpret_cast<const float4 *>(qrow + col0);
-      y[1] = *reinterpret_cast<const float4 *>(qrow + col1);
-#pragma unroll
-      for (int r = 0; r < kRowBatch; ++r) {
-        const float *rp = a.src32 + (int64_t)row[r] * a.dp;
-        v[0][r] = *reinterpret_cast<const float4 *>(rp + col0);
-        v[1][r] = *reinterpret_cast<const float4 *>(rp + col1);
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const double y0 = y[h].x, y1 = y[h].y, y2 = y[h].z, y3 = y[h].w;
-#pragma unroll
-        for (int r = 0; r < kRowBatch; ++r) {
-          double t;
-          t = y0 - (double)v[h][r].x; acc[r] = fma(t, t, acc[r]);
-          t = y1 - (double)v[h][r].y; acc[r] = fma(t, t, acc[r]);
-          t = y2 - (double)v[h][r].z; acc[r] = fma(t, t, acc[r]);
-          t = y3 - (double)v[h][r].w; acc[r] = fma(t, t, acc[r]);
-        }
-      }
-    }
-    return;
-  }
   for (int c = 0; c <= nch; ++c) {
     const int col = c * 256 + lane * 4;
     if (c == nch && (tail == 0 || col >= a.dp)) break;
@@ -333,7 +303,7 @@ __device__ __forceinline__ void rerank_batch(const SelRerankArgs &a, const float
 // (kKeyNone, 0x80000000 | s), distinct and after every row. The calling
 // wave takes the batches of kRowBatch rows starting at first, step apart;
 // the tie ids are requested with the row values.
-template <bool LEAN, bool PAIR>
+template <bool LEAN>
 __device__ void rerank_rows(const SelRerankArgs &a, const float *qrow, const uint32_t *srow,
                             uint64_t *sort_hi, uint32_t *sort_lo, int s1, int first, int step) {
   const int lane = lane_id();
@@ -349,8 +319,8 @@ __device__ void rerank_rows(const SelRerankArgs &a, const float *qrow, const uin
     const uint32_t rw = (lane & 7) == 0 && sidx < s1 ? srow[sidx] : kNoRow;
     const uint32_t tie = rw != kNoRow && a.tie_of ? (uint32_t)a.tie_of[rw] : rw;
     double acc[kRowBatch];
-    if (a.src32) rerank_batch<LEAN, PAIR, true>(a, qrow, row, acc);
-    else rerank_batch<LEAN, PAIR, false>(a, qrow, row, acc);
+    if (a.src32) rerank_batch<LEAN, true>(a, qrow, row, acc);
+    else rerank_batch<LEAN, false>(a, qrow, row, acc);
     const double d = wave_sum8_f64(acc);
     if ((lane & 7) == 0 && sidx < s1) {
       if (rw == kNoRow) {
@@ -369,8 +339,8 @@ template <bool LEAN>
 __device__ void rerank_range(const SelRerankArgs &a, SelShared &sh, const float *qrow, int s0,
                              int s1) {
   const int w = wave_id(), nw = blockDim.x >> 6;
-  rerank_rows<LEAN, kPairChunks && !LEAN>(a, qrow, sh.srow, sh.sort_hi, sh.sort_lo, s1,
-                                          s0 + w * kRowBatch, nw * kRowBatch);
+  rerank_rows<LEAN>(a, qrow, sh.srow, sh.sort_hi, sh.sort_lo, s1, s0 + w * kRowBatch,
+                    nw * kRowBatch);
 }
 
 // Sorts hi / lo[0, cnt), cnt <= kWaveSort, by (hi, lo) in one wave: lane l
@@ -1326,7 +1296,7 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
         if (a.tie_of) tie = (uint32_t)a.tie_of[tie];
       }
       double acc[kRowBatch];
-      rerank_batch<false, false, kBlocks>(a, qrow, row, acc);
+      rerank_batch<false, kBlocks>(a, qrow, row, acc);
       const uint64_t d = (uint64_t)__double_as_longlong(wave_sum8_f64(acc));
       const bool keep = own && pair_less(d, tie, mh, ml);
       const uint64_t bal = __ballot(keep);
