@@ -183,3 +183,49 @@ def test_static_batch_that_fills_the_array(torch_cuda):
     for key in out:
         assert torch_cuda.equal(out[key], ref[key]), key
     db.close()
+
+
+def test_binding_inputs_on_another_stream(torch_cuda):
+    # calls on a side stream with inputs that the binding copies (strided
+    # frames, int64 offsets and lists) while the current stream is busy: the
+    # copies belong to the side stream, so they are made before its kernels
+    # read them and not reused under them; outputs likewise
+    torch = torch_cuda
+    db, q = _line_db("fp32", 64, 100, 64)
+    db.set_region_labels((np.arange(64) % 2).astype(np.int32), 2)
+    wide = torch.from_numpy(np.repeat(q[:256], 2, axis=1)).cuda()
+    sig = torch.randn(64, 512, device="cuda")
+    frames, strided, sig2 = wide[:, ::2], wide[:, ::2].contiguous(), sig.t().contiguous().t()
+    offs = torch.arange(0, 257, 8, device="cuda")
+    lists = torch.arange(256, device="cuda")
+    st = [hloc.Streams(db, 256, 3, 8, 256) for _ in range(4)]
+    one = torch.arange(257, device="cuda")
+
+    def calls(f, sg, i, **kw):
+        return [db.query(f, 8, 5, offs, **kw), db.query_static(f, 8, 5, offs, **kw),
+                db.query_labels(f, 8, 5, 2, offs, **kw),
+                db.query_windows(f, 8, 5, offs, lists, **kw),
+                st[i].query(f, one, one[:256], 5, **kw),
+                {"out": hloc.fft_features(sg, 200, **kw)}]
+
+    ref = calls(strided, sig, 0)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    calls(frames, sig2, 1, stream=side)  # (memory of the side stream)
+    torch.cuda.synchronize()
+    # copies made earlier hold other values by now
+    calls(frames.flip(1).t().contiguous().t(), -2 * sig2, 2)
+    a = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(100):
+        a = (a @ a).clamp_(-1, 1)
+    say("[case] six calls on a side stream beside a busy current stream")
+    got = calls(frames, sig2, 3, stream=side)
+    side.synchronize()
+    say(f"[ok] current stream still busy after them: {not torch.cuda.current_stream().query()}")
+    for r, g in zip(ref, got):
+        for key in r:
+            assert np.array_equal(g[key].cpu().numpy(), r[key].cpu().numpy(), equal_nan=True), key
+    for s in st:
+        s.close()
+    db.close()
