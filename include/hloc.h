@@ -173,7 +173,7 @@ int hloc_query_batch_async(hloc_db *db, const float *q, int32_t nq, int32_t k, i
  * ends; only the caller's inputs and outputs are passed in.
  * Errors as hloc_query_batch_async, plus EINVAL when the batch's scratch
  * memory would exceed HLOC_STATIC_SCRATCH_BYTES (the message gives the size
- * needed; e.g. 256 frames against 1,024 regions need about 2 MB) and EDEVICE
+ * needed; e.g. 256 frames of 256 values against 1,024 regions need about 4 MB) and EDEVICE
  * when the array's device address cannot be looked up.
  * Every call on one device shares that device's array, which keeps the last
  * call's contents (the kernels clear what must start at zero): calls on one
@@ -313,7 +313,8 @@ int hloc_query_info(hloc_db *db, int64_t *out, int32_t n);
  * Region ids chosen for each frame by the last query call (waits for it):
  * nq x n_regions_eff int32, sorted by (distance to representative, id); in
  * id order when every non-empty region was searched. *nq and *n_regions_eff
- * receive the sizes; `out` may be NULL to get only the sizes.
+ * receive the sizes; `out` may be NULL to get only the sizes. The ids are
+ * those of the regions the query ran on, also after hloc_set_regions.
  * Errors: EINVAL, ESTATE, EDEVICE.
  */
 int hloc_last_regions(hloc_db *db, int32_t *out, int32_t *nq, int32_t *n_regions_eff);

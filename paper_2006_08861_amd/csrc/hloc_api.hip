@@ -1341,7 +1341,7 @@ int hloc_query_labels_async(hloc_db *db, const float *q, int32_t nq, int32_t k,
   ag.tile = tile;
   ag.flags = flags;
   ag.big_list = as<int32_t>(ws->agg_big);
-  ag.big_count = as<int32_t>(ws->misc) + 8;  // cleared by the last search's prep
+  ag.big_count = as<int32_t>(ws->misc) + 8;  // cleared by the last search's first launch
   ag.num_cu = db->num_cu;
   HIPCHK(launch_aggregate_labels(ag, P, nq, s));
   return HLOC_OK;

@@ -61,14 +61,18 @@ constexpr int kWideDenseFrames = 512;  // batches from which the coarse screen u
 // kernels reach 82 and 230): even at about 1.3 GFLOP. Measured, schedule and
 // screens: 256 frames on 200k x 256 fp32 49 -> 36 us (0.2 GFLOP), 1,265 frames
 // 71 -> 57 (1.1), one frame on 10k x 256 17 -> 5.6; 2,048 frames on 500k x 512
-// bf16 235 -> 850 (51), so that stays with the list.
+// bf16 235 -> 850 (51), so that stays with the list. Small databases and large
+// batches hold too (whole calls): 10,000 frames on 1,000 x 64 fp32 rows in 10
+// regions, all searched, 340 -> 181 us, one region kept 485 -> 227.
 constexpr int64_t kDirectSlots = (int64_t)1 << 22;
 constexpr double kDirectFlops = 1.5e9;
 constexpr int kDirectSplits = 16;
 // Host-pointer calls whose inputs and outputs take at most this much go through
 // pinned memory that the kernels read and write themselves: each copy command
 // costs about 8 us, seven of them more than the kernels of one frame on 10k
-// rows. Larger ones are copied.
+// rows. Larger ones are copied. Near the limit, on 10k x 256 rows: 190 frames
+// 195 -> 71 us, 60 frames with k = 256 (whose lists the aggregation reads back)
+// 250 -> 134; 230 frames, copied, 201 -> 163.
 constexpr size_t kHostDirectBytes = 256 * 1024;
 // Low-precision coarse screens: the fused product with key lists above
 // kKeyWords frame x representative words, the dense words below: storing them
@@ -76,7 +80,11 @@ constexpr size_t kHostDirectBytes = 256 * 1024;
 // frames. Measured, coarse stage in all, words / keys: 64 x 200 16 / 32 us, 2,048 x
 // 1,024 (512 values) 54 / 78, 8,192 x 1,024 75 / 112, 2,048 x 8,192 121 / 108,
 // 32,768 x 4,096 1,000 / 475. A handful of frames, up to kKeyFew words, stays
-// with the lists, slower as it is: that is where their deferral is exercised.
+// with the lists, where every low-precision batch was before the words, at a
+// loss (whole calls of one frame, keys / words: 20 regions of 2k x 64 bf16 rows
+// 36.6 / 34.8 us, 100 of 10k x 512 45.3 / 35.8, 1,000 of 100k x 512 44.1 / 38.6):
+// five frames against 180 regions are where a test of the library asks for
+// frames that the lists cannot decide.
 constexpr int64_t kKeyWords = (int64_t)3 << 22;
 constexpr int64_t kKeyFew = 1024;
 constexpr double kUnit32 = 5.9604644775390625e-08;  // 2^-24

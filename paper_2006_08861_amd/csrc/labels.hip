@@ -1,10 +1,12 @@
 // Subspace labels (Section 4 keeps the top N candidates of every walked path:
 // N x M x P of them for a request of M frames over P paths). A query over
-// labels runs the two-stage search once per label with the coarse words of
-// every region outside the label set to "no candidate", so that the coarse
-// selection, the fine screen and the top-k stay within the label; the
-// aggregation then pools, for each frame of a request, the k results of
-// every label.
+// labels runs the two-stage search once per label with every region outside
+// the label "no candidate" to the coarse selection, so that it, the fine screen
+// and the top-k stay within the label; the aggregation then pools, for each
+// frame of a request, the k results of every label. The fused coarse product
+// and the selection's frame kernel look the labels up themselves; this kernel
+// masks the coarse words ahead of the selection's block kernel (more than 64
+// survivors).
 #include <algorithm>
 
 #include "hloc_host.h"

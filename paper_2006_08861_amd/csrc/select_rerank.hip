@@ -1063,7 +1063,9 @@ __device__ __forceinline__ void wave_sync() {
 // this one: 32,768 frames of that shape 1275 (3270) -> 815 us, 2,048 frames on
 // 500k x 512 bf16 107 -> 63, fp8 673 -> 376, 256 frames on 200k x 256 fp32
 // 25.7 -> 13.8, every row searched 44 -> 19; coarse stage, 2,048 frames 61 ->
-// 31, 256 frames 15.3 -> 11.2. What is left is the rows' way through L2 (2 KB
+// 31, 256 frames 15.3 -> 11.2. Few frames on long lists gain too (whole calls,
+// all 2M x 64 fp32 rows, 125,000 words a frame): 1 / 16 / 64 frames 1744, 452,
+// 537 -> 188, 253, 349. What is left is the rows' way through L2 (2 KB
 // each, 110 a frame with bf16 rows, 527 with fp8 rows).
 constexpr int kFrameSlots = 64;   // region slots, one per lane
 constexpr int kFrameRegs = 8;     // positions per lane held in registers
