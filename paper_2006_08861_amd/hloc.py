@@ -9,7 +9,6 @@ no CPU fallback.
 """
 from __future__ import annotations
 
-import contextlib
 import ctypes
 import os
 import re
@@ -147,25 +146,17 @@ def _is_torch_cuda(x) -> bool:
     return isinstance(x, torch.Tensor) and x.is_cuda
 
 
-_SAME = contextlib.nullcontext()
-
-
-def _stream(stream, dev):
-    """The stream of a call on device dev (default: torch's current one), a
-    context in which it is the current one, so that copies that the binding
-    makes of its inputs, and the outputs, are allocated on and ordered by the
-    stream that uses them, and the stream that is current outside if another."""
+def _on_stream(stream, dev, call):
+    """What call() returns with `stream` as torch's current one: the copies that
+    the binding makes of its inputs, and the outputs, are allocated on and
+    ordered by the stream that uses them. The outputs (a tensor or a dict of
+    tensors) may be used on the stream that is current outside, too."""
     import torch
-    cur = torch.cuda.current_stream(dev)
-    if stream is None or stream.cuda_stream == cur.cuda_stream:
-        return cur, _SAME, None
-    return stream, torch.cuda.stream(stream), cur
-
-
-def _returned(out, outside):
-    """out, whose tensors the caller may use on the stream that is current outside."""
-    if outside is not None:
-        for t in out.values():
+    outside = torch.cuda.current_stream(dev)
+    with torch.cuda.stream(stream):
+        out = call()
+    for t in out.values() if isinstance(out, dict) else [out]:
+        if _is_torch_cuda(t):
             t.record_stream(outside)
     return out
 
@@ -177,23 +168,24 @@ def fft_features(signals, d: int, stream=None):
     device and back and returns a NumPy array."""
     import torch
     host = not _is_torch_cuda(signals)
-    dev = torch.device("cuda", torch.cuda.current_device()) if host else signals.device
-    s, ctx, outside = _stream(stream, dev)
-    with ctx:
-        x = (torch.from_numpy(np.ascontiguousarray(signals, dtype=np.float32)).to(dev) if host
-             else signals.contiguous())
-        if x.dtype != torch.float32 or x.dim() != 2:
-            raise HlocError(EINVAL, "signals must be a 2-D float32 array")
-        nsig, length = x.shape
-        out = torch.empty((nsig, d), dtype=torch.float32, device=dev)
-        lib = load_library()
-        with torch.cuda.device(dev):
-            _check(lib.hloc_fft_features_async(_P(x.data_ptr()), nsig, length, d,
-                                               _P(out.data_ptr()), _P(s.cuda_stream)))
-        if host:
-            s.synchronize()
-            return out.cpu().numpy()
-    return _returned({"out": out}, outside)["out"]
+    if stream is not None:
+        dev = stream.device if host else signals.device
+        return _on_stream(stream, dev, lambda: fft_features(signals, d))
+    x = (torch.from_numpy(np.ascontiguousarray(signals, dtype=np.float32)).cuda() if host
+         else signals.contiguous())
+    if x.dtype != torch.float32 or x.dim() != 2:
+        raise HlocError(EINVAL, "signals must be a 2-D float32 array")
+    nsig, length = x.shape
+    out = torch.empty((nsig, d), dtype=torch.float32, device=x.device)
+    stream = torch.cuda.current_stream(x.device)
+    lib = load_library()
+    with torch.cuda.device(x.device):
+        _check(lib.hloc_fft_features_async(_P(x.data_ptr()), nsig, length, d, _P(out.data_ptr()),
+                                           _P(stream.cuda_stream)))
+    if host:
+        stream.synchronize()
+        return out.cpu().numpy()
+    return out
 
 
 class HlocDB:
@@ -289,32 +281,34 @@ class HlocDB:
         lib = load_library()
         if q.dtype != torch.float32 or q.dim() != 2 or q.shape[1] != self.d:
             raise HlocError(EINVAL, f"q must be an nq x {self.d} float32 tensor")
+        if stream is not None:
+            return _on_stream(stream, q.device, lambda: self._query_device(
+                q, k, n_regions, req_offsets, prec, aggregate, None, entry))
+        q = q.contiguous()
         dev = q.device
-        s, ctx, outside = _stream(stream, dev)
-        with ctx:
-            q = q.contiguous()
-            nq = q.shape[0]
-            offs = None
-            if req_offsets is not None:
-                offs = torch.as_tensor(req_offsets, dtype=torch.int32, device=dev).contiguous()
-            nreq = nq if offs is None else offs.numel() - 1
-            idx = torch.empty((nq, k), dtype=torch.int64, device=dev)
-            dist = torch.empty((nq, k), dtype=torch.float32, device=dev)
-            out = dict(idx=idx, dist=dist)
-            xy = tile = flags = None
-            if aggregate:
-                xy = torch.empty((nreq, 2), dtype=torch.float64, device=dev)
-                tile = torch.empty((nreq, 2), dtype=torch.int32, device=dev)
-                flags = torch.empty(nreq, dtype=torch.int32, device=dev)
-                out.update(xy=xy, tile=tile, flags=flags)
+        nq = q.shape[0]
+        offs = None
+        if req_offsets is not None:
+            offs = torch.as_tensor(req_offsets, dtype=torch.int32, device=dev).contiguous()
+        nreq = nq if offs is None else offs.numel() - 1
+        idx = torch.empty((nq, k), dtype=torch.int64, device=dev)
+        dist = torch.empty((nq, k), dtype=torch.float32, device=dev)
+        out = dict(idx=idx, dist=dist)
+        xy = tile = flags = None
+        if aggregate:
+            xy = torch.empty((nreq, 2), dtype=torch.float64, device=dev)
+            tile = torch.empty((nreq, 2), dtype=torch.int32, device=dev)
+            flags = torch.empty(nreq, dtype=torch.int32, device=dev)
+            out.update(xy=xy, tile=tile, flags=flags)
+        s = torch.cuda.current_stream(dev)
 
-            def p(t):
-                return None if t is None else ctypes.c_void_p(t.data_ptr())
+        def p(t):
+            return None if t is None else ctypes.c_void_p(t.data_ptr())
 
-            _check(getattr(lib, entry)(self._h, p(q), nq, k, n_regions, p(offs), nreq, prec,
-                                       p(idx), p(dist), p(xy), p(tile), p(flags),
-                                       ctypes.c_void_p(s.cuda_stream)))
-        return _returned(out, outside)
+        _check(getattr(lib, entry)(self._h, p(q), nq, k, n_regions, p(offs), nreq, prec,
+                                   p(idx), p(dist), p(xy), p(tile), p(flags),
+                                   ctypes.c_void_p(s.cuda_stream)))
+        return out
 
     def set_region_labels(self, labels, n_labels: int):
         lab = np.ascontiguousarray(labels, dtype=np.int32)
@@ -328,27 +322,29 @@ class HlocDB:
         idx / dist come back as n_labels x nq x k CUDA tensors."""
         import torch
         dev = q.device if _is_torch_cuda(q) else torch.device("cuda", torch.cuda.current_device())
-        s, ctx, outside = _stream(stream, dev)
-        with ctx:
-            qd = q.float().contiguous() if _is_torch_cuda(q) else \
-                torch.from_numpy(np.ascontiguousarray(q, dtype=np.float32)).to(dev)
-            nq = int(qd.shape[0])
-            offs = None
-            if req_offsets is not None:
-                offs = req_offsets.to(torch.int32).contiguous() if _is_torch_cuda(req_offsets) \
-                    else torch.from_numpy(np.ascontiguousarray(req_offsets, dtype=np.int32)).to(dev)
-            nreq = nq if offs is None else int(offs.shape[0]) - 1
-            out = {"idx": torch.empty((n_labels, nq, k), dtype=torch.int64, device=dev),
-                   "dist": torch.empty((n_labels, nq, k), dtype=torch.float32, device=dev),
-                   "xy": torch.empty((nreq, 2), dtype=torch.float64, device=dev),
-                   "tile": torch.empty((nreq, 2), dtype=torch.int32, device=dev),
-                   "flags": torch.empty(nreq, dtype=torch.int32, device=dev)}
-            _check(load_library().hloc_query_labels_async(
-                self._h, _P(qd.data_ptr()), nq, k, n_regions, n_labels,
-                None if offs is None else _P(offs.data_ptr()), nreq, PRECISIONS[precision],
-                *(_P(out[key].data_ptr()) for key in ("idx", "dist", "xy", "tile", "flags")),
-                _P(s.cuda_stream)))
-        return _returned(out, outside)
+        if stream is not None:
+            return _on_stream(stream, dev, lambda: self.query_labels(
+                q, k, n_regions, n_labels, req_offsets, precision))
+        qd = q.float().contiguous() if _is_torch_cuda(q) else \
+            torch.from_numpy(np.ascontiguousarray(q, dtype=np.float32)).to(dev)
+        nq = int(qd.shape[0])
+        offs = None
+        if req_offsets is not None:
+            offs = req_offsets.to(torch.int32).contiguous() if _is_torch_cuda(req_offsets) else \
+                torch.from_numpy(np.ascontiguousarray(req_offsets, dtype=np.int32)).to(dev)
+        nreq = nq if offs is None else int(offs.shape[0]) - 1
+        out = {"idx": torch.empty((n_labels, nq, k), dtype=torch.int64, device=dev),
+               "dist": torch.empty((n_labels, nq, k), dtype=torch.float32, device=dev),
+               "xy": torch.empty((nreq, 2), dtype=torch.float64, device=dev),
+               "tile": torch.empty((nreq, 2), dtype=torch.int32, device=dev),
+               "flags": torch.empty(nreq, dtype=torch.int32, device=dev)}
+        stream = torch.cuda.current_stream(dev)
+        _check(load_library().hloc_query_labels_async(
+            self._h, _P(qd.data_ptr()), nq, k, n_regions, n_labels,
+            None if offs is None else _P(offs.data_ptr()), nreq, PRECISIONS[precision],
+            *(_P(out[key].data_ptr()) for key in ("idx", "dist", "xy", "tile", "flags")),
+            _P(stream.cuda_stream)))
+        return out
 
     def query_windows(self, q, k: int, n_regions: int, req_offsets, req_frames,
                       precision="fp32", stream=None) -> dict:
@@ -359,28 +355,30 @@ class HlocDB:
         import torch
         dev = q.device if _is_torch_cuda(q) else torch.device("cuda", torch.cuda.current_device())
 
+        if stream is not None:
+            return _on_stream(stream, dev, lambda: self.query_windows(
+                q, k, n_regions, req_offsets, req_frames, precision))
         def on_dev(a, dtype):
             if _is_torch_cuda(a):
                 return a.to(dtype).contiguous()
             return torch.from_numpy(np.ascontiguousarray(a)).to(dtype).to(dev)
 
-        s, ctx, outside = _stream(stream, dev)
-        with ctx:
-            qd = on_dev(q, torch.float32)
-            offs = on_dev(req_offsets, torch.int32)
-            frames = on_dev(req_frames, torch.int32)
-            nq, nreq = int(qd.shape[0]), int(offs.shape[0]) - 1
-            out = {"idx": torch.empty((nq, k), dtype=torch.int64, device=dev),
-                   "dist": torch.empty((nq, k), dtype=torch.float32, device=dev),
-                   "xy": torch.empty((nreq, 2), dtype=torch.float64, device=dev),
-                   "tile": torch.empty((nreq, 2), dtype=torch.int32, device=dev),
-                   "flags": torch.empty(nreq, dtype=torch.int32, device=dev)}
-            _check(load_library().hloc_query_windows_async(
-                self._h, _P(qd.data_ptr()), nq, k, n_regions, _P(offs.data_ptr()),
-                _P(frames.data_ptr()), int(frames.shape[0]), nreq, PRECISIONS[precision],
-                *(_P(out[key].data_ptr()) for key in ("idx", "dist", "xy", "tile", "flags")),
-                _P(s.cuda_stream)))
-        return _returned(out, outside)
+        qd = on_dev(q, torch.float32)
+        offs = on_dev(req_offsets, torch.int32)
+        frames = on_dev(req_frames, torch.int32)
+        nq, nreq = int(qd.shape[0]), int(offs.shape[0]) - 1
+        out = {"idx": torch.empty((nq, k), dtype=torch.int64, device=dev),
+               "dist": torch.empty((nq, k), dtype=torch.float32, device=dev),
+               "xy": torch.empty((nreq, 2), dtype=torch.float64, device=dev),
+               "tile": torch.empty((nreq, 2), dtype=torch.int32, device=dev),
+               "flags": torch.empty(nreq, dtype=torch.int32, device=dev)}
+        stream = torch.cuda.current_stream(dev)
+        _check(load_library().hloc_query_windows_async(
+            self._h, _P(qd.data_ptr()), nq, k, n_regions, _P(offs.data_ptr()),
+            _P(frames.data_ptr()), int(frames.shape[0]), nreq, PRECISIONS[precision],
+            *(_P(out[key].data_ptr()) for key in ("idx", "dist", "xy", "tile", "flags")),
+            _P(stream.cuda_stream)))
+        return out
 
     def info(self) -> dict:
         out = (ctypes.c_int64 * len(_INFO_KEYS))()
@@ -551,28 +549,30 @@ class Streams:
         import torch
         dev = q.device if _is_torch_cuda(q) else torch.device("cuda", torch.cuda.current_device())
 
+        if stream is not None:
+            return _on_stream(stream, dev, lambda: self.query(
+                q, seg_offsets, seg_stream, n_regions, precision))
         def on_dev(a, dtype):
             if _is_torch_cuda(a):
                 return a.to(dtype).contiguous()
             return torch.from_numpy(np.ascontiguousarray(a)).to(dtype).to(dev)
 
-        s, ctx, outside = _stream(stream, dev)
-        with ctx:
-            qd = on_dev(q, torch.float32)
-            offs = on_dev(seg_offsets, torch.int32)
-            sid = on_dev(seg_stream, torch.int32)
-            nq, nseg = int(qd.shape[0]), int(sid.shape[0])
-            out = {"idx": torch.empty((nq, self.k), dtype=torch.int64, device=dev),
-                   "dist": torch.empty((nq, self.k), dtype=torch.float32, device=dev),
-                   "xy": torch.empty((nq, 2), dtype=torch.float64, device=dev),
-                   "tile": torch.empty((nq, 2), dtype=torch.int32, device=dev),
-                   "flags": torch.empty(nq, dtype=torch.int32, device=dev)}
-            _check(load_library().hloc_query_streams_async(
-                self._h, _P(qd.data_ptr()), nq, n_regions, PRECISIONS[precision],
-                _P(offs.data_ptr()), _P(sid.data_ptr()), nseg,
-                *(_P(out[key].data_ptr()) for key in ("idx", "dist", "xy", "tile", "flags")),
-                _P(s.cuda_stream)))
-        return _returned(out, outside)
+        qd = on_dev(q, torch.float32)
+        offs = on_dev(seg_offsets, torch.int32)
+        sid = on_dev(seg_stream, torch.int32)
+        nq, nseg = int(qd.shape[0]), int(sid.shape[0])
+        out = {"idx": torch.empty((nq, self.k), dtype=torch.int64, device=dev),
+               "dist": torch.empty((nq, self.k), dtype=torch.float32, device=dev),
+               "xy": torch.empty((nq, 2), dtype=torch.float64, device=dev),
+               "tile": torch.empty((nq, 2), dtype=torch.int32, device=dev),
+               "flags": torch.empty(nq, dtype=torch.int32, device=dev)}
+        stream = torch.cuda.current_stream(dev)
+        _check(load_library().hloc_query_streams_async(
+            self._h, _P(qd.data_ptr()), nq, n_regions, PRECISIONS[precision],
+            _P(offs.data_ptr()), _P(sid.data_ptr()), nseg,
+            *(_P(out[key].data_ptr()) for key in ("idx", "dist", "xy", "tile", "flags")),
+            _P(stream.cuda_stream)))
+        return out
 
     def reset(self):
         _check(load_library().hloc_streams_reset(self._h))
