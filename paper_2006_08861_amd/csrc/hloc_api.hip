@@ -323,11 +323,11 @@ struct Phaser {
 
 // Survivor blocks of a frame: k' rows if every block were full. A region's last
 // block is shorter, and with regions of about a block the survivors may hold
-// fewer than k rows; then nothing bounds the k-th distance and the frame's whole
-// list is re-scored. So they are as many as hold k rows nearly always (two
-// standard deviations), up to what the frame kernel takes. With 20 rows a
-// region and k = 10, two blocks fail one frame in four: 5,000 frames on 20k x 64
-// rows, all searched, 2,986 us with two blocks and 322 with four.
+// fewer than k rows; then a second pass over the frame's words bounds the k-th
+// distance (in the frame kernel; the block kernel re-scores the whole list). So
+// they are as many as hold k rows nearly always (two standard deviations), up to
+// what the frame kernel takes. With 20 rows a region and k = 10, two blocks fail
+// one frame in four.
 int32_t survivor_blocks(const hloc_db *db, int32_t kp, int32_t k) {
   const int32_t full = (kp + kBlockRows - 1) / kBlockRows;
   for (int32_t L = full; L <= kFrameBlocks; ++L)

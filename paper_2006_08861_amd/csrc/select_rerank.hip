@@ -1051,7 +1051,11 @@ __device__ __forceinline__ void wave_sync() {
 //   * tau = the m-th distance + the screen's error bound: every position not
 //     yet re-scored with a word up to tau is (the band), kBandBlocks blocks
 //     (or kBandRows rows) at a time, and a row ordered before the m-th best so
-//     far enters the merge. Nothing above tau can enter the m best.
+//     far enters the merge. Nothing above tau can enter the m best. Survivor
+//     blocks that hold fewer than m rows say nothing of the m-th distance; then
+//     it is bounded by the m-th smallest word of a block, found by bisection
+//     over the words (200k x 64 fp32 rows in 3,000 regions, 60 of them kept, 8,192
+//     frames: whole lists of the frames it happens to 967 us, this bound 549).
 // Key mode: a band that reaches the words the key lists may have dropped
 // (their smallest bound) defers the frame.
 // The block kernel spends most of its instructions on histograms, scans and
@@ -1225,6 +1229,35 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
 #pragma unroll
     for (int u = 0; u < 4; ++u) account(v[u], p[u]);
   }
+  // A word that at least `want` positions do not exceed, no more than 2^-10
+  // above the smallest such (kWordNone if there are fewer positions). Each block
+  // holds a row no farther than its word and the error bound, so the want-th
+  // distance is not beyond this word and the bound either.
+  auto word_bound = [&](int want) -> uint32_t {
+    auto reach = [&](uint32_t x) {
+      int c = 0;
+#pragma unroll 1
+      for (int t = w; t < nt; t += W) {
+        uint32_t v, p;
+        fetch(t * 64 + lane, v, p);
+        c += __popcll(__ballot(v <= x));
+      }
+      if (W > 1) {
+        if (lane == 0) ctr[8 + w] = c;
+        __syncthreads();
+        c = 0;
+        for (int i = 0; i < W; ++i) c += ctr[8 + i];
+        __syncthreads();
+      }
+      return c >= want;
+    };
+    uint32_t x = 0;
+    if (!reach(0x7FFFFFFFu)) return kWordNone;
+#pragma unroll 1
+    for (int b = 30; b >= 13; --b)
+      if (!reach(x | ((1u << b) - 1u))) x |= 1u << b;
+    return x | 0x1FFFu;
+  };
   // the survivors: lane t < cnt holds the t-th
   uint32_t sw = kWordNone, sp = 0;
   int cnt = take_smallest(m1, p1, m2, p2, L, sw, sp);
@@ -1355,8 +1388,12 @@ __global__ __launch_bounds__(64 * W, MODE == kFineBlocks ? 4 : 3) void k_select_
     }
     if (band < 0) {
       // certificate: what is within the error bound of the m-th distance
-      const double dm =
+      double dm =
           have == m ? __longlong_as_double((long long)srt_hi[cur * m + m - 1]) : __builtin_inf();
+      if (kBlocks && have < m) {
+        const uint32_t wm = word_bound(m);
+        if (wm < 0x7F800000u) dm = (double)__uint_as_float(wm) + err;
+      }
       tau_w = __float_as_uint(__double2float_ru(dm * (1.0 + 1e-12) + err));
       if (kKeys) {
         const uint32_t bw = (uint32_t)(wave_min_u64(bound) >> 32);

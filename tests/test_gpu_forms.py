@@ -193,3 +193,36 @@ def test_key_lists_and_words_agree(torch_cuda, precision, labels):
         st = judge_frames(full["idx"][:12].numpy(), full["dist"][:12].numpy(), None, ora, feats,
                           region_of, R, q[:12], k)
         assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "fp8"])
+@pytest.mark.parametrize("rows,k,n_reg", [(2, 50, 1500), (1, 17, 20), (2, 10, 3), (3, 200, 60)])
+def test_survivor_blocks_of_fewer_rows_than_k(torch_cuda, rows, k, n_reg, precision):
+    # no 16 blocks of one to three rows hold k: the k-th smallest word of a block
+    # and the error bound say what can still be among the k nearest, not half of the
+    # 1,500 blocks (16 row slots each) of the exhaustive search even behind fp8; a
+    # list of fewer blocks than k is re-scored whole. 8, 4 and 2 waves a frame:
+    # bitwise the fp32 screens' results, and 12 frames against the oracle
+    rng = np.random.default_rng(46)
+    R, d, nq = 1500, 64, 4100
+    feats = rng.standard_normal((R * rows, d)).astype(np.float32)
+    region_of = np.repeat(np.arange(R), rows).astype(np.int32)
+    xy = rng.uniform(0, 40, size=(len(feats), 2))
+    q = feats[rng.integers(0, len(feats), nq)] + 0.3 * rng.standard_normal((nq, d), dtype=np.float32)
+    db = hloc.HlocDB(feats, xy, mirrors=hloc.MIRROR_BF16 | hloc.MIRROR_FP8)
+    db.set_regions(region_of, R)
+    qd = torch_cuda.from_numpy(q).cuda()
+    ref = db.query(qd, k, n_reg)
+    for frames in (40, 1600, nq):
+        got = db.query(qd[:frames], k, n_reg, precision=precision)
+        info = db.info()
+        say(f"[case] {precision} {frames} frames: {info}")
+        for key in got:
+            assert torch_cuda.equal(got[key], ref[key][:frames]), (frames, key)
+        assert n_reg < R or info["rerank_rows"] <= 750 * 16 * frames
+    db.close()
+    ora = oracle.localize(feats, xy, region_of, R, q[:12], np.arange(13), k, n_reg,
+                          (0.5, 1, 0.0, 0))
+    idx, dist = (ref[key][:12].cpu().numpy() for key in ("idx", "dist"))
+    st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:12], k)
+    assert st["recall"] == 1.0
