@@ -481,14 +481,15 @@ int enqueue_query(hloc_ws *ws, const Plan &plan, const float *q, const int32_t *
       HIPCHK(wide_dense ? launch_screen_wide_f32(sa, p.grid1, db->num_cu, s)
                         : launch_screen_f32(sa, p.grid1, s));
     }
-    if (masked && p.L1 > kFrameL)
+    const bool look_up = list ? p.L1 <= kFrameL : words_in_frame_kernel(p.L1, p.nq, db->R);
+    if (masked && !look_up)
       HIPCHK(launch_mask_label(as<uint32_t>(ws->cand1), p.nq, db->R, db->rlabel, label,
                                label_frames, s));
     if (!list) ph.begin(HLOC_PHASE_COARSE_SELECT);
     SelRerankArgs ra{};
     ra.cand = as<uint32_t>(ws->cand1);
     ra.cap = db->R;
-    if (masked && p.L1 <= kFrameL) {
+    if (masked && look_up) {
       ra.rlabel = db->rlabel;
       ra.label = label;
       ra.label_frames = label_frames;

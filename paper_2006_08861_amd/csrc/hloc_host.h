@@ -87,6 +87,8 @@ constexpr size_t kHostDirectBytes = 256 * 1024;
 // frames that the lists cannot decide.
 constexpr int64_t kKeyWords = (int64_t)3 << 22;
 constexpr int64_t kKeyFew = 1024;
+// Words of a frame that the selection still reads with few waves.
+constexpr int64_t kLongWords = 32768;
 constexpr double kUnit32 = 5.9604644775390625e-08;  // 2^-24
 
 template <class T>
@@ -257,6 +259,9 @@ int enqueue_query(hloc_ws *ws, const Plan &p, const float *q, const int32_t *req
                   const int32_t *req_k, int64_t *idx, float *dist, double *xy, int32_t *tile,
                   int32_t *flags, hipStream_t s, const int32_t *req_frames = nullptr,
                   int32_t n_frames = 0, int32_t label = -1, int32_t label_frames = 0);
+// Whether coarse words, cap of them a frame of which L survive, go to the frame
+// kernel, the only one that looks up labels itself.
+bool words_in_frame_kernel(int32_t L, int32_t nq, int64_t cap);
 hipError_t launch_mask_label(uint32_t *words, int32_t nq, int32_t R, const int32_t *rlabel,
                              int32_t p, int32_t per, hipStream_t s);
 // The aggregation of aggregate.hip over a frame list (NULL: contiguous frames).

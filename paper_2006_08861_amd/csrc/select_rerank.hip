@@ -25,6 +25,7 @@
 //      the frame.
 // Distances are squared L2 (same order as the Euclidean distance of Section 4).
 #include "hloc_device.h"
+#include "hloc_host.h"
 #include "hloc_internal.h"
 
 namespace hloc {
@@ -1557,6 +1558,17 @@ bool few_blocks(const SelRerankArgs &a) {
          (a.cap > kBigFrame ? a.nq >= 512 : !a.q_err && a.cap > 256);
 }
 
+// Coarse words: the block kernel reads a long list with 1,024 threads where the
+// frame kernel has 64 to 256, and of more than 32 survivors each of its waves
+// (one or two then, their lists must fit) takes its own before they are merged.
+// Whole calls on fp32 rows, frame kernel / block kernel: 12 survivors, 10,000
+// words 256 frames 64 / 65 us, 2,048 frames 224 / 295; 40,000 words 336 / 297 and
+// 852 / 747; 100,000 words 811 / 719 and 2,134 / 1,909. 64 survivors, 1,000 words
+// 96 / 66 and 218 / 182; 33 survivors 66 / 54 and 143 / 152.
+bool words_in_frame_kernel(int32_t L, int32_t nq, int64_t cap) {
+  return L <= kFrameL && cap <= kLongWords && (L <= 32 || (L <= 40 && nq > 512));
+}
+
 template <int MODE>
 hipError_t launch_frame(const SelRerankArgs &a, hipStream_t s) {
   const int W = frame_waves(a);
@@ -1593,7 +1605,11 @@ hipError_t launch_select_rerank(SelRerankArgs a, hipStream_t s) {
     a.cache = (int32_t)std::min<int64_t>(a.cap, kWordCache);
   }
   // the frame kernel, unless its lists do not hold the survivors or the slots
-  if (a.L <= kFrameL && a.m >= 1 && a.nslots <= kFrameSlots && (!a.blocks || few_blocks(a))) {
+  const bool frame = a.blocks ? few_blocks(a)
+                     : a.keys || a.frame_list ? a.L <= kFrameL
+                                              : words_in_frame_kernel(a.L, a.nq, a.cap);
+  if (a.rlabel && !frame) return hipErrorInvalidValue;
+  if (frame && a.m >= 1 && a.nslots <= kFrameSlots) {
     if (a.blocks) return launch_frame<kFineBlocks>(a, s);
     return a.keys ? launch_frame<kCoarseKeys>(a, s) : launch_frame<kCoarseWords>(a, s);
   }

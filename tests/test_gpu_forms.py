@@ -226,3 +226,54 @@ def test_survivor_blocks_of_fewer_rows_than_k(torch_cuda, rows, k, n_reg, precis
     idx, dist = (ref[key][:12].cpu().numpy() for key in ("idx", "dist"))
     st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:12], k)
     assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("R,n_reg,nqs,labels", [
+    (40_000, 8, (1, 300), 2), (32_768, 8, (40,), 2), (900, 28, (40, 600), 0),
+    (900, 29, (40, 512, 513), 3), (900, 37, (513,), 0), (900, 60, (600,), 3), (900, 61, (40,), 3)])
+def test_coarse_words_of_long_lists_and_many_survivors(torch_cuda, R, n_reg, nqs, labels):
+    # regions where the coarse selection goes from the frame kernel to the block
+    # kernel: 32,768 words and more, 32 / 33 / 41 / 64 / 65 survivors, 512 and 513
+    # frames, with labels (looked up by the one, masked ahead of the other):
+    # bitwise the results of bf16 screens and of halves of the batch, and 8
+    # frames against the oracle
+    rng = np.random.default_rng(45)
+    rows, d, k = 3, 64, 10
+    feats = rng.standard_normal((R * rows, d)).astype(np.float32)
+    region_of = np.repeat(np.arange(R), rows).astype(np.int32)
+    xy = rng.uniform(0, 40, size=(len(feats), 2))
+    q = (feats[rng.integers(0, len(feats), max(nqs))]
+         + 0.3 * rng.standard_normal((max(nqs), d))).astype(np.float32)
+    of = (np.arange(R) % max(labels, 1)).astype(np.int32)
+    db = hloc.HlocDB(feats, xy, mirrors=hloc.MIRROR_BF16)
+    db.set_regions(region_of, R)
+    if labels:
+        db.set_region_labels(of, labels)
+
+    def run(frames, prec):
+        fd = torch_cuda.from_numpy(frames).cuda()
+        if labels:
+            offs = torch_cuda.arange(len(frames) + 1, dtype=torch_cuda.int32, device="cuda")
+            return [db.query_labels(fd, k, n_reg, labels, offs, precision=prec),
+                    db.query(fd, k, n_reg, precision=prec)]
+        return [db.query(fd, k, n_reg, precision=prec)]
+
+    for nq in nqs:
+        say(f"[case] {nq} frames, {n_reg} of {R} regions, {labels} labels")
+        full = run(q[:nq], "fp32")
+        cut = (nq + 1) // 2
+        parts = [run(q[:cut], "fp32"), run(q[cut:nq], "fp32")] if nq > 1 else [full]
+        for i, (f, b) in enumerate(zip(full, run(q[:nq], "bf16"))):
+            per_label = labels and i == 0
+            for key in f:
+                assert torch_cuda.equal(f[key], b[key]), (nq, i, key)
+                dim = 1 if per_label and key in ("idx", "dist") else 0
+                whole = torch_cuda.cat([p[i][key] for p in parts], dim=dim)
+                assert torch_cuda.equal(f[key], whole), (nq, i, key)
+    db.close()
+    m = min(8, max(nqs))
+    ora = oracle.localize(feats, xy, region_of, R, q[:m], np.arange(m + 1), k, n_reg,
+                          (0.5, 1, 0.0, 0))
+    idx, dist = (full[-1][key][:m].cpu().numpy() for key in ("idx", "dist"))
+    st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:m], k)
+    assert st["recall"] == 1.0
