@@ -98,7 +98,7 @@ void dev_free(T *&p) {
 // Batches of nq frames on low-precision screens take the key lists.
 bool takes_keys(const hloc_db *db, int64_t nq) {
   return db->lp[HLOC_BF16].reps && coarse_gemm_supports(db->dp) && db->R < (1 << 28) &&
-         (nq * db->R > kKeyWords || nq * db->R <= kKeyFew);
+         (nq * db->R > (db->R > kLongWords ? kDirectSlots : kKeyWords) || nq * db->R <= kKeyFew);
 }
 
 // Ranges of the representatives of the fused coarse product, *reps each.

@@ -84,10 +84,14 @@ constexpr size_t kHostDirectBytes = 256 * 1024;
 // loss (whole calls of one frame, keys / words: 20 regions of 2k x 64 bf16 rows
 // 36.6 / 34.8 us, 100 of 10k x 512 45.3 / 35.8, 1,000 of 100k x 512 44.1 / 38.6):
 // five frames against 180 regions are where a test of the library asks for
-// frames that the lists cannot decide.
+// frames that the lists cannot decide. Above kLongWords words a frame, which the
+// selection reads with one block a frame, the lists are ahead from kDirectSlots
+// words on, where the frame lists of the direct screens end (whole calls, words /
+// keys: 100k regions of 200k x 256 bf16 rows, 60 frames 750 / 609 us, 70k of
+// 200k x 64 496 / 402, 40k, 300 frames 370 / 274; only frames that the lists
+// cannot decide cost more, 100k of 200k x 64, 44 kept, 60 frames 716 / 804).
 constexpr int64_t kKeyWords = (int64_t)3 << 22;
 constexpr int64_t kKeyFew = 1024;
-// Words of a frame that the selection still reads with few waves.
 constexpr int64_t kLongWords = 32768;
 constexpr double kUnit32 = 5.9604644775390625e-08;  // 2^-24
 

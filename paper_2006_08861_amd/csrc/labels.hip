@@ -5,8 +5,8 @@
 // and the top-k stay within the label; the aggregation then pools, for each
 // frame of a request, the k results of every label. The fused coarse product
 // and the selection's frame kernel look the labels up themselves; this kernel
-// masks the coarse words ahead of the selection's block kernel (more than 64
-// survivors).
+// masks the coarse words ahead of the selection's block kernel (more than 32 to 64
+// survivors, by the batch, or long lists).
 #include <algorithm>
 
 #include "hloc_host.h"

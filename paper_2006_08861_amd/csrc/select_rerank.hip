@@ -1,7 +1,8 @@
 // Top candidates per frame ("select top candidates", Algorithm 1), in one
 // kernel: k_select_frame (W waves per frame) for lists that fit a wave's
 // lanes, k_select_rerank (one block per frame) past them (more than 64 region
-// slots or survivor rows, or 16 survivor blocks). Both do the same three things; the block
+// slots or survivor regions, or 16 survivor blocks) and where it is the faster
+// (few_blocks, words_in_frame_kernel). Both do the same three things; the block
 // kernel's way:
 //   1. select: the L + 1 smallest (screen word, position) pairs, the word
 //      being the float bits of the screen distance (the bits of a
@@ -1528,8 +1529,9 @@ hipError_t prepare_select_kernels() {
 // 13 / 12 / 11 / 13. A frame list names the few frames of a large batch that
 // the coarse keys could not decide (79 of those 32,768, each with 4,096 words
 // to read): their launch waits for one frame, not for the chip, and takes 51 /
-// 39 / 33 with the dense screen before it. The lists of all waves are merged in
-// two registers per lane: W * L <= 128.
+// 39 / 33 with the dense screen before it. (Past kLongWords words the block
+// kernel reads them: 200k words, 44 regions kept, 100 frames 1,751 -> 1,537 us.)
+// The lists of all waves are merged in two registers per lane: W * L <= 128.
 int frame_waves(const SelRerankArgs &a) {
   int W;
   if (a.blocks) W = a.long_bands ? (a.nq >= 8192 ? 4 : 8) : a.nq >= 4096 ? 2 : a.nq >= 1536 ? 4 : 8;
@@ -1606,8 +1608,9 @@ hipError_t launch_select_rerank(SelRerankArgs a, hipStream_t s) {
   }
   // the frame kernel, unless its lists do not hold the survivors or the slots
   const bool frame = a.blocks ? few_blocks(a)
-                     : a.keys || a.frame_list ? a.L <= kFrameL
-                                              : words_in_frame_kernel(a.L, a.nq, a.cap);
+                     : a.keys       ? a.L <= kFrameL
+                     : a.frame_list ? a.L <= kFrameL && (a.rlabel || a.cap <= kLongWords)
+                                    : words_in_frame_kernel(a.L, a.nq, a.cap);
   if (a.rlabel && !frame) return hipErrorInvalidValue;
   if (frame && a.m >= 1 && a.nslots <= kFrameSlots) {
     if (a.blocks) return launch_frame<kFineBlocks>(a, s);

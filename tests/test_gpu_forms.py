@@ -277,3 +277,55 @@ def test_coarse_words_of_long_lists_and_many_survivors(torch_cuda, R, n_reg, nqs
     idx, dist = (full[-1][key][:m].cpu().numpy() for key in ("idx", "dist"))
     st = judge_frames(idx, dist, None, ora, feats, region_of, R, q[:m], k)
     assert st["recall"] == 1.0
+
+
+@pytest.mark.parametrize("precision,n_reg,labels", [
+    ("bf16", 3, 0), ("bf16", 44, 0), ("fp8", 44, 0), ("bf16", 3, 3), ("bf16", 44, 3)])
+def test_coarse_keys_of_long_lists(torch_cuda, precision, n_reg, labels):
+    # 40,000 regions: 104 frames take dense words, 105 and 300 (and three labels of
+    # 35) the key lists, and those of them near the regions that hold the same
+    # rows, every tenth, the words: bitwise the fp32 screens' results, and 12
+    # frames against the oracle
+    rng = np.random.default_rng(47)
+    R, rows, d, k, nq = 40_000, 2, 64, 10, 300
+    feats = rng.standard_normal((R * rows, d)).astype(np.float32)
+    feats[:120 * rows] = np.tile(feats[:rows], (120, 1))
+    region_of = np.repeat(np.arange(R), rows).astype(np.int32)
+    xy = rng.uniform(0, 40, size=(len(feats), 2))
+    src = rng.integers(120 * rows, len(feats), nq)
+    src[::10] = 0
+    q = (feats[src] + 0.05 * rng.standard_normal((nq, d))).astype(np.float32)
+    of = (np.arange(R) * 3 // R).astype(np.int32)
+    db = hloc.HlocDB(feats, xy, mirrors=hloc.MIRROR_BF16 | hloc.MIRROR_FP8)
+    db.set_regions(region_of, R)
+    if labels:
+        db.set_region_labels(of, labels)
+
+    def run(frames, prec):
+        fd = torch_cuda.from_numpy(frames).cuda()
+        if labels:
+            offs = torch_cuda.arange(len(frames) + 1, dtype=torch_cuda.int32, device="cuda")
+            return db.query_labels(fd, k, n_reg, labels, offs, precision=prec)
+        return db.query(fd, k, n_reg, precision=prec)
+
+    for frames in (34, 35, 100) if labels else (104, 105, 300):
+        got = run(q[:frames], precision)
+        info = db.info()
+        say(f"[case] {precision} {frames} frames, {labels} labels: {info}")
+        ref = run(q[:frames], "fp32")
+        for key in got:
+            assert torch_cuda.equal(got[key], ref[key]), (frames, key)
+        assert (info["coarse_deferred"] >= len(src[:frames:10])) == (frames not in (34, 104))
+    db.close()
+    if labels:
+        ora = oracle.localize_labels(feats, xy, region_of, R, of, q[:12], np.arange(13), k, n_reg,
+                                     (0.5, 1, 0.0, 0))["per_label"]
+        sides = [(ref["idx"][p, :12], ref["dist"][p, :12]) for p in range(labels)]
+    else:
+        ora = [oracle.localize(feats, xy, region_of, R, q[:12], np.arange(13), k, n_reg,
+                               (0.5, 1, 0.0, 0))]
+        sides = [(ref["idx"][:12], ref["dist"][:12])]
+    for o, (idx, dist) in zip(ora, sides):
+        st = judge_frames(idx.cpu().numpy(), dist.cpu().numpy(), None, o, feats, region_of, R,
+                          q[:12], k)
+        assert st["recall"] == 1.0
