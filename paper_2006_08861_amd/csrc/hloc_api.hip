@@ -1378,11 +1378,13 @@ int hloc_query_batch_static_async(hloc_db *db, const float *q, int32_t nq, int32
   const Carve carve{base};
   CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
   // the schedule's item list takes less than the direct screen's frame lists,
-  // one fp8 vector per frame less than two
+  // one fp8 vector per frame less than two, the coarse words alone less than
+  // the key lists beside them
   const size_t limit = (size_t)HLOC_STATIC_SCRATCH_BYTES + kStaticCounterBytes;
-  if (used > limit && (p.direct || p.terms == 2)) {
+  if (used > limit && (p.direct || p.terms == 2 || words_do(db, p))) {
     p.direct = false;
     p.terms = 1;
+    if (words_do(db, p)) p.coarse_keys = false;
     used = 0;
     CHK(ensure_workspace(&ws, p, agg_internal, &used, &carve));
   }

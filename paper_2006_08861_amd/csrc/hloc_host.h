@@ -219,6 +219,12 @@ struct Plan {
   int32_t grid1, grid2;
 };
 
+// A batch on key lists whose dense words are as few as batches against fewer
+// regions store: where memory is short it takes those.
+inline bool words_do(const hloc_db *db, const Plan &p) {
+  return p.coarse_keys && (int64_t)p.nq * db->R <= kKeyWords;
+}
+
 void free_buf(WsBuf &b);
 // Grows b to at least bytes (waits for the device first: the old buffer may
 // be in use).

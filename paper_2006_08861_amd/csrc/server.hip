@@ -310,16 +310,23 @@ int hloc_server_create(hloc_db *db, const hloc_server_config *cfg, hloc_server *
   if (!srv) return fail(HLOC_ENOMEM, "host allocation failed");
   srv->db = db;
   srv->cfg = c;
-  {
+  auto size_slots = [&](int64_t *nslots) -> int {
     hloc_ws probe;
     probe.db = db;
     size_t ws_bytes = 0;
     CHK(ensure_workspace(&probe, full, false, &ws_bytes));
     srv->slot_bytes = ws_bytes + io_bytes(db, c.max_batch_frames, c.k);
+    *nslots = c.max_slots;
+    if (c.hbm_budget_bytes > 0)
+      *nslots = std::min<int64_t>(*nslots, c.hbm_budget_bytes / (int64_t)srv->slot_bytes);
+    return HLOC_OK;
+  };
+  int64_t nslots = 0;
+  CHK(size_slots(&nslots));
+  if (nslots < c.max_slots && words_do(db, full)) {
+    full.coarse_keys = false;  // as many slots as the budget has room for
+    CHK(size_slots(&nslots));
   }
-  int64_t nslots = c.max_slots;
-  if (c.hbm_budget_bytes > 0)
-    nslots = std::min<int64_t>(nslots, c.hbm_budget_bytes / (int64_t)srv->slot_bytes);
   if (nslots < 1) {
     const size_t need = srv->slot_bytes;
     delete srv;

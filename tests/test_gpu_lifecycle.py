@@ -185,6 +185,41 @@ def test_static_batch_that_fills_the_array(torch_cuda):
     db.close()
 
 
+@pytest.mark.parametrize("precision", ["bf16", "fp8"])
+def test_key_lists_where_memory_is_short(torch_cuda, precision):
+    # 300 frames against 40,000 regions: 48 MB of coarse words, with the key lists
+    # beside them more than the static array. Both the call on that array and a
+    # server whose budget is just below a slot with the lists run on the words
+    rng = np.random.default_rng(12)
+    R, rows, d, k, n_reg, nq = 40_000, 2, 64, 8, 5, 300
+    feats = rng.standard_normal((R * rows, d)).astype(np.float32)
+    q = (feats[rng.integers(0, len(feats), nq)]
+         + 0.05 * rng.standard_normal((nq, d))).astype(np.float32)
+    db = hloc.HlocDB(feats, rng.uniform(0, 40, size=(len(feats), 2)),
+                     mirrors=hloc.MIRROR_BF16 | hloc.MIRROR_FP8)
+    db.set_regions(np.repeat(np.arange(R), rows).astype(np.int32), R)
+    qd = torch_cuda.from_numpy(q).cuda()
+    ref = db.query(qd, k, n_reg, precision=precision)
+    say(f"[case] {precision} static batch of {nq} frames")
+    out = db.query_static(qd, k, n_reg, precision=precision)
+    torch_cuda.cuda.synchronize()
+    for key in out:
+        assert torch_cuda.equal(out[key], ref[key]), key
+    cfg = dict(max_batch_frames=nq, max_slots=1)
+    srv = hloc.Server(db, k, n_reg, precision, **cfg)
+    slot = srv.stats()["slot_bytes"]
+    srv.close()
+    srv = hloc.Server(db, k, n_reg, precision, hbm_budget_bytes=slot - 1, **cfg)
+    assert srv.stats()["slots"] == 1 and srv.stats()["slot_bytes"] < slot
+    say(f"[case] {precision} server requests")
+    for f in (nq, 7):
+        got = srv.wait(srv.submit(q[:f]), f)
+        assert (got["idx"] == ref["idx"][:f].cpu().numpy()).all()
+        assert (got["dist"] == ref["dist"][:f].cpu().numpy()).all()
+    srv.close()
+    db.close()
+
+
 def test_binding_inputs_on_another_stream(torch_cuda):
     # calls on a side stream with inputs that the binding copies (strided
     # frames, int64 offsets and lists) while the current stream is busy: the
